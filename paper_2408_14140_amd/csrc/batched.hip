@@ -659,21 +659,32 @@ k_finalize(Grid g, const int32_t* __restrict__ slot, const T* __restrict__ G,
                                 (lx + g.ngrow);
             const int64_t go =
                 (int64_t)s * 3 * TILE_CELLS + (lx & 7) + TILE * (yy + TILE * (cz & 7));
+            // every load before the first store: the stores may alias u0, so
+            // a load behind one would wait for it
+            T v[3], a[3];
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                const T v = s >= 0 ? G[go + c * TILE_CELLS] : T(0);
+                v[c] = s >= 0 ? G[go + c * TILE_CELLS] : T(0);
+                if (copy)
+                    a[c] = u0[off + c * g.cstride];
+            }
+            if (ustar && !copy) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    a[c] = v[c] != T(0) ? u0[off + c * g.cstride] : T(0);
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
                 const int64_t o = off + c * g.cstride;
                 // streaming stores: nothing here is read again by this kernel
                 if (f && !F_ACC)
-                    __builtin_nontemporal_store(v, &f[o]);
-                else if (f && v != T(0))
-                    f[o] += v;
-                if (!ustar)
-                    continue;
-                if (v != T(0))
-                    __builtin_nontemporal_store(u0[o] + tdt * v, &ustar[o]);
+                    __builtin_nontemporal_store(v[c], &f[o]);
+                else if (f && v[c] != T(0))
+                    f[o] += v[c];
+                if (ustar && v[c] != T(0))
+                    __builtin_nontemporal_store(a[c] + tdt * v[c], &ustar[o]);
                 else if (copy)
-                    __builtin_nontemporal_store(u0[o], &ustar[o]);
+                    __builtin_nontemporal_store(a[c], &ustar[o]);
             }
         }
         __syncthreads();
@@ -691,10 +702,28 @@ struct Pair<double> {
     typedef double type __attribute__((ext_vector_type(2)));
 };
 
+// Store of the finalize, streamed (nothing here is read again by this kernel)
+// or plain.  In place, streaming leaves more of the next loop's inputs in the
+// caches (interp_u0 of spheres1000_256: 137 us after streamed stores, 155 after
+// plain ones).  Out of place in FP32, box rows end inside a 32-byte sector, and
+// streamed pieces of a sector reach memory apart where the L2 joins plain ones
+// (finalize of spheres1000_256: 262 us plain, 301 streamed).  FP64 rows are
+// whole sectors: streamed (spheres8_256: 447 us, plain 455).
+// (A template parameter: the compiler merges the two stores of a branch at run
+// time into one plain store.)
+template <bool STREAM, typename V>
+__device__ inline void put(V v, V* p)
+{
+    if constexpr (STREAM)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
+
 // The same for an even ghost width, two neighbouring x cells per thread (every
 // pair starts on an even element of the box layout and of the tile slots):
 // one workgroup per (box, row of tiles in y, pair of z planes).
-template <typename T, bool F_ACC, bool MASK>
+template <typename T, bool F_ACC, bool MASK, bool STREAM>
 __global__ void __launch_bounds__(256)
 k_finalize_pairs(Grid g, const int32_t* __restrict__ slot, const T* __restrict__ G,
                  const uint64_t* __restrict__ tilemask, const T* u0, T* ustar, T* __restrict__ f,
@@ -738,28 +767,41 @@ k_finalize_pairs(Grid g, const int32_t* __restrict__ slot, const T* __restrict__
                                 (lx + g.ngrow);
             const int64_t go =
                 (int64_t)s * 3 * TILE_CELLS + (lx & 7) + TILE * (yy + TILE * ((cz0 + pz) & 7));
+            // every load before the first store: the stores may alias u0, so
+            // a load behind one would wait for it
+            V2 v[3], a[3], w[3];
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                V2 v = {T(0), T(0)};
+                v[c] = V2{T(0), T(0)};
                 if (s >= 0)
-                    v = *reinterpret_cast<const V2*>(G + go + c * TILE_CELLS);
+                    v[c] = *reinterpret_cast<const V2*>(G + go + c * TILE_CELLS);
+                if (copy)
+                    a[c] = *reinterpret_cast<const V2*>(u0 + off + c * g.cstride);
+            }
+            // in place, a pair without force keeps u0 and needs no traffic
+            bool force[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                force[c] = v[c].x != T(0) || v[c].y != T(0);
+                if (ustar && !copy) {
+                    a[c] = V2{T(0), T(0)};
+                    if (force[c])
+                        a[c] = *reinterpret_cast<const V2*>(u0 + off + c * g.cstride);
+                }
+                if (F_ACC && f && force[c])
+                    w[c] = *reinterpret_cast<const V2*>(f + off + c * g.cstride);
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
                 const int64_t o = off + c * g.cstride;
-                // in place, a pair without force keeps u0 and needs no traffic
-                const bool force = v.x != T(0) || v.y != T(0);
-                if (f && !F_ACC) {
-                    __builtin_nontemporal_store(v, reinterpret_cast<V2*>(f + o));
-                } else if (f && force) {
-                    V2 w = *reinterpret_cast<const V2*>(f + o);
-                    *reinterpret_cast<V2*>(f + o) = w + v;
-                }
-                if (!ustar) {
-                } else if (force) {
-                    const V2 a = *reinterpret_cast<const V2*>(u0 + o);
-                    __builtin_nontemporal_store(a + tdt * v, reinterpret_cast<V2*>(ustar + o));
-                } else if (copy) {
-                    const V2 a = *reinterpret_cast<const V2*>(u0 + o);
-                    __builtin_nontemporal_store(a, reinterpret_cast<V2*>(ustar + o));
-                }
+                if (f && !F_ACC)
+                    put<STREAM, V2>(v[c], reinterpret_cast<V2*>(f + o));
+                else if (f && force[c])
+                    *reinterpret_cast<V2*>(f + o) = w[c] + v[c];
+                if (ustar && force[c])
+                    put<STREAM, V2>(a[c] + tdt * v[c], reinterpret_cast<V2*>(ustar + o));
+                else if (copy)
+                    put<STREAM, V2>(a[c], reinterpret_cast<V2*>(ustar + o));
             }
         }
         __syncthreads();
@@ -772,9 +814,12 @@ static void finalize_kernel(bool pairs, unsigned grid, unsigned gp, hipStream_t 
                             const T* u0, T* ustar, T* f, double dt, int use_g, int copy,
                             const int32_t* flag, T* Fp, int64_t nF)
 {
-    if (pairs)
-        k_finalize_pairs<T, F_ACC, MASK><<<gp, 256, 0, st>>>(g, slot, G, tilemask, u0, ustar, f,
-                                                             dt, use_g, copy, flag, Fp, nF);
+    if (pairs && (sizeof(T) == 8 || !copy))
+        k_finalize_pairs<T, F_ACC, MASK, true><<<gp, 256, 0, st>>>(
+            g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF);
+    else if (pairs)
+        k_finalize_pairs<T, F_ACC, MASK, false><<<gp, 256, 0, st>>>(
+            g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF);
     else
         k_finalize<T, F_ACC, MASK><<<grid, 256, 0, st>>>(g, slot, G, tilemask, u0, ustar, f, dt,
                                                          use_g, copy, flag, Fp, nF);
