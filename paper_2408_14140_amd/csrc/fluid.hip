@@ -13,186 +13,22 @@
 //   L: the 7-point Laplacian; the convective term in central flux form with
 //       face values the mean of the two cells (the paper cites a Godunov
 //       scheme without giving it).
-// Both implicit solves are diagonal in Fourier space: a complex radix-2
-// Stockham FFT along each axis (one workgroup per line, the line in LDS), a
-// per-mode scaling, and the inverse.
+// Both implicit solves are diagonal in Fourier space: real-to-complex along x,
+// complex along y and z (fft.h), a per-mode scaling, and the way back.  A solve
+// is five passes over the half spectrum [z][y][pitch] (n/2 + 1 of its columns
+// used): the right-hand side is formed in the x pass, and the z pass goes
+// forward, scales and comes back without leaving the registers.
+#include <type_traits>
+
+#include "fft.h"
 #include "paths.h"
 
 namespace ibx {
 
-template <typename T>
-struct Cx {
-    T x, y;
-};
-
-// ------------------------------------------------------------------ FFT
-
-// W[q] = exp(-2 pi i q / n), q < n/2.
-template <typename T>
-__global__ void k_twiddles(int n, Cx<T>* W)
-{
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n / 2)
-        return;
-    double s, c;
-    sincospi(-2.0 * (double)q / (double)n, &s, &c);
-    W[q].x = (T)c;
-    W[q].y = (T)s;
-}
-
-// One line per workgroup (n/2 threads, one butterfly each per stage).  Line
-// L along `axis`: element j at base(L) + j * stride.  INV uses the conjugate
-// twiddles; every output is multiplied by `scale`.
-template <typename T, bool INV>
-__global__ void __launch_bounds__(512)
-k_fft_lines(Cx<T>* __restrict__ data, int n, int logn, int axis, const Cx<T>* __restrict__ W,
-            T scale)
-{
-    extern __shared__ unsigned char smem[];
-    Cx<T>* a = reinterpret_cast<Cx<T>*>(smem);
-    Cx<T>* b = a + n;
-    Cx<T>* w = b + n;
-    const int t = threadIdx.x;
-    const int64_t L = blockIdx.x;
-    const int64_t nn = (int64_t)n * n;
-    int64_t base, stride;
-    if (axis == 0) {
-        base = L * n;
-        stride = 1;
-    } else if (axis == 1) {
-        base = (L % n) + (L / n) * nn;
-        stride = n;
-    } else {
-        base = L;
-        stride = nn;
-    }
-    const int half = n >> 1;
-    for (int j = t; j < n; j += blockDim.x)
-        a[j] = data[base + j * stride];
-    for (int q = t; q < half; q += blockDim.x)
-        w[q] = W[q];
-    __syncthreads();
-    Cx<T>* src = a;
-    Cx<T>* dst = b;
-    for (int s = 0; s < logn; ++s) {
-        const int ns = 1 << s;                     // length of the transforms done so far
-        for (int i = t; i < half; i += blockDim.x) {
-            const int k = i & (ns - 1), jb = i >> s;
-            const Cx<T> u = src[i], v = src[i + half];
-            Cx<T> tw = w[k << (logn - 1 - s)];
-            if (INV)
-                tw.y = -tw.y;
-            Cx<T> vt;
-            vt.x = tw.x * v.x - tw.y * v.y;
-            vt.y = tw.x * v.y + tw.y * v.x;
-            const int o = (jb << (s + 1)) + k;
-            dst[o].x = u.x + vt.x;
-            dst[o].y = u.y + vt.y;
-            dst[o + ns].x = u.x - vt.x;
-            dst[o + ns].y = u.y - vt.y;
-        }
-        __syncthreads();
-        Cx<T>* tmp = src;
-        src = dst;
-        dst = tmp;
-    }
-    for (int j = t; j < n; j += blockDim.x) {
-        Cx<T> v = src[j];
-        v.x *= scale;
-        v.y *= scale;
-        data[base + j * stride] = v;
-    }
-}
-
-// Lines along y or z, 2^lx of them side by side (consecutive x) per
-// workgroup, so that every load and store moves 2^lx consecutive elements:
-// LDS holds [n][2^lx] (element j of line xi at j * 2^lx + xi).
-template <typename T, bool INV>
-__global__ void __launch_bounds__(256)
-k_fft_cols(Cx<T>* __restrict__ data, int n, int logn, int lx, int axis,
-           const Cx<T>* __restrict__ W, T scale)
-{
-    extern __shared__ unsigned char smem[];
-    const int X = 1 << lx;
-    Cx<T>* a = reinterpret_cast<Cx<T>*>(smem);
-    Cx<T>* b = a + (size_t)n * X;
-    Cx<T>* w = b + (size_t)n * X;
-    const int t = threadIdx.x;
-    const int64_t nn = (int64_t)n * n;
-    const int groups_x = n >> lx;
-    const int64_t x0 = (int64_t)(blockIdx.x % groups_x) << lx;
-    const int64_t other = blockIdx.x / groups_x;
-    const int64_t stride = axis == 1 ? n : nn;
-    const int64_t base = x0 + (axis == 1 ? other * nn : other * n);
-    const int half = n >> 1;
-    const int tot = n << lx;
-    for (int idx = t; idx < tot; idx += blockDim.x) {
-        const int j = idx >> lx, xi = idx & (X - 1);
-        a[idx] = data[base + xi + j * stride];
-    }
-    for (int q = t; q < half; q += blockDim.x)
-        w[q] = W[q];
-    __syncthreads();
-    Cx<T>* src = a;
-    Cx<T>* dst = b;
-    for (int s = 0; s < logn; ++s) {
-        const int ns = 1 << s;
-        for (int idx = t; idx < (half << lx); idx += blockDim.x) {
-            const int i = idx >> lx, xi = idx & (X - 1);
-            const int k = i & (ns - 1), jb = i >> s;
-            const Cx<T> u = src[(i << lx) + xi], v = src[((i + half) << lx) + xi];
-            Cx<T> tw = w[k << (logn - 1 - s)];
-            if (INV)
-                tw.y = -tw.y;
-            Cx<T> vt;
-            vt.x = tw.x * v.x - tw.y * v.y;
-            vt.y = tw.x * v.y + tw.y * v.x;
-            const int o = (jb << (s + 1)) + k;
-            dst[(o << lx) + xi].x = u.x + vt.x;
-            dst[(o << lx) + xi].y = u.y + vt.y;
-            dst[((o + ns) << lx) + xi].x = u.x - vt.x;
-            dst[((o + ns) << lx) + xi].y = u.y - vt.y;
-        }
-        __syncthreads();
-        Cx<T>* tmp = src;
-        src = dst;
-        dst = tmp;
-    }
-    for (int idx = t; idx < tot; idx += blockDim.x) {
-        const int j = idx >> lx, xi = idx & (X - 1);
-        Cx<T> v = src[idx];
-        v.x *= scale;
-        v.y *= scale;
-        data[base + xi + j * stride] = v;
-    }
-}
-
-template <typename T>
-static void fft3(Cx<T>* data, int n, int logn, const Cx<T>* W, bool inv, hipStream_t st)
-{
-    const unsigned lines = (unsigned)((int64_t)n * n);
-    const int threads = n / 2 < 64 ? 64 : (n / 2 > 512 ? 512 : n / 2);
-    const size_t lds = sizeof(Cx<T>) * (2 * (size_t)n + n / 2);
-    const T scale = inv ? (T)(1.0 / (double)n) : (T)1;
-    if (inv)
-        k_fft_lines<T, true><<<lines, threads, lds, st>>>(data, n, logn, 0, W, scale);
-    else
-        k_fft_lines<T, false><<<lines, threads, lds, st>>>(data, n, logn, 0, W, scale);
-    // y and z: as many side-by-side lines as keep the two LDS planes and the
-    // twiddles within 64 KiB (at most 16, at most n)
-    int lx = 0;
-    while (lx < 4 && (2 << lx) <= n &&
-           (2 * (size_t)n * (2u << lx) + n / 2) * sizeof(Cx<T>) <= 65536)
-        ++lx;
-    const size_t ldsc = sizeof(Cx<T>) * (2 * ((size_t)n << lx) + n / 2);
-    const unsigned groups = (unsigned)(((int64_t)n * n) >> lx);
-    for (int axis = 1; axis < 3; ++axis) {
-        if (inv)
-            k_fft_cols<T, true><<<groups, 256, ldsc, st>>>(data, n, logn, lx, axis, W, scale);
-        else
-            k_fft_cols<T, false><<<groups, 256, ldsc, st>>>(data, n, logn, lx, axis, W, scale);
-    }
-}
+// Complex values per x row of the half spectrum: n/2 + 1, padded so that a
+// group of columns starts on a 128-byte line (64 and above) and the three
+// velocity components fit the workspace (below).
+constexpr int spec_pitch(int n) { return n / 2 + (n >= 64 ? 16 : n >= 16 ? 8 : 4); }
 
 // ------------------------------------------------------------------ stencils
 
@@ -251,113 +87,52 @@ __device__ inline A grad_node_as(const T* __restrict__ p, const Idx& I, int i, i
     return (A(0.25) * hi - A(0.25) * lo) * inv_h;
 }
 
-// rhs of Eq. (31) for every cell, paired into two complex planes
+// rhs of Eq. (31) at a cell
 template <typename T>
-__global__ void k_predict_rhs(int n, T h, T rho, T a, T dt, T g0, T g1, T g2,
-                              const T* __restrict__ u, const T* __restrict__ p,
-                              Cx<T>* __restrict__ r)
-{
-    const int64_t N = (int64_t)n * n * n;
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N)
-        return;
-    const Idx I{n};
-    const int i = (int)(q & (n - 1)), j = (int)((q / n) & (n - 1)), k = (int)(q / ((int64_t)n * n));
-    const T inv_h = T(1) / h, inv_h2 = inv_h * inv_h;
-    const T g[3] = {g0, g1, g2};
-    T uc[3];
+struct PredictRhs {
+    int n;
+    T h, rho, a, dt, g0, g1, g2;
+    const T* u;
+    const T* p;
+    __device__ void cell(int i, int j, int k, T* rv) const
+    {
+        const int64_t N = (int64_t)n * n * n;
+        const Idx I{n};
+        const int64_t q = I.at(i, j, k);
+        const T inv_h = T(1) / h, inv_h2 = inv_h * inv_h;
+        const T g[3] = {g0, g1, g2};
+        T uc[3];
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-        uc[c] = u[c * N + q];
-    T conv[3] = {0, 0, 0}, lap[3] = {0, 0, 0};
+        for (int c = 0; c < 3; ++c)
+            uc[c] = u[c * N + q];
+        T conv[3] = {0, 0, 0}, lap[3] = {0, 0, 0};
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const int dp[3] = {d == 0, d == 1, d == 2};
-        const int64_t qp = I.at(i + dp[0], j + dp[1], k + dp[2]);
-        const int64_t qm = I.at(i - dp[0], j - dp[1], k - dp[2]);
-        T up[3], um[3];
+        for (int d = 0; d < 3; ++d) {
+            const int dp[3] = {d == 0, d == 1, d == 2};
+            const int64_t qp = I.at(i + dp[0], j + dp[1], k + dp[2]);
+            const int64_t qm = I.at(i - dp[0], j - dp[1], k - dp[2]);
+            T up[3], um[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                up[c] = u[c * N + qp];
+                um[c] = u[c * N + qm];
+            }
+            const T fd_p = T(0.5) * (uc[d] + up[d]), fd_m = T(0.5) * (um[d] + uc[d]);
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const T fp = fd_p * (T(0.5) * (uc[c] + up[c]));
+                const T fm = fd_m * (T(0.5) * (um[c] + uc[c]));
+                conv[c] += (fp - fm) * inv_h;
+                lap[c] += (up[c] - T(2) * uc[c] + um[c]) * inv_h2;
+            }
+        }
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            up[c] = u[c * N + qp];
-            um[c] = u[c * N + qm];
-        }
-        const T fd_p = T(0.5) * (uc[d] + up[d]), fd_m = T(0.5) * (um[d] + uc[d]);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const T fp = fd_p * (T(0.5) * (uc[c] + up[c]));
-            const T fm = fd_m * (T(0.5) * (um[c] + uc[c]));
-            conv[c] += (fp - fm) * inv_h;
-            lap[c] += (up[c] - T(2) * uc[c] + um[c]) * inv_h2;
+            const T gp = grad_node(p, I, i, j, k, c, inv_h);
+            rv[c] = uc[c] - dt * conv[c] - (dt / rho) * gp + a * lap[c] + dt * g[c];
         }
     }
-    T rv[3];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const T gp = grad_node(p, I, i, j, k, c, inv_h);
-        rv[c] = uc[c] - dt * conv[c] - (dt / rho) * gp + a * lap[c] + dt * g[c];
-    }
-    // the solve's operator is real, so two real fields share one complex
-    // transform: plane 0 holds x + i y, plane 1 holds z
-    Cx<T> v0, v1;
-    v0.x = rv[0];
-    v0.y = rv[1];
-    v1.x = rv[2];
-    v1.y = T(0);
-    r[q] = v0;
-    r[N + q] = v1;
-}
-
-// r^[c][k] /= 1 - a lam(k) on both planes, lam the 7-point eigenvalue of mode k
-template <typename T>
-__global__ void k_helmholtz_scale(int n, double h, double a, Cx<T>* __restrict__ r)
-{
-    const int64_t N = (int64_t)n * n * n;
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N)
-        return;
-    const int kk[3] = {(int)(q & (n - 1)), (int)((q / n) & (n - 1)), (int)(q / ((int64_t)n * n))};
-    double lam = 0.0;
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-        lam += (2.0 * cospi(2.0 * (double)kk[d] / (double)n) - 2.0) / (h * h);
-    const T f = (T)(1.0 / (1.0 - a * lam));
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        Cx<T> v = r[c * N + q];
-        v.x *= f;
-        v.y *= f;
-        r[c * N + q] = v;
-    }
-}
-
-// the three velocity components back from the two planes
-template <typename T>
-__global__ void k_unpair(int64_t N, const Cx<T>* __restrict__ r, T* __restrict__ out)
-{
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N)
-        return;
-    const Cx<T> v0 = r[q], v1 = r[N + q];
-    out[q] = v0.x;
-    out[N + q] = v0.y;
-    out[2 * N + q] = v1.x;
-}
-
-template <typename T>
-__global__ void k_real_part(int64_t m, const Cx<T>* __restrict__ r, T* __restrict__ out)
-{
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q < m)
-        out[q] = r[q].x;
-}
-
-template <typename T>
-__global__ void k_copy(int64_t m, const T* __restrict__ a, T* __restrict__ b)
-{
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q < m)
-        b[q] = a[q];
-}
+};
 
 // V = u*/dt + G p_old / rho (Eq. (ns_lp1)) for every cell
 template <typename T>
@@ -376,70 +151,6 @@ __global__ void k_proj_V(int n, T h, T rho, T dt, const T* __restrict__ us,
         V[c * N + q] = us[c * N + q] / dt + grad_node(p_old, I, i, j, k, c, inv_h) / rho;
 }
 
-// D V at every node, as complex numbers
-template <typename T>
-__global__ void k_proj_div(int n, T h, const T* __restrict__ V, Cx<T>* __restrict__ r)
-{
-    const int64_t N = (int64_t)n * n * n;
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N)
-        return;
-    const Idx I{n};
-    const int i = (int)(q & (n - 1)), j = (int)((q / n) & (n - 1)), k = (int)(q / ((int64_t)n * n));
-    const T inv_h = T(1) / h;
-    T div = 0;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const T* v = V + d * N;
-        const int e1 = d == 0 ? 1 : 0, e2 = d == 2 ? 1 : 2;
-        T s[2] = {0, 0};                         // layer of cells at -1 (s[0]) and 0 (s[1]) along d
-#pragma unroll
-        for (int l = 0; l < 2; ++l)
-#pragma unroll
-            for (int a = 0; a < 2; ++a)
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    int o[3];
-                    o[d] = l - 1;
-                    o[e1] = -a;
-                    o[e2] = -b;
-                    s[l] += v[I.at(i + o[0], j + o[1], k + o[2])];
-                }
-        div += (T(0.25) * s[1] - T(0.25) * s[0]) * inv_h;
-    }
-    Cx<T> c;
-    c.x = div;
-    c.y = T(0);
-    r[q] = c;
-}
-
-// r^[k] *= rho / sigma(k), or 0 where sigma (the symbol of D G) vanishes
-template <typename T>
-__global__ void k_proj_scale(int n, double h, double rho, Cx<T>* __restrict__ r)
-{
-    const int64_t N = (int64_t)n * n * n;
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N)
-        return;
-    const int kk[3] = {(int)(q & (n - 1)), (int)((q / n) & (n - 1)), (int)(q / ((int64_t)n * n))};
-    double s2[3], c2[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const double sv = sinpi((double)kk[d] / (double)n), cv = cospi((double)kk[d] / (double)n);
-        s2[d] = sv * sv;
-        c2[d] = cv * cv;
-    }
-    const double sig = -4.0 / (h * h) *
-                       (s2[0] * c2[1] * c2[2] + s2[1] * c2[0] * c2[2] + s2[2] * c2[0] * c2[1]);
-    // the largest |sigma| over all modes is 4/h^2 (one component at Nyquist)
-    const bool keep = fabs(sig) > 1e-10 * 4.0 / (h * h);
-    const T f = keep ? (T)(rho / sig) : T(0);
-    Cx<T> v = r[q];
-    v.x *= f;
-    v.y *= f;
-    r[q] = v;
-}
-
 // The FP32 projection with one step of iterative refinement.  The FFT solve
 // rounds its spectrum to FP32, and the low modes of that rounding are
 // amplified by up to the condition number of D G (about n^2/pi^2).  A second
@@ -450,42 +161,40 @@ __global__ void k_proj_scale(int n, double h, double rho, Cx<T>* __restrict__ r)
 //   W = V - G p1/rho;  d = rho (D G)^+ D W  (D W is the residual of p1)
 //   p = p1 + d;  u^{n+1} = dt (W - G d/rho)
 
-// D V at every node summed in A from V of type T, rounded to complex T
+// D V at a node, summed in A from V of type T, rounded to T
 template <typename T, typename A>
-__global__ void k_proj_div_as(int n, A h, const T* __restrict__ V, Cx<T>* __restrict__ r)
-{
-    const int64_t N = (int64_t)n * n * n;
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= N)
-        return;
-    const Idx I{n};
-    const int i = (int)(q & (n - 1)), j = (int)((q / n) & (n - 1)), k = (int)(q / ((int64_t)n * n));
-    const A inv_h = A(1) / h;
-    A div = 0;
+struct DivV {
+    int n;
+    A h;
+    const T* V;
+    __device__ void cell(int i, int j, int k, T* out) const
+    {
+        const int64_t N = (int64_t)n * n * n;
+        const Idx I{n};
+        const A inv_h = A(1) / h;
+        A div = 0;
 #pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const T* v = V + d * N;
-        const int e1 = d == 0 ? 1 : 0, e2 = d == 2 ? 1 : 2;
-        A sl[2] = {0, 0};
+        for (int d = 0; d < 3; ++d) {
+            const T* v = V + d * N;
+            const int e1 = d == 0 ? 1 : 0, e2 = d == 2 ? 1 : 2;
+            A sl[2] = {0, 0};                // layer of cells at -1 and 0 along d
 #pragma unroll
-        for (int l = 0; l < 2; ++l)
+            for (int l = 0; l < 2; ++l)
 #pragma unroll
-            for (int a = 0; a < 2; ++a)
+                for (int a = 0; a < 2; ++a)
 #pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    int o[3];
-                    o[d] = l - 1;
-                    o[e1] = -a;
-                    o[e2] = -b;
-                    sl[l] += (A)v[I.at(i + o[0], j + o[1], k + o[2])];
-                }
-        div += (A(0.25) * sl[1] - A(0.25) * sl[0]) * inv_h;
+                    for (int b = 0; b < 2; ++b) {
+                        int o[3];
+                        o[d] = l - 1;
+                        o[e1] = -a;
+                        o[e2] = -b;
+                        sl[l] += (A)v[I.at(i + o[0], j + o[1], k + o[2])];
+                    }
+            div += (A(0.25) * sl[1] - A(0.25) * sl[0]) * inv_h;
+        }
+        out[0] = (T)div;
     }
-    Cx<T> c;
-    c.x = (T)div;
-    c.y = T(0);
-    r[q] = c;
-}
+};
 
 // W = V - G p/rho, in place, formed in A
 template <typename T, typename A>
@@ -503,11 +212,11 @@ __global__ void k_proj_W(int n, A h, A rho, const T* __restrict__ p, T* __restri
         V[c * N + q] = (T)((A)V[c * N + q] - grad_node_as<A>(p, I, i, j, k, c, inv_h) / rho);
 }
 
-// u^{n+1} = dt (W - G d/rho) and p = p1 + d
+// u^{n+1} = dt (W - G d/rho) and p = p1 + d (pn holds p1)
 template <typename T, typename A>
 __global__ void k_proj_final_refined(int n, A h, A rho, A dt, const T* __restrict__ W,
-                                     const T* __restrict__ p1, const T* __restrict__ dl,
-                                     T* __restrict__ un, T* __restrict__ pn)
+                                     const T* __restrict__ dl, T* __restrict__ un,
+                                     T* __restrict__ pn)
 {
     const int64_t N = (int64_t)n * n * n;
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -519,7 +228,7 @@ __global__ void k_proj_final_refined(int n, A h, A rho, A dt, const T* __restric
 #pragma unroll
     for (int c = 0; c < 3; ++c)
         un[c * N + q] = (T)(dt * ((A)W[c * N + q] - grad_node_as<A>(dl, I, i, j, k, c, inv_h) / rho));
-    pn[q] = (T)((A)p1[q] + (A)dl[q]);
+    pn[q] = (T)((A)pn[q] + (A)dl[q]);
 }
 
 // u^{n+1} = dt (V - G p / rho), Eq. (ns_lp3)
@@ -537,6 +246,281 @@ __global__ void k_proj_final(int n, T h, T rho, T dt, const T* __restrict__ V, c
 #pragma unroll
     for (int c = 0; c < 3; ++c)
         un[c * N + q] = dt * (V[c * N + q] - grad_node(pr, I, i, j, k, c, inv_h) / rho);
+}
+
+// ------------------------------------------------------------------ passes
+
+// x pass forward: R rows of y of one z plane per workgroup, NC fields.  The
+// fields' values (src.cell) are formed cell by cell into LDS; rows 2 m and
+// 2 m + 1 of a field then share one complex transform, and its spectrum Z
+// splits into theirs, A = (Z(k) + Z*(-k)) / 2 and B = (Z(k) - Z*(-k)) / 2i.
+// Rows per workgroup: about 2048 cells of each field, so that the three
+// fields stay near 26 KB of LDS in FP32; fewer on grids of up to 64, whose
+// n^2 rows would leave compute units idle.
+template <int LOGN, int NC>
+struct XFwd {
+    static constexpr int R = LOGN <= 4 ? 2 : LOGN == 5 ? 4 : LOGN == 6 ? 8 : 2048 >> LOGN;
+    static constexpr int NL = NC * (R / 2);
+    static constexpr int NT =
+        NL * Line<LOGN>::TPL > 64 ? (NL * Line<LOGN>::TPL + 63) / 64 * 64 : 64;
+};
+
+template <typename T, int LOGN, int NC, typename Src>
+__global__ void __launch_bounds__((XFwd<LOGN, NC>::NT))
+k_fft_x_fwd(Src src, Cx<T>* __restrict__ spec)
+{
+    using L = Line<LOGN>;
+    using K = XFwd<LOGN, NC>;
+    constexpr int n = L::n, h = n / 2, PX = spec_pitch(n), R = K::R;
+    __shared__ __align__(16) Cx<T> buf[K::NL * L::LDS];
+    __shared__ Cx<T> W[n];
+    T* const real = reinterpret_cast<T*>(buf);        // [NC][R][n]
+    fill_twiddles<T, LOGN>(W);
+    const int j0 = (blockIdx.x * R) & (n - 1), k = (blockIdx.x * R) >> LOGN;
+    for (int q = threadIdx.x; q < R * n; q += K::NT) {
+        T v[NC];
+        src.cell(q & (n - 1), j0 + (q >> LOGN), k, v);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            real[c * R * n + q] = v[c];
+    }
+    __syncthreads();
+    const int line = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
+    const bool live = line < K::NL;
+    const int c = live ? line / (R / 2) : 0, m = live ? line % (R / 2) : 0;
+    Cx<T> v[L::E];
+#pragma unroll
+    for (int e = 0; e < L::E; ++e) {
+        const T* r = real + (c * R + 2 * m) * n + t + L::TPL * e;
+        v[e].x = r[0];
+        v[e].y = r[n];
+    }
+    Cx<T>* const lb = buf + (live ? line : 0) * L::LDS;
+    fft_line<T, false, LOGN>(v, t, live, lb, lds_at, W);
+    __syncthreads();
+    if (live) {
+#pragma unroll
+        for (int e = 0; e < L::E; ++e)
+            lb[lds_at(t + L::TPL * e)] = v[e];
+    }
+    __syncthreads();
+    if (!live)
+        return;
+    Cx<T>* const ra = spec + (((int64_t)c * n + k) * n + j0 + 2 * m) * PX;
+    Cx<T>* const rb = ra + PX;
+    auto split = [&](int q) {
+        const Cx<T> z = lb[lds_at(q)], w = lb[lds_at((n - q) & (n - 1))];
+        ra[q] = Cx<T>{T(0.5) * (z.x + w.x), T(0.5) * (z.y - w.y)};
+        rb[q] = Cx<T>{T(0.5) * (z.y + w.y), T(0.5) * (w.x - z.x)};
+    };
+#pragma unroll
+    for (int e = 0; e < L::E / 2; ++e)
+        split(t + L::TPL * e);
+    if (t == 0)
+        split(h);
+}
+
+// x pass back to reals: rows 2 m and 2 m + 1 as the real and imaginary part of
+// one complex transform, NL pairs per workgroup; out[c][z][y][x].
+template <int LOGN>
+struct XInv {
+    static constexpr int NL = LOGN <= 3 ? 4 : LOGN <= 6 ? 4 : 128 / Line<LOGN>::TPL;
+    static constexpr int NT = NL * Line<LOGN>::TPL > 64 ? NL * Line<LOGN>::TPL : 64;
+};
+
+template <typename T, int LOGN>
+__global__ void __launch_bounds__(XInv<LOGN>::NT)
+k_fft_x_inv(const Cx<T>* __restrict__ spec, T* __restrict__ out)
+{
+    using L = Line<LOGN>;
+    using K = XInv<LOGN>;
+    constexpr int n = L::n, h = n / 2, PX = spec_pitch(n);
+    __shared__ __align__(16) Cx<T> buf[K::NL * L::LDS];
+    __shared__ Cx<T> W[n];
+    fill_twiddles<T, LOGN>(W);
+    const int line = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
+    const bool live = line < K::NL;
+    const int64_t row = 2 * ((int64_t)blockIdx.x * K::NL + (live ? line : 0));
+    const Cx<T>* const ra = spec + row * PX;
+    const Cx<T>* const rb = ra + PX;
+    Cx<T> v[L::E];
+    // Z(k) = A(k) + i B(k), with A(n - k) = A*(k); A and B are real at 0 and h
+#pragma unroll
+    for (int e = 0; e < L::E / 2; ++e) {
+        const int k = t + L::TPL * e;
+        const Cx<T> a = ra[k], b = rb[k];
+        v[e].x = k == 0 ? a.x : a.x - b.y;
+        v[e].y = k == 0 ? b.x : a.y + b.x;
+    }
+#pragma unroll
+    for (int e = L::E / 2; e < L::E; ++e) {
+        const int k = n - (t + L::TPL * e);           // 1 .. h
+        const Cx<T> a = ra[k], b = rb[k];
+        v[e].x = k == h ? a.x : a.x + b.y;
+        v[e].y = k == h ? b.x : b.x - a.y;
+    }
+    __syncthreads();
+    fft_line<T, true, LOGN>(v, t, live, buf + (live ? line : 0) * L::LDS, lds_at, W);
+    if (!live)
+        return;
+    constexpr T scale = T(1.0 / n);
+    T* const oa = out + row * n + t;
+#pragma unroll
+    for (int e = 0; e < L::E; ++e) {
+        oa[L::TPL * e] = v[e].x * scale;
+        oa[n + L::TPL * e] = v[e].y * scale;
+    }
+}
+
+// y and z passes: C neighbouring columns per workgroup, so that an access
+// moves C consecutive values (128 bytes where the LDS allows it).
+template <typename T, int LOGN>
+struct Cols {
+    static constexpr int C = (LOGN <= 6 ? 8 : LOGN <= 8 ? 16 : LOGN == 9 ? 8 : 4) /
+                             (sizeof(T) == 8 && LOGN > 6 ? 2 : 1);
+    static constexpr int NT = C * Line<LOGN>::TPL;
+    static constexpr int groups = ((1 << LOGN) / 2 + C) / C;   // of the n/2 + 1 columns
+};
+
+template <typename T, int LOGN, bool INV>
+__global__ void __launch_bounds__((Cols<T, LOGN>::NT))
+k_fft_y(Cx<T>* __restrict__ spec)
+{
+    using L = Line<LOGN>;
+    using K = Cols<T, LOGN>;
+    constexpr int n = L::n, PX = spec_pitch(n), C = K::C;
+    __shared__ __align__(16) Cx<T> buf[L::LDS * C];
+    __shared__ Cx<T> W[n];
+    fill_twiddles<T, LOGN>(W);
+    const int c = threadIdx.x % C, t = threadIdx.x / C;
+    const int col = (int)(blockIdx.x % K::groups) * C + c;
+    const bool live = col <= n / 2;
+    Cx<T>* const p = spec + (int64_t)(blockIdx.x / K::groups) * n * PX + col;
+    Cx<T> v[L::E];
+    if (live) {
+#pragma unroll
+        for (int e = 0; e < L::E; ++e)
+            v[e] = p[(t + L::TPL * e) * PX];
+    }
+    __syncthreads();
+    fft_line<T, INV, LOGN>(v, t, live, buf, [&](int i) { return lds_at(i) * C + c; }, W);
+    if (!live)
+        return;
+    constexpr T scale = INV ? T(1.0 / n) : T(1);
+#pragma unroll
+    for (int e = 0; e < L::E; ++e) {
+        v[e].x *= scale;
+        v[e].y *= scale;
+        p[(t + L::TPL * e) * PX] = v[e];
+    }
+}
+
+// Symbols along one axis, formed once per workgroup for the three axes alike,
+// and a mode's factor from them.
+// 1 / (1 - a lam(k)), lam the eigenvalue of the 7-point Laplacian
+struct Helmholtz {
+    double h, a;
+    static constexpr int tables = 1;
+    template <int N>
+    __device__ void fill(double (*tab)[N], int k) const
+    {
+        tab[0][k] = (2.0 * cospi(2.0 * (double)k / (double)N) - 2.0) / (h * h);
+    }
+    template <int N>
+    __device__ double factor(double (*tab)[N], int kx, int ky, int kz) const
+    {
+        const double lam = tab[0][kx] + tab[0][ky] + tab[0][kz];
+        return 1.0 / (1.0 - a * lam);
+    }
+};
+
+// rho / sigma(k), or 0 where sigma (the symbol of D G) vanishes
+struct Poisson {
+    double h, rho;
+    static constexpr int tables = 2;
+    template <int N>
+    __device__ void fill(double (*tab)[N], int k) const
+    {
+        const double sv = sinpi((double)k / (double)N), cv = cospi((double)k / (double)N);
+        tab[0][k] = sv * sv;
+        tab[1][k] = cv * cv;
+    }
+    template <int N>
+    __device__ double factor(double (*tab)[N], int kx, int ky, int kz) const
+    {
+        const double sig =
+            -4.0 / (h * h) *
+            (tab[0][kx] * tab[1][ky] * tab[1][kz] + tab[0][ky] * tab[1][kx] * tab[1][kz] +
+             tab[0][kz] * tab[1][kx] * tab[1][ky]);
+        // the largest |sigma| over all modes is 4/h^2 (one component at Nyquist)
+        return fabs(sig) > 1e-10 * 4.0 / (h * h) ? rho / sig : 0.0;
+    }
+};
+
+// z pass: forward, times the symbol, back, for NC fields with one symbol.
+template <typename T, int LOGN, int NC, typename Sym>
+__global__ void __launch_bounds__((Cols<T, LOGN>::NT))
+k_fft_z_solve(Sym sym, Cx<T>* __restrict__ spec)
+{
+    using L = Line<LOGN>;
+    using K = Cols<T, LOGN>;
+    constexpr int n = L::n, PX = spec_pitch(n), C = K::C;
+    __shared__ __align__(16) Cx<T> buf[L::LDS * C];
+    __shared__ Cx<T> W[n];
+    __shared__ double tab[Sym::tables][n];
+    fill_twiddles<T, LOGN>(W);
+    for (int q = threadIdx.x; q < n; q += K::NT)
+        sym.template fill<n>(tab, q);
+    const int c = threadIdx.x % C, t = threadIdx.x / C;
+    const int col = (int)(blockIdx.x % K::groups) * C + c, ky = (int)(blockIdx.x / K::groups);
+    const bool live = col <= n / 2;
+    auto at = [&](int i) { return lds_at(i) * C + c; };
+    __syncthreads();
+    T f[L::E];
+    if (live) {
+#pragma unroll
+        for (int e = 0; e < L::E; ++e)
+            f[e] = (T)sym.template factor<n>(tab, col, ky, t + L::TPL * e) * T(1.0 / n);
+    }
+#pragma unroll 1
+    for (int m = 0; m < NC; ++m) {
+        Cx<T>* const p = spec + ((int64_t)m * n * n + ky) * PX + col;
+        Cx<T> v[L::E];
+        if (live) {
+#pragma unroll
+            for (int e = 0; e < L::E; ++e)
+                v[e] = p[(int64_t)(t + L::TPL * e) * n * PX];
+        }
+        fft_line<T, false, LOGN>(v, t, live, buf, at, W);
+        if (live) {
+#pragma unroll
+            for (int e = 0; e < L::E; ++e) {
+                v[e].x *= f[e];
+                v[e].y *= f[e];
+            }
+        }
+        fft_line<T, true, LOGN>(v, t, live, buf, at, W);
+        if (live) {
+#pragma unroll
+            for (int e = 0; e < L::E; ++e)
+                p[(int64_t)(t + L::TPL * e) * n * PX] = v[e];
+        }
+    }
+}
+
+// out = the inverse of sym applied to NC fields given cell by cell.
+template <typename T, int LOGN, int NC, typename Src, typename Sym>
+static void solve(const Src& src, const Sym& sym, Cx<T>* spec, T* out, hipStream_t st)
+{
+    constexpr unsigned n = 1u << LOGN;
+    using X = XFwd<LOGN, NC>;
+    using XI = XInv<LOGN>;
+    using K = Cols<T, LOGN>;
+    k_fft_x_fwd<T, LOGN, NC, Src><<<n * n / X::R, X::NT, 0, st>>>(src, spec);
+    k_fft_y<T, LOGN, false><<<K::groups * n * NC, K::NT, 0, st>>>(spec);
+    k_fft_z_solve<T, LOGN, NC, Sym><<<K::groups * n, K::NT, 0, st>>>(sym, spec);
+    k_fft_y<T, LOGN, true><<<K::groups * n * NC, K::NT, 0, st>>>(spec);
+    k_fft_x_inv<T, LOGN><<<NC * n * n / (2 * XI::NL), XI::NT, 0, st>>>(spec, out);
 }
 
 // ------------------------------------------------------------------ layouts
@@ -593,48 +577,75 @@ static int log2_exact(int32_t n)
     return (1 << l) == n ? l : -1;
 }
 
-template <typename T>
-struct FluidWs {
-    Cx<T>* r;      // [2][N] complex
-    T* V;          // [3][N]
-    Cx<T>* W;      // [n/2] twiddles
-};
+// Reals of the workspace: a predictor holds the half spectra of three fields, a
+// projection V, one half spectrum and (FP32) the correction.
+static size_t fluid_reals(int32_t n) { return 7 * (size_t)n * n * n; }
 
-template <typename T>
-static FluidWs<T> carve_fluid(int32_t n, void* ws, size_t bytes, size_t* need)
+template <typename T, int LOGN>
+static void predict_n(double h, double rho, double mu, double dt, const double* grav, const T* u,
+                      const T* p, T* ustar, T* ws, hipStream_t st)
 {
-    Carver cv(ws, bytes);
-    const size_t N = (size_t)n * n * n;
-    FluidWs<T> w;
-    w.r = cv.take<Cx<T>>(2 * N);
-    w.V = cv.take<T>(3 * N);
-    w.W = cv.take<Cx<T>>(n / 2 > 0 ? n / 2 : 1);
-    *need = cv.used;
-    return w;
+    constexpr int n = 1 << LOGN;
+    static_assert(3 * 2 * (size_t)n * n * spec_pitch(n) <= 7 * (size_t)n * n * n,
+                  "three half spectra fit the workspace");
+    const double a = 0.5 * (mu / rho) * dt;
+    const PredictRhs<T> src{n,          (T)h,       (T)rho,     (T)a, (T)dt,
+                            (T)grav[0], (T)grav[1], (T)grav[2], u,    p};
+    solve<T, LOGN, 3>(src, Helmholtz{h, a}, reinterpret_cast<Cx<T>*>(ws), ustar, st);
+}
+
+template <typename T, int LOGN>
+static void project_n(double h, double rho, double dt, const T* ustar, const T* p_old, T* u_new,
+                      T* p_new, T* ws, hipStream_t st)
+{
+    constexpr int n = 1 << LOGN;
+    constexpr size_t N = (size_t)n * n * n, S = 2 * (size_t)n * n * spec_pitch(n);
+    static_assert(3 * N + S + N <= 7 * N, "V, a half spectrum and the correction fit");
+    const unsigned gc = (unsigned)((N + 255) / 256);
+    T* V = ws;
+    Cx<T>* spec = reinterpret_cast<Cx<T>*>(ws + 3 * N);
+    T* dl = ws + 3 * N + S;
+    const Poisson sym{h, rho};
+    // p_old, which p_new may overwrite, is read by the first kernel only
+    k_proj_V<T><<<gc, 256, 0, st>>>(n, (T)h, (T)rho, (T)dt, ustar, p_old, V);
+    if constexpr (sizeof(T) == 4) {
+        // FP32: two solves, the divergences and the residual summed in FP64
+        const DivV<T, double> div{n, h, V};
+        solve<T, LOGN, 1>(div, sym, spec, p_new, st);
+        k_proj_W<T, double><<<gc, 256, 0, st>>>(n, h, rho, p_new, V);
+        solve<T, LOGN, 1>(div, sym, spec, dl, st);
+        k_proj_final_refined<T, double><<<gc, 256, 0, st>>>(n, h, rho, dt, V, dl, u_new, p_new);
+    } else {
+        solve<T, LOGN, 1>(DivV<T, T>{n, (T)h, V}, sym, spec, p_new, st);
+        k_proj_final<T><<<gc, 256, 0, st>>>(n, (T)h, (T)rho, (T)dt, V, p_new, u_new);
+    }
+}
+
+// fn<LOGN>() for the grid's LOGN (8 <= n <= 1024 was checked).
+template <typename Fn>
+static void for_logn(int32_t n, Fn fn)
+{
+    switch (log2_exact(n)) {
+    case 3: fn(std::integral_constant<int, 3>()); break;
+    case 4: fn(std::integral_constant<int, 4>()); break;
+    case 5: fn(std::integral_constant<int, 5>()); break;
+    case 6: fn(std::integral_constant<int, 6>()); break;
+    case 7: fn(std::integral_constant<int, 7>()); break;
+    case 8: fn(std::integral_constant<int, 8>()); break;
+    case 9: fn(std::integral_constant<int, 9>()); break;
+    case 10: fn(std::integral_constant<int, 10>()); break;
+    }
 }
 
 template <typename T>
 static int predict_t(int32_t n, double h, double rho, double mu, double dt, const double* grav,
                      const T* u, const T* p, T* ustar, void* ws, size_t ws_bytes, hipStream_t st)
 {
-    size_t need = 0;
-    carve_fluid<T>(n, nullptr, 0, &need);
-    if (!ws || ws_bytes < need)
+    if (!ws || ws_bytes < fluid_reals(n) * sizeof(T))
         return IB_EWORKSPACE;
-    FluidWs<T> w = carve_fluid<T>(n, ws, ws_bytes, &need);
-    const int logn = log2_exact(n);
-    const int64_t N = (int64_t)n * n * n;
-    const unsigned gc = (unsigned)((N + 255) / 256);
-    const double a = 0.5 * (mu / rho) * dt;
-    k_twiddles<T><<<(unsigned)((n / 2 + 255) / 256), 256, 0, st>>>(n, w.W);
-    k_predict_rhs<T><<<gc, 256, 0, st>>>(n, (T)h, (T)rho, (T)a, (T)dt, (T)grav[0], (T)grav[1],
-                                         (T)grav[2], u, p, w.r);
-    for (int c = 0; c < 2; ++c)
-        fft3<T>(w.r + c * N, n, logn, w.W, false, st);
-    k_helmholtz_scale<T><<<gc, 256, 0, st>>>(n, h, a, w.r);
-    for (int c = 0; c < 2; ++c)
-        fft3<T>(w.r + c * N, n, logn, w.W, true, st);
-    k_unpair<T><<<gc, 256, 0, st>>>(N, w.r, ustar);
+    for_logn(n, [&](auto L) {
+        predict_n<T, L.value>(h, rho, mu, dt, grav, u, p, ustar, (T*)ws, st);
+    });
     return launch_status();
 }
 
@@ -642,46 +653,11 @@ template <typename T>
 static int project_t(int32_t n, double h, double rho, double dt, const T* ustar, const T* p_old,
                      T* u_new, T* p_new, void* ws, size_t ws_bytes, hipStream_t st)
 {
-    size_t need = 0;
-    carve_fluid<T>(n, nullptr, 0, &need);
-    if (!ws || ws_bytes < need)
+    if (!ws || ws_bytes < fluid_reals(n) * sizeof(T))
         return IB_EWORKSPACE;
-    FluidWs<T> w = carve_fluid<T>(n, ws, ws_bytes, &need);
-    const int logn = log2_exact(n);
-    const int64_t N = (int64_t)n * n * n;
-    const unsigned gc = (unsigned)((N + 255) / 256);
-    k_twiddles<T><<<(unsigned)((n / 2 + 255) / 256), 256, 0, st>>>(n, w.W);
-    if constexpr (sizeof(T) == 4) {
-        // FP32: two solves, the divergences and the residual summed in FP64;
-        // p1 and the correction as reals in the second complex plane
-        T* p1 = reinterpret_cast<T*>(w.r + N);
-        T* dl = p1 + N;
-        k_proj_V<T><<<gc, 256, 0, st>>>(n, (T)h, (T)rho, (T)dt, ustar, p_old, w.V);
-        k_proj_div_as<T, double><<<gc, 256, 0, st>>>(n, h, w.V, w.r);
-        fft3<T>(w.r, n, logn, w.W, false, st);
-        k_proj_scale<T><<<gc, 256, 0, st>>>(n, h, rho, w.r);
-        fft3<T>(w.r, n, logn, w.W, true, st);
-        k_real_part<T><<<gc, 256, 0, st>>>(N, w.r, p1);
-        k_proj_W<T, double><<<gc, 256, 0, st>>>(n, h, rho, p1, w.V);
-        k_proj_div_as<T, double><<<gc, 256, 0, st>>>(n, h, w.V, w.r);
-        fft3<T>(w.r, n, logn, w.W, false, st);
-        k_proj_scale<T><<<gc, 256, 0, st>>>(n, h, rho, w.r);
-        fft3<T>(w.r, n, logn, w.W, true, st);
-        k_real_part<T><<<gc, 256, 0, st>>>(N, w.r, dl);
-        k_proj_final_refined<T, double><<<gc, 256, 0, st>>>(n, h, rho, dt, w.V, p1, dl, u_new,
-                                                             p_new);
-        return launch_status();
-    }
-    k_proj_V<T><<<gc, 256, 0, st>>>(n, (T)h, (T)rho, (T)dt, ustar, p_old, w.V);
-    k_proj_div<T><<<gc, 256, 0, st>>>(n, (T)h, w.V, w.r);
-    fft3<T>(w.r, n, logn, w.W, false, st);
-    k_proj_scale<T><<<gc, 256, 0, st>>>(n, h, rho, w.r);
-    fft3<T>(w.r, n, logn, w.W, true, st);
-    // p as reals in the (unused) second complex plane, then u^{n+1}, then p_new
-    T* pr = reinterpret_cast<T*>(w.r + N);
-    k_real_part<T><<<gc, 256, 0, st>>>(N, w.r, pr);
-    k_proj_final<T><<<gc, 256, 0, st>>>(n, (T)h, (T)rho, (T)dt, w.V, pr, u_new);
-    k_copy<T><<<gc, 256, 0, st>>>(N, pr, p_new);
+    for_logn(n, [&](auto L) {
+        project_n<T, L.value>(h, rho, dt, ustar, p_old, u_new, p_new, (T*)ws, st);
+    });
     return launch_status();
 }
 
@@ -702,12 +678,7 @@ extern "C" size_t ib_fluid_workspace(int32_t n, ib_prec prec)
 {
     if (check_fluid(n, 1.0, prec))
         return 0;
-    size_t need = 0;
-    if (prec == IB_F64)
-        carve_fluid<double>(n, nullptr, 0, &need);
-    else
-        carve_fluid<float>(n, nullptr, 0, &need);
-    return need;
+    return fluid_reals(n) * (prec == IB_F64 ? sizeof(double) : sizeof(float));
 }
 
 extern "C" int ib_fluid_predict(int32_t n, double h, ib_prec prec, double rho, double mu,

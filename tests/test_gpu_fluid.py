@@ -76,6 +76,48 @@ def test_predict_and_project_match_oracle(dev, n, dtype):
     assert np.abs(div).max() <= (1e-4 if dtype == "f32" else 1e-11) * scale
 
 
+@pytest.mark.parametrize("n,dtype", [(16, "f32"), (16, "f64"), (128, "f32"), (128, "f64")])
+def test_every_line_plan_matches_oracle(dev, n, dtype):
+    """The line lengths whose transform splits into radices that the sizes
+    above do not use (4 x 4 and 16 x 8), at the same tolerances."""
+    test_predict_and_project_match_oracle(dev, n, dtype)
+
+
+@pytest.mark.parametrize("n,dtype", [(512, "f32"), (512, "f64"), (1024, "f32")])
+def test_long_lines_recover_a_known_pressure(dev, n, dtype):
+    """u* = dt G phi / rho for one Fourier mode phi per axis: p = phi and u = 0
+    (grids beyond what the oracle solves in a test; three-pass lines)."""
+    import torch
+
+    import paper_2408_14140_amd as ibx
+    announce(f"projection of a known pressure n={n} {dtype}")
+    tdt = torch.float64 if dtype == "f64" else torch.float32
+    h, rho, dt = 1.0 / n, 1.3, 0.5 / n
+    th = 2.0 * np.pi / n * torch.arange(n, dtype=torch.float64, device=dev)
+    # phi = cos(3 x + 2 y + z) on the nodes; G phi of a plane wave is the wave
+    # at the cell centre times -2 sin(th_d / 2) / h prod_{e != d} cos(th_e / 2)
+    kk = (3, 2, 1)
+    half = [np.pi * k / n for k in kk]
+    amp = [-2.0 * np.sin(half[d]) / h * np.prod([np.cos(half[e]) for e in range(3) if e != d])
+           for d in range(3)]
+    us = torch.empty((3, n, n, n), dtype=tdt, device=dev)
+    phi = torch.empty((n, n, n), dtype=tdt, device=dev)
+    for k in range(n):
+        ph = (kk[0] * th)[None, :] + (kk[1] * th)[:, None] + kk[2] * th[k]
+        phi[k] = torch.cos(ph).to(tdt)
+        s = torch.sin(ph + sum(half))
+        for d in range(3):
+            us[d, k] = (dt / rho * amp[d] * s).to(tdt)
+    fl = ibx.Fluid(n, h, tdt, dev)
+    zero = torch.zeros_like(phi)
+    scale = float(us.abs().max())
+    u1, p1 = fl.project(us, zero, rho, dt, u_out=us, p_out=zero)
+    torch.cuda.synchronize()
+    tol = TOL64 * _kappa(n) if dtype == "f64" else TOL32
+    assert float((p1 - phi).abs().max()) <= tol
+    assert float(u1.abs().max()) <= tol * scale
+
+
 def test_in_place_aliasing(dev):
     import torch
 
