@@ -32,123 +32,162 @@ constexpr int spec_pitch(int n) { return n / 2 + (n >= 64 ? 16 : n >= 16 ? 8 : 4
 
 // ------------------------------------------------------------------ stencils
 
-struct Idx {
-    int n;
-    __device__ int64_t at(int i, int j, int k) const
-    {
-        i &= n - 1;
-        j &= n - 1;
-        k &= n - 1;
-        return (int64_t)i + (int64_t)n * ((int64_t)j + (int64_t)n * k);
-    }
+// The stencils take 16 bytes of x cells per thread (4 in FP32, 2 in FP64) and
+// one or two neighbours at the ends, so a cell costs about a quarter of the
+// loads it would alone.  n is a multiple of 8, so a segment never wraps; rows
+// may start at any element of the caller's arrays (global vector loads need
+// element alignment only).
+template <typename T>
+struct Wide {
+    static constexpr int W = 16 / sizeof(T);
+    typedef T type __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));
 };
 
-// component d of G p at cell (i, j, k)
+// v[0 .. LO) the LO cells before cell i of a row, then cells i .. i + W - 1,
+// then the HI cells after them (LO and HI 0 or 1, wrapped).
+template <typename T, int LO, int HI>
+__device__ inline void load_row(const T* row, int n, int i, T (&v)[LO + Wide<T>::W + HI])
+{
+    constexpr int W = Wide<T>::W;
+    const typename Wide<T>::type m = *reinterpret_cast<const typename Wide<T>::type*>(row + i);
+    if (LO)
+        v[0] = row[(i - 1) & (n - 1)];
+#pragma unroll
+    for (int x = 0; x < W; ++x)
+        v[LO + x] = m[x];
+    if (HI)
+        v[LO + W + HI - 1] = row[(i + W) & (n - 1)];
+}
+
 template <typename T>
-__device__ inline T grad_node(const T* __restrict__ p, const Idx& I, int i, int j, int k, int d,
-                              T inv_h)
+__device__ inline void store_row(T* at, const T (&v)[Wide<T>::W])
 {
-    int o[3] = {0, 0, 0};
-    T lo = 0, hi = 0;
-    const int e1 = d == 0 ? 1 : 0, e2 = d == 2 ? 1 : 2;
+    typename Wide<T>::type m;
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            o[e1] = a;
-            o[e2] = b;
-            o[d] = 0;
-            lo += p[I.at(i + o[0], j + o[1], k + o[2])];
-            o[d] = 1;
-            hi += p[I.at(i + o[0], j + o[1], k + o[2])];
-        }
-    return (T(0.25) * hi - T(0.25) * lo) * inv_h;
+    for (int x = 0; x < Wide<T>::W; ++x)
+        m[x] = v[x];
+    *reinterpret_cast<typename Wide<T>::type*>(at) = m;
 }
 
-// the same, read from values of type T and formed in A
-template <typename A, typename T>
-__device__ inline A grad_node_as(const T* __restrict__ p, const Idx& I, int i, int j, int k, int d,
-                                 A inv_h)
+// First element of row (j, k), wrapped.
+__device__ inline int64_t row_at(int n, int j, int k)
 {
-    int o[3] = {0, 0, 0};
-    A lo = 0, hi = 0;
-    const int e1 = d == 0 ? 1 : 0, e2 = d == 2 ? 1 : 2;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            o[e1] = a;
-            o[e2] = b;
-            o[d] = 0;
-            lo += (A)p[I.at(i + o[0], j + o[1], k + o[2])];
-            o[d] = 1;
-            hi += (A)p[I.at(i + o[0], j + o[1], k + o[2])];
-        }
-    return (A(0.25) * hi - A(0.25) * lo) * inv_h;
+    return (int64_t)n * ((j & (n - 1)) + (int64_t)n * (k & (n - 1)));
 }
 
-// rhs of Eq. (31) at a cell
+// G p at the W cells from (i, j, k), read from values of type T, formed in A,
+// times scale (1/h, or 1/(h rho)).
+template <typename T, typename A>
+__device__ inline void grad_cells(const T* p, int n, int i, int j, int k, A scale,
+                                  A (&g)[3][Wide<T>::W])
+{
+    constexpr int W = Wide<T>::W;
+    A yl[W + 1], yh[W + 1], zd[W + 1];       // sums over z at j, at j + 1; difference along z
+    T a[W + 1], b[W + 1], c[W + 1], d[W + 1];
+    load_row<T, 0, 1>(p + row_at(n, j, k), n, i, a);
+    load_row<T, 0, 1>(p + row_at(n, j + 1, k), n, i, b);
+    load_row<T, 0, 1>(p + row_at(n, j, k + 1), n, i, c);
+    load_row<T, 0, 1>(p + row_at(n, j + 1, k + 1), n, i, d);
+#pragma unroll
+    for (int x = 0; x <= W; ++x) {
+        yl[x] = (A)a[x] + (A)c[x];
+        yh[x] = (A)b[x] + (A)d[x];
+        zd[x] = ((A)c[x] + (A)d[x]) - ((A)a[x] + (A)b[x]);
+    }
+    const A q = A(0.25) * scale;
+#pragma unroll
+    for (int x = 0; x < W; ++x) {
+        g[0][x] = ((yl[x + 1] + yh[x + 1]) - (yl[x] + yh[x])) * q;
+        g[1][x] = ((yh[x] + yh[x + 1]) - (yl[x] + yl[x + 1])) * q;
+        g[2][x] = (zd[x] + zd[x + 1]) * q;
+    }
+}
+
+// rhs of Eq. (31)
 template <typename T>
 struct PredictRhs {
     int n;
     T h, rho, a, dt, g0, g1, g2;
     const T* u;
     const T* p;
-    __device__ void cell(int i, int j, int k, T* rv) const
+    __device__ void cells(int i, int j, int k, T (&rv)[3][Wide<T>::W]) const
     {
+        constexpr int W = Wide<T>::W;
         const int64_t N = (int64_t)n * n * n;
-        const Idx I{n};
-        const int64_t q = I.at(i, j, k);
         const T inv_h = T(1) / h, inv_h2 = inv_h * inv_h;
         const T g[3] = {g0, g1, g2};
-        T uc[3];
+        T uc[3][W + 2];
 #pragma unroll
         for (int c = 0; c < 3; ++c)
-            uc[c] = u[c * N + q];
-        T conv[3] = {0, 0, 0}, lap[3] = {0, 0, 0};
+            load_row<T, 1, 1>(u + c * N + row_at(n, j, k), n, i, uc[c]);
+        T conv[3][W], lap[3][W];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            const int dp[3] = {d == 0, d == 1, d == 2};
-            const int64_t qp = I.at(i + dp[0], j + dp[1], k + dp[2]);
-            const int64_t qm = I.at(i - dp[0], j - dp[1], k - dp[2]);
-            T up[3], um[3];
+            T um[3][W], up[3][W];
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                up[c] = u[c * N + qp];
-                um[c] = u[c * N + qm];
-            }
-            const T fd_p = T(0.5) * (uc[d] + up[d]), fd_m = T(0.5) * (um[d] + uc[d]);
+                if (d == 0) {
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const T fp = fd_p * (T(0.5) * (uc[c] + up[c]));
-                const T fm = fd_m * (T(0.5) * (um[c] + uc[c]));
-                conv[c] += (fp - fm) * inv_h;
-                lap[c] += (up[c] - T(2) * uc[c] + um[c]) * inv_h2;
+                    for (int x = 0; x < W; ++x) {
+                        um[c][x] = uc[c][x];
+                        up[c][x] = uc[c][x + 2];
+                    }
+                } else {
+                    const int dj = d == 1, dk = d == 2;
+                    load_row<T, 0, 0>(u + c * N + row_at(n, j - dj, k - dk), n, i, um[c]);
+                    load_row<T, 0, 0>(u + c * N + row_at(n, j + dj, k + dk), n, i, up[c]);
+                }
+            }
+#pragma unroll
+            for (int x = 0; x < W; ++x) {
+                const T fd_p = T(0.5) * (uc[d][x + 1] + up[d][x]);
+                const T fd_m = T(0.5) * (um[d][x] + uc[d][x + 1]);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const T v = uc[c][x + 1];
+                    const T fp = fd_p * (T(0.5) * (v + up[c][x]));
+                    const T fm = fd_m * (T(0.5) * (um[c][x] + v));
+                    const T cv = (fp - fm) * inv_h;
+                    const T lp = (up[c][x] - T(2) * v + um[c][x]) * inv_h2;
+                    conv[c][x] = d == 0 ? cv : conv[c][x] + cv;
+                    lap[c][x] = d == 0 ? lp : lap[c][x] + lp;
+                }
             }
         }
+        T gp[3][W];
+        grad_cells<T, T>(p, n, i, j, k, inv_h, gp);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            const T gp = grad_node(p, I, i, j, k, c, inv_h);
-            rv[c] = uc[c] - dt * conv[c] - (dt / rho) * gp + a * lap[c] + dt * g[c];
-        }
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+            for (int x = 0; x < W; ++x)
+                rv[c][x] = uc[c][x + 1] - dt * conv[c][x] - (dt / rho) * gp[c][x] +
+                           a * lap[c][x] + dt * g[c];
     }
 };
 
-// V = u*/dt + G p_old / rho (Eq. (ns_lp1)) for every cell
+// V = u*/dt + G p_old / rho (Eq. (ns_lp1))
 template <typename T>
-__global__ void k_proj_V(int n, T h, T rho, T dt, const T* __restrict__ us,
-                         const T* __restrict__ p_old, T* __restrict__ V)
+__global__ void __launch_bounds__(256)
+k_proj_V(int n, T h, T rho, T dt, const T* __restrict__ us, const T* __restrict__ p_old,
+         T* __restrict__ V)
 {
+    constexpr int W = Wide<T>::W;
     const int64_t N = (int64_t)n * n * n;
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t q = ((int64_t)blockIdx.x * 256 + threadIdx.x) * W;
     if (q >= N)
         return;
-    const Idx I{n};
     const int i = (int)(q & (n - 1)), j = (int)((q / n) & (n - 1)), k = (int)(q / ((int64_t)n * n));
-    const T inv_h = T(1) / h;
+    T g[3][W];
+    grad_cells<T, T>(p_old, n, i, j, k, T(1) / h, g);
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-        V[c * N + q] = us[c * N + q] / dt + grad_node(p_old, I, i, j, k, c, inv_h) / rho;
+    for (int c = 0; c < 3; ++c) {
+        T v[W];
+        load_row<T, 0, 0>(us + c * N + q - i, n, i, v);
+#pragma unroll
+        for (int x = 0; x < W; ++x)
+            v[x] = v[x] / dt + g[c][x] / rho;
+        store_row(V + c * N + q, v);
+    }
 }
 
 // The FP32 projection with one step of iterative refinement.  The FFT solve
@@ -161,97 +200,127 @@ __global__ void k_proj_V(int n, T h, T rho, T dt, const T* __restrict__ us,
 //   W = V - G p1/rho;  d = rho (D G)^+ D W  (D W is the residual of p1)
 //   p = p1 + d;  u^{n+1} = dt (W - G d/rho)
 
-// D V at a node, summed in A from V of type T, rounded to T
+// D V at the nodes, summed in A from V of type T, rounded to T
 template <typename T, typename A>
 struct DivV {
     int n;
     A h;
     const T* V;
-    __device__ void cell(int i, int j, int k, T* out) const
+    __device__ void cells(int i, int j, int k, T (&out)[1][Wide<T>::W]) const
     {
+        constexpr int W = Wide<T>::W;
         const int64_t N = (int64_t)n * n * n;
-        const Idx I{n};
-        const A inv_h = A(1) / h;
-        A div = 0;
+        const A q = A(0.25) / h;
+        A sx[W + 1], syz[W + 1];             // x sums of the four rows; y and z differences
+        T r[4][W + 1];
+        auto rows = [&](int c) {
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const T* v = V + d * N;
-            const int e1 = d == 0 ? 1 : 0, e2 = d == 2 ? 1 : 2;
-            A sl[2] = {0, 0};                // layer of cells at -1 and 0 along d
+            for (int m = 0; m < 4; ++m)      // (j - 1, k - 1), (j, k - 1), (j - 1, k), (j, k)
+                load_row<T, 1, 0>(V + c * N + row_at(n, j - 1 + (m & 1), k - 1 + (m >> 1)), n, i,
+                                  r[m]);
+        };
+        rows(0);
 #pragma unroll
-            for (int l = 0; l < 2; ++l)
+        for (int x = 0; x <= W; ++x)
+            sx[x] = ((A)r[0][x] + (A)r[1][x]) + ((A)r[2][x] + (A)r[3][x]);
+        rows(1);
 #pragma unroll
-                for (int a = 0; a < 2; ++a)
+        for (int x = 0; x <= W; ++x)
+            syz[x] = ((A)r[1][x] + (A)r[3][x]) - ((A)r[0][x] + (A)r[2][x]);
+        rows(2);
 #pragma unroll
-                    for (int b = 0; b < 2; ++b) {
-                        int o[3];
-                        o[d] = l - 1;
-                        o[e1] = -a;
-                        o[e2] = -b;
-                        sl[l] += (A)v[I.at(i + o[0], j + o[1], k + o[2])];
-                    }
-            div += (A(0.25) * sl[1] - A(0.25) * sl[0]) * inv_h;
-        }
-        out[0] = (T)div;
+        for (int x = 0; x <= W; ++x)
+            syz[x] += ((A)r[2][x] + (A)r[3][x]) - ((A)r[0][x] + (A)r[1][x]);
+#pragma unroll
+        for (int x = 0; x < W; ++x)
+            out[0][x] = (T)(((sx[x + 1] - sx[x]) + (syz[x] + syz[x + 1])) * q);
     }
 };
 
 // W = V - G p/rho, in place, formed in A
 template <typename T, typename A>
-__global__ void k_proj_W(int n, A h, A rho, const T* __restrict__ p, T* __restrict__ V)
+__global__ void __launch_bounds__(256)
+k_proj_W(int n, A h, A rho, const T* __restrict__ p, T* __restrict__ V)
 {
+    constexpr int W = Wide<T>::W;
     const int64_t N = (int64_t)n * n * n;
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t q = ((int64_t)blockIdx.x * 256 + threadIdx.x) * W;
     if (q >= N)
         return;
-    const Idx I{n};
     const int i = (int)(q & (n - 1)), j = (int)((q / n) & (n - 1)), k = (int)(q / ((int64_t)n * n));
-    const A inv_h = A(1) / h;
+    A g[3][W];
+    grad_cells<T, A>(p, n, i, j, k, A(1) / (h * rho), g);
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-        V[c * N + q] = (T)((A)V[c * N + q] - grad_node_as<A>(p, I, i, j, k, c, inv_h) / rho);
+    for (int c = 0; c < 3; ++c) {
+        T v[W];
+        load_row<T, 0, 0>(V + c * N + q - i, n, i, v);
+#pragma unroll
+        for (int x = 0; x < W; ++x)
+            v[x] = (T)((A)v[x] - g[c][x]);
+        store_row(V + c * N + q, v);
+    }
 }
 
 // u^{n+1} = dt (W - G d/rho) and p = p1 + d (pn holds p1)
 template <typename T, typename A>
-__global__ void k_proj_final_refined(int n, A h, A rho, A dt, const T* __restrict__ W,
-                                     const T* __restrict__ dl, T* __restrict__ un,
-                                     T* __restrict__ pn)
+__global__ void __launch_bounds__(256)
+k_proj_final_refined(int n, A h, A rho, A dt, const T* __restrict__ Wf, const T* __restrict__ dl,
+                     T* __restrict__ un, T* __restrict__ pn)
 {
+    constexpr int W = Wide<T>::W;
     const int64_t N = (int64_t)n * n * n;
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t q = ((int64_t)blockIdx.x * 256 + threadIdx.x) * W;
     if (q >= N)
         return;
-    const Idx I{n};
     const int i = (int)(q & (n - 1)), j = (int)((q / n) & (n - 1)), k = (int)(q / ((int64_t)n * n));
-    const A inv_h = A(1) / h;
+    A g[3][W];
+    grad_cells<T, A>(dl, n, i, j, k, A(1) / (h * rho), g);
+    T v[W], d[W];
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-        un[c * N + q] = (T)(dt * ((A)W[c * N + q] - grad_node_as<A>(dl, I, i, j, k, c, inv_h) / rho));
-    pn[q] = (T)((A)pn[q] + (A)dl[q]);
+    for (int c = 0; c < 3; ++c) {
+        load_row<T, 0, 0>(Wf + c * N + q - i, n, i, v);
+#pragma unroll
+        for (int x = 0; x < W; ++x)
+            v[x] = (T)(dt * ((A)v[x] - g[c][x]));
+        store_row(un + c * N + q, v);
+    }
+    load_row<T, 0, 0>(pn + q - i, n, i, v);
+    load_row<T, 0, 0>(dl + q - i, n, i, d);
+#pragma unroll
+    for (int x = 0; x < W; ++x)
+        v[x] = (T)((A)v[x] + (A)d[x]);
+    store_row(pn + q, v);
 }
 
 // u^{n+1} = dt (V - G p / rho), Eq. (ns_lp3)
 template <typename T>
-__global__ void k_proj_final(int n, T h, T rho, T dt, const T* __restrict__ V, const T* __restrict__ pr,
-                             T* __restrict__ un)
+__global__ void __launch_bounds__(256)
+k_proj_final(int n, T h, T rho, T dt, const T* __restrict__ V, const T* __restrict__ pr,
+             T* __restrict__ un)
 {
+    constexpr int W = Wide<T>::W;
     const int64_t N = (int64_t)n * n * n;
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t q = ((int64_t)blockIdx.x * 256 + threadIdx.x) * W;
     if (q >= N)
         return;
-    const Idx I{n};
     const int i = (int)(q & (n - 1)), j = (int)((q / n) & (n - 1)), k = (int)(q / ((int64_t)n * n));
-    const T inv_h = T(1) / h;
+    T g[3][W];
+    grad_cells<T, T>(pr, n, i, j, k, T(1) / h, g);
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-        un[c * N + q] = dt * (V[c * N + q] - grad_node(pr, I, i, j, k, c, inv_h) / rho);
+    for (int c = 0; c < 3; ++c) {
+        T v[W];
+        load_row<T, 0, 0>(V + c * N + q - i, n, i, v);
+#pragma unroll
+        for (int x = 0; x < W; ++x)
+            v[x] = dt * (v[x] - g[c][x] / rho);
+        store_row(un + c * N + q, v);
+    }
 }
 
 // ------------------------------------------------------------------ passes
 
 // x pass forward: R rows of y of one z plane per workgroup, NC fields.  The
-// fields' values (src.cell) are formed cell by cell into LDS; rows 2 m and
+// fields' values (src.cells) are formed into LDS; rows 2 m and
 // 2 m + 1 of a field then share one complex transform, and its spectrum Z
 // splits into theirs, A = (Z(k) + Z*(-k)) / 2 and B = (Z(k) - Z*(-k)) / 2i.
 // Rows per workgroup: about 2048 cells of each field, so that the three
@@ -277,12 +346,15 @@ k_fft_x_fwd(Src src, Cx<T>* __restrict__ spec)
     T* const real = reinterpret_cast<T*>(buf);        // [NC][R][n]
     fill_twiddles<T, LOGN>(W);
     const int j0 = (blockIdx.x * R) & (n - 1), k = (blockIdx.x * R) >> LOGN;
-    for (int q = threadIdx.x; q < R * n; q += K::NT) {
-        T v[NC];
-        src.cell(q & (n - 1), j0 + (q >> LOGN), k, v);
+    constexpr int VW = Wide<T>::W;
+    for (int q = VW * threadIdx.x; q < R * n; q += VW * K::NT) {
+        T v[NC][VW];
+        src.cells(q & (n - 1), j0 + (q >> LOGN), k, v);
 #pragma unroll
         for (int c = 0; c < NC; ++c)
-            real[c * R * n + q] = v[c];
+#pragma unroll
+            for (int x = 0; x < VW; ++x)
+                real[c * R * n + q + x] = v[c][x];
     }
     __syncthreads();
     const int line = threadIdx.x / L::TPL, t = threadIdx.x % L::TPL;
@@ -601,7 +673,7 @@ static void project_n(double h, double rho, double dt, const T* ustar, const T* 
     constexpr int n = 1 << LOGN;
     constexpr size_t N = (size_t)n * n * n, S = 2 * (size_t)n * n * spec_pitch(n);
     static_assert(3 * N + S + N <= 7 * N, "V, a half spectrum and the correction fit");
-    const unsigned gc = (unsigned)((N + 255) / 256);
+    const unsigned gc = (unsigned)((N / Wide<T>::W + 255) / 256);
     T* V = ws;
     Cx<T>* spec = reinterpret_cast<Cx<T>*>(ws + 3 * N);
     T* dl = ws + 3 * N + S;
