@@ -22,9 +22,8 @@
 // tiles.h for the two hot ones):
 //   interp   work item = up to bw markers of one tile; tile + halo of u0 or G
 //            staged in LDS, one thread per marker.
-//   spread   work item = one tile with a non-empty source list; one wavefront,
-//            lane = (y, z) row of the tile accumulated in registers.  Result
-//            to the compact per-tile G slots.
+//   spread   work item = one tile with a non-empty source list, one wavefront.
+//            Result to the compact per-tile G slots.
 //   finalize f and ustar = u0 + dt G on every valid cell of the covered boxes,
 //            box-wide rows per workgroup.  No float atomics anywhere.
 #include "paths.h"
@@ -234,8 +233,9 @@ __device__ inline void prep_marker(int64_t i, const Grid& g, int64_t nl,
 // per XCD (workgroups are dealt to the XCDs round-robin by id, and each XCD
 // has its own L2, so neighbouring tiles -- which share source markers -- stay
 // on one XCD); inside a slab they are ordered by decreasing source count, so
-// that a static snake deal over the slab's workgroups gives each a similar
-// load.  Cost bins (source count, clamped) are counted per block in LDS and
+// that the workgroups that take them one by one end together.  (Ordered by
+// blocks of neighbouring tiles instead: 930 us a launch against 886 on
+// spheres20000_512, 100 against 82 on spheres1000_256.)  Cost bins (source count, clamped) are counted per block in LDS and
 // then globally; the order inside a bin is whatever the atomics give, which
 // moves no result (each tile is summed by one wavefront in its own fixed
 // order and stored to its own slot).
@@ -891,6 +891,7 @@ struct BatchedWs {
     Item* items;
     int32_t *item_cnt, *item_offs, *act, *act_offs, *slot, *nitems, *nactive;
     int32_t *hist, *cur;
+    int32_t* queue; // spreading entries handed out, by queue (the histogram's memory, free by then)
     int4* sent;     // spreading order by decreasing cost: (slot, tile, sources begin, end)
     T* G;
     uint64_t* rmask;   // per slot: bit r set when row r of the slot is not all zeros
@@ -921,6 +922,8 @@ static BatchedWs<T> carve_batched(const Grid& g, int64_t nl, int bw, void* ws, s
     w.act = cv.take<int32_t>(T_);
     w.act_offs = cv.take<int32_t>(T_);
     w.hist = cv.take<int32_t>(NXCD * COST_BINS);
+    static_assert(NXCD * NQ * QSTRIDE <= NXCD * COST_BINS, "the counters fit the histogram");
+    w.queue = w.hist;
     w.cur = cv.take<int32_t>(NXCD * COST_BINS);
     w.sent = cv.take<int4>(T_);
     w.slot = cv.take<int32_t>(T_);
@@ -942,11 +945,11 @@ static void interp_kernel(const BatchedCfg& cfg, hipStream_t st, const Grid& g, 
                           double dt, const Item* items, const int32_t* nitems, const T* u0,
                           const T* G, const uint64_t* rmask, const int64_t* nbase,
                           const MarkerData<T>& s, double* e2, T* Fout, const int32_t* perm,
-                          const T* vin, double* gX, int use_dv)
+                          const T* vin, double* gX, int use_dv, int32_t* queue)
 {
     constexpr auto K = k_interp_tiles<T, P, MODE, BW, MASK, TXW>;
     K<<<resident_grid<K, BW>(cfg.ncu, 0), BW, 0, st>>>(g, nl, dt, items, nitems, u0, G, nbase, s,
-                                                       e2, Fout, perm, vin, gX, use_dv, rmask);
+                                                       e2, Fout, perm, vin, gX, use_dv, rmask, queue);
 }
 
 template <typename T, int P, int MODE, bool MASK, int TXW>
@@ -954,19 +957,19 @@ static void launch_interp_txw(const BatchedCfg& cfg, hipStream_t st, const Grid&
                               double dt, const Item* items, const int32_t* nitems, const T* u0,
                               const T* G, const uint64_t* rmask, const int64_t* nbase,
                               const MarkerData<T>& s, double* e2, T* Fout, const int32_t* perm,
-                              const T* vin, double* gX, int use_dv)
+                              const T* vin, double* gX, int use_dv, int32_t* queue)
 {
     if (cfg.bw == 64)
         interp_kernel<T, P, MODE, MASK, TXW, 64>(cfg, st, g, nl, dt, items, nitems, u0, G, rmask,
-                                                 nbase, s, e2, Fout, perm, vin, gX, use_dv);
+                                                 nbase, s, e2, Fout, perm, vin, gX, use_dv, queue);
     else if (cfg.bw == 128)
         interp_kernel<T, P, MODE, MASK, TXW, 128>(cfg, st, g, nl, dt, items, nitems, u0, G,
                                                   rmask, nbase, s, e2, Fout, perm, vin, gX,
-                                                  use_dv);
+                                                  use_dv, queue);
     else
         interp_kernel<T, P, MODE, MASK, TXW, 256>(cfg, st, g, nl, dt, items, nitems, u0, G,
                                                   rmask, nbase, s, e2, Fout, perm, vin, gX,
-                                                  use_dv);
+                                                  use_dv, queue);
 }
 
 // Work tiles of two x neighbours are compiled for FP32 only (their halo in
@@ -982,18 +985,18 @@ static void launch_interp_bw(const BatchedCfg& cfg, hipStream_t st, const Grid& 
                              double dt, const Item* items, const int32_t* nitems, const T* u0,
                              const T* G, const uint64_t* rmask, const int64_t* nbase,
                              const MarkerData<T>& s, double* e2, T* Fout, const int32_t* perm,
-                             const T* vin, double* gX, int use_dv)
+                             const T* vin, double* gX, int use_dv, int32_t* queue)
 {
     if constexpr (sizeof(T) == 4) {
         if (pair_items<T>(cfg)) {
             launch_interp_txw<T, P, MODE, MASK, 2 * TILE>(cfg, st, g, nl, dt, items, nitems, u0,
                                                           G, rmask, nbase, s, e2, Fout, perm,
-                                                          vin, gX, use_dv);
+                                                          vin, gX, use_dv, queue);
             return;
         }
     }
     launch_interp_txw<T, P, MODE, MASK, TILE>(cfg, st, g, nl, dt, items, nitems, u0, G, rmask,
-                                              nbase, s, e2, Fout, perm, vin, gX, use_dv);
+                                              nbase, s, e2, Fout, perm, vin, gX, use_dv, queue);
 }
 
 // Interpolation from the G slots (modes 1, 2) uses the slot row masks when the
@@ -1002,36 +1005,48 @@ template <typename T, int P, int MODE>
 static void launch_interp(const BatchedCfg& cfg, hipStream_t st, const Grid& g, int64_t nl,
                           double dt, const Item* items, const int32_t* nitems, const T* u0,
                           const T* G, const uint64_t* rmask, const int64_t* nbase,
-                          const MarkerData<T>& s, double* e2, T* Fout = nullptr,
+                          const MarkerData<T>& s, double* e2, int32_t* queue, T* Fout = nullptr,
                           const int32_t* perm = nullptr, const T* vin = nullptr,
                           double* gX = nullptr, int use_dv = 0)
 {
     if constexpr (MODE == 1 || MODE == 2) {
         if (cfg.masks) {
             launch_interp_bw<T, P, MODE, true>(cfg, st, g, nl, dt, items, nitems, u0, G, rmask,
-                                               nbase, s, e2, Fout, perm, vin, gX, use_dv);
+                                               nbase, s, e2, Fout, perm, vin, gX, use_dv, queue);
             return;
         }
     }
     launch_interp_bw<T, P, MODE, false>(cfg, st, g, nl, dt, items, nitems, u0, G, rmask, nbase,
-                                        s, e2, Fout, perm, vin, gX, use_dv);
+                                        s, e2, Fout, perm, vin, gX, use_dv, queue);
 }
 
-// The tile spreading: one 2 x 2 x 2 block per lane for the 3-point kernel,
-// one row per lane for the 4-point one (the faster layout for each width).
+// The tile spreading by kernel K.
+template <auto K, typename T>
+static void spread_with(const BatchedCfg& cfg, hipStream_t st, const Grid& g,
+                        const BatchedWs<T>& w, const ib_buckets* b, int use_dv)
+{
+    K<<<resident_grid<K, 64>(cfg.ncu, cfg.wgs_s), 64, 0, st>>>(
+        w.sent, w.nactive, b->src_idx, g, w.s, w.G, w.rmask, w.tmask, use_dv, w.queue);
+}
+
 template <typename T, int P, bool MASK>
 static void spread_kernel(const BatchedCfg& cfg, hipStream_t st, const Grid& g,
                           const BatchedWs<T>& w, const ib_buckets* b, int use_dv)
 {
-    if constexpr (P == 3) {
-        constexpr auto K = k_spread_blocks<T, P, MASK>;
-        K<<<resident_grid<K, 64>(cfg.ncu, cfg.wgs_s), 64, 0, st>>>(
-            w.sent, w.nactive, b->src_idx, g, w.s, w.G, w.rmask, w.tmask, use_dv);
-    } else {
-        constexpr auto K = k_spread_tiles<T, P, MASK>;
-        K<<<resident_grid<K, 64>(cfg.ncu, cfg.wgs_s), 64, 0, st>>>(
-            w.sent, w.nactive, b->src_idx, g, w.s, w.G, w.rmask, w.tmask, use_dv);
+    if constexpr (sizeof(T) == 4) {
+        if (!cfg.products) {
+            // one 2 x 2 x 2 block per lane for the 3-point kernel, one row per
+            // lane for the 4-point one (the faster layout for each width)
+            if constexpr (P == 3)
+                spread_with<k_spread_blocks<T, P, MASK>>(cfg, st, g, w, b, use_dv);
+            else if (cfg.wgs_s > 20)
+                spread_with<k_spread_tiles<T, P, MASK, 6>>(cfg, st, g, w, b, use_dv);
+            else
+                spread_with<k_spread_tiles<T, P, MASK, 5>>(cfg, st, g, w, b, use_dv);
+            return;
+        }
     }
+    spread_with<k_spread_mfma<T, P, MASK>>(cfg, st, g, w, b, use_dv);
 }
 
 // The tile spreading, with or without the slot row masks.
@@ -1172,7 +1187,7 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
     IBX_PROF_BEGIN(PK_INTERP_U0);
     // the last interpolation of the loop also writes F in marker order
     launch_interp<T, P, 0>(cfg, st, g, nl, dt, w.items, w.nitems, u0, w.G, w.rmask, w.nb_u, w.s,
-                           e2, ns == 1 ? F : nullptr, b->perm);
+                           e2, w.queue, ns == 1 ? F : nullptr, b->perm);
     IBX_PROF_END();
     if (resid)
         sum_to(w.e2, nl, w.part, resid + 0, true, st);
@@ -1192,7 +1207,7 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
         IBX_PROF_END();
         IBX_PROF_BEGIN(PK_INTERP_G);
         launch_interp<T, P, 1>(cfg, st, g, nl, dt, w.items, w.nitems, u0, w.G, w.rmask, w.nb_g,
-                               w.s, e2, mi == ns ? F : nullptr, b->perm);
+                               w.s, e2, w.queue, mi == ns ? F : nullptr, b->perm);
         IBX_PROF_END();
         if (resid)
             sum_to(w.e2, nl, w.part, resid + (mi - 1), true, st);
@@ -1213,7 +1228,7 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
     if (resid) {
         IBX_PROF_BEGIN(PK_RESID);
         launch_interp<T, P, 2>(cfg, st, g, nl, dt, w.items, w.nitems, u0, w.G, w.rmask, w.nb_g,
-                               w.s, w.e2);
+                               w.s, w.e2, w.queue);
         IBX_PROF_END();
         sum_to(w.e2, nl, w.part, resid + ns, true, st);
     }
@@ -1232,9 +1247,11 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
 
 template <typename T>
 __global__ void k_sort_vec(int64_t nl, const int32_t* __restrict__ perm, const T* __restrict__ v,
-                           typename Vec4<T>::type* __restrict__ f4)
+                           typename Vec4<T>::type* __restrict__ f4, int32_t* __restrict__ queue)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < NXCD * NQ)
+        queue[i * QSTRIDE] = 0;       // the spreading that follows takes its tiles from these counters
     if (i >= nl)
         return;
     const int64_t l = perm[i];
@@ -1299,7 +1316,8 @@ static void spread_t(const Grid& g, const BatchedCfg& cfg, const ib_markers* m,
     const int64_t nfin = (int64_t)g.nbox * (g.box / TILE) * g.box;
     const unsigned gfin = (unsigned)(nfin < 65535 ? (nfin > 0 ? nfin : 1) : 65535);
     if (nl > 0) {
-        k_sort_vec<T><<<(unsigned)((nl + 255) / 256), 256, 0, st>>>(nl, b->perm, v, w.s.f4);
+        k_sort_vec<T><<<(unsigned)((nl + 255) / 256), 256, 0, st>>>(nl, b->perm, v, w.s.f4,
+                                                                    w.queue);
         launch_spread<T, P>(cfg, st, g, w, b, use_dv);
     }
     // u0 given: out = u0 + dt G; else out = G (zero where no marker reaches)
@@ -1343,7 +1361,7 @@ static void interp_grad_t(const Grid& g, const BatchedCfg& cfg, const ib_markers
     size_t need = 0;
     BatchedWs<T> w = carve_batched<T>(g, m->nl, cfg.bw, ws, bytes, &need);
     launch_interp<T, P, 3>(cfg, st, g, m->nl, 0.0, w.items, w.nitems, fld, nullptr, nullptr,
-                           w.nb_u, w.s, nullptr, U, b->perm, v, gX, use_dv);
+                           w.nb_u, w.s, nullptr, w.queue, U, b->perm, v, gX, use_dv);
 }
 
 int tile_interp_grad(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,

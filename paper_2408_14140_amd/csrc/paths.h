@@ -31,6 +31,7 @@ struct BatchedCfg {
     int masks;     // G slot row masks: zero rows neither stored nor loaded
     int txw;       // x extent of an interpolation work tile: 8 (one tile) or 16 (FP32)
     Profiler* prof;  // nullable: per-kernel event timing
+    int products = 0;  // FP32: spread by matrix products (FP64 always does)
 };
 
 size_t batched_workspace(const Grid& g, ib_prec prec, int64_t nl, const BatchedCfg& cfg);

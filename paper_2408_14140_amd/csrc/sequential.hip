@@ -328,6 +328,11 @@ int sequential_multidirect(const ib_level* lv, const Grid& g, int P, ib_prec pre
     const int32_t np = p->np;
     const int64_t nl = m->nl;
     size_t need = 0;
+    BatchedCfg sc = cfg;
+    // a level's loop owes no bits to the Jacobi loop, and with a few thousand
+    // tiles a level the matrix products are the faster spreading (20 us a
+    // launch against 32 on the levels of spheres1000_256)
+    sc.products = 1;
     carve_seq(lv, g, prec, np, nl, cfg, nullptr, 0, &need);
     if (!ws || ws_bytes < need)
         return IB_EWORKSPACE;
@@ -405,7 +410,7 @@ int sequential_multidirect(const ib_level* lv, const Grid& g, int P, ib_prec pre
         if (flag)
             k_or_flags<<<1, 64, 0, st>>>(w.b.flag, flag);
         k_or_flags<<<1, 64, 0, st>>>(w.b.flag, w.anyflag);
-        rc = batched_multidirect(g, P, prec, cfg, &pr, &mc, &w.b, ns, dt, uin, ustar, f,
+        rc = batched_multidirect(g, P, prec, sc, &pr, &mc, &w.b, ns, dt, uin, ustar, f,
                                  w.F + 3 * n0 * es, nullptr, nullptr, w.lws, w.lws_bytes, st,
                                  first ? 0 : 1);
         if (rc)

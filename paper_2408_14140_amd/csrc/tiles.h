@@ -11,16 +11,20 @@
 // stencil each), so all waves of the workgroup share the compute phase.
 //
 // Spreading (one work item = one tile with a non-empty source list, one
-// wavefront): lane = one (y, z) row of the tile, holding its 8 cells x 3
-// components in registers.  Sources are staged 64 at a time in LDS; ballots
-// give each lane the set of staged sources whose stencil covers its row.
-// Rows near a particle surface are covered by several times more sources than
-// the mean, so the visits are balanced in two phases: each lane first takes up
-// to K sources of its own row, then the rest of the heavier rows is dealt out
-// in pieces of K to all lanes and added back by the row's owner in order.  No
-// atomics: each cell's sum is formed in a fixed order, so the result is
-// reproducible bit for bit.  Each lane then stores its row (8 consecutive
-// cells per component in the tile's slot) straight from registers.
+// wavefront).  FP64, and FP32 outside the Jacobi loop and the adjoint: a matrix
+// product over the tile's sources, octant by octant on the matrix cores
+// (k_spread_mfma).  FP32 loop and adjoint: lane = one (y, z) row of the tile
+// (P = 4) or one 2 x 2 x 2 block (P = 3), accumulated in registers.  Sources are
+// staged 64 at a time in LDS; ballots give each lane the set of staged sources
+// whose stencil covers its row.  Rows near a particle surface are covered by
+// several times more sources than the mean, so the visits are balanced in two
+// phases: each lane first takes up to K sources of its own row, then the rest
+// of the heavier rows is dealt out in pieces of K to all lanes and added back
+// by the row's owner in order.  The matrix products are faster (82 us against
+// 103 a launch on spheres1000_256), but round otherwise: sums over markers and
+// gradients, which are FP64 values of the loop's FP32 forces, would move by
+// 1e-8.  No float atomics in either: each cell's sum is formed in a fixed order,
+// so the result is reproducible bit for bit.
 #pragma once
 
 // XCD-aware static work split.  Workgroups are dispatched to the 8 XCDs of
@@ -31,6 +35,14 @@
 // The grid is a multiple of 8 workgroups.  Which workgroup computes an item
 // never changes the item's result.
 constexpr int NXCD = 8;
+
+// Spreading queues: the entries of an XCD's slab are dealt to NQ queues, each
+// served by the XCD's workgroups of one residue, with a counter in a cache
+// line of its own.  (A device-scope atomic on a line that many workgroups
+// share takes about 12 ns: with one counter per XCD the spreading of
+// spheres1000_256 went from 80 to 96 us, with one line for all to 443 us.)
+constexpr int NQ = 8;
+constexpr int QSTRIDE = 32;         // ints between two counters
 
 struct Slab {
     int begin, end, stride;
@@ -101,8 +113,11 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
                const T* __restrict__ G, const int64_t* __restrict__ nbase, MarkerData<T> s,
                double* __restrict__ e2, T* __restrict__ Fout, const int32_t* __restrict__ perm,
                const T* __restrict__ vin, double* __restrict__ gX, int use_dv,
-               const uint64_t* __restrict__ rmask)
+               const uint64_t* __restrict__ rmask, int32_t* __restrict__ queue)
 {
+    // the spreading that follows takes its tiles from these counters
+    if (MODE < 2 && blockIdx.x == 0 && threadIdx.x < NXCD * NQ)
+        queue[threadIdx.x * QSTRIDE] = 0;
     constexpr bool BOX = MODE == 0 || MODE == 3;   // field in the box layout
     constexpr int gh = Halo<P>::g, R = Halo<P>::R;
     // The work tile is TXW x 8 x 8 cells: one tile, or two x neighbours
@@ -450,6 +465,44 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
     }
 }
 
+// The spreading entries of one workgroup, (slot, tile, first source, end of
+// sources): every NQ-th entry of its XCD's slab of `sent` (ordered by
+// decreasing cost) is its queue's, which nw workgroups share.  next() gives
+// entries me, 2 nw - 1 - me and 2 nw + me of the queue, then what its counter
+// hands out, and zeros at the end.  A ticket is drawn one entry before it is
+// used (lane 0 holds it till then), so nothing waits for the atomic.  Dealing
+// all entries out beforehand (in a snake) left wavefronts idle at the end: 1151
+// us a launch of the block kernel on spheres20000_512 against 933 (on
+// spheres1000_256, where a wavefront gets about six tiles, no change).
+struct SpreadQueue {
+    const int4* entries;
+    int32_t* counter;
+    int me, nw, count, r, tick;
+    __device__ SpreadQueue(const int4* sent, int32_t* queue, int n_act)
+    {
+        const int per = (n_act + NXCD - 1) / NXCD;
+        const int x = blockIdx.x % NXCD, nwg = gridDim.x / NXCD, wg = blockIdx.x / NXCD;
+        const int sub = wg % NQ, slab = min(n_act, (x + 1) * per) - x * per;
+        me = wg / NQ;
+        nw = (nwg - sub + NQ - 1) / NQ;
+        count = slab > sub ? (slab - sub + NQ - 1) / NQ : 0;
+        entries = sent + x * per + sub;
+        counter = queue + (x * NQ + sub) * QSTRIDE;
+        r = tick = 0;
+    }
+    __device__ int4 next()
+    {
+        const int q = r == 0   ? me
+                      : r == 1 ? 2 * nw - 1 - me
+                      : r == 2 ? 2 * nw + me
+                               : 3 * nw + __builtin_amdgcn_readfirstlane(tick);
+        if (r >= 2 && 3 * nw < count && threadIdx.x == 0)
+            tick = atomicAdd(counter, 1);
+        ++r;
+        return q < count ? entries[(int64_t)q * NQ] : make_int4(0, 0, 0, 0);
+    }
+};
+
 // floor(a / b) for 0 <= a < 128, 1 <= b <= 128: the quotient's distance to
 // the next integer is at least 1/b unless it is exact, far above the error
 // of the single-precision product, so a small bias makes the floor exact.
@@ -512,11 +565,9 @@ __device__ inline uint64_t drop_low_bits(uint64_t m, int s)
     return m & (~0ull << p);
 }
 
-// One wavefront per workgroup; the tile is stored to its G slot.  The
-// workgroups of XCD x (ids = x mod 8) take the entries of slab x of `sent`
-// (the x-th of 8 equal cuts, each by decreasing cost) dealt in a snake: with
-// W workgroups on the XCD, round r gives its w-th workgroup entry r W + w
-// (r even) or r W + W - 1 - w (r odd) of the slab.
+// One wavefront per workgroup; the tile is stored to its G slot.  (This kernel
+// and k_spread_blocks run in FP32, whose loop and adjoint keep the bits of their
+// row and block sums; k_spread_mfma below serves the rest.)
 //
 // Sources are staged 64 at a time as structure-of-arrays in LDS: the weight
 // of every tile x cell (zero outside the stencil), the P weights along y and
@@ -527,16 +578,16 @@ __device__ inline uint64_t drop_low_bits(uint64_t m, int s)
 // visits exactly those sources in list order.  Each lane holds one (y, z) row
 // of the tile and stores it straight to the slot (rows are contiguous there).
 // LDS stays near 5.9 KB so that 24 or more workgroups fit on a CU.
-// (FP32: registers capped so that 6 waves fit per SIMD, the residency that the
-// latency-bound visit chain wants; at that cap the 4-point kernel spills two
-// registers, which costs less than the prefetch of the source indices saves.)
-template <typename T, int P, bool MASK = false>
-__global__ void __launch_bounds__(64)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 1, 8)))
+// EU: waves per SIMD that the registers allow.  6 cost four spilled registers,
+// which pays only where more than five run (a plan that allows more than 20
+// workgroups per CU; loop of spheres1000_256 1.090 ms against 1.098): with the
+// default 16, 5 waves take 103 us a launch there and 6 take 110.
+template <typename T, int P, bool MASK, int EU>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(EU, 8)))
 k_spread_tiles(const int4* __restrict__ sent, const int32_t* __restrict__ nactive,
                const int32_t* __restrict__ src_idx, Grid g, MarkerData<T> s,
                T* __restrict__ G, uint64_t* __restrict__ rmask, uint64_t* __restrict__ tmask,
-               int use_dv)
+               int use_dv, int32_t* __restrict__ queue)
 {
     constexpr int NW = TILE + 2 * P + 3;                   // staged values per source
     constexpr int NBUF = NW * 64;
@@ -565,20 +616,13 @@ k_spread_tiles(const int4* __restrict__ sent, const int32_t* __restrict__ nactiv
     };
     const int lane = threadIdx.x;
     const int ly = lane & 7, lz = lane >> 3;
-    const int n_act = *nactive;
-    const int per = (n_act + NXCD - 1) / NXCD;
-    const int x = blockIdx.x % NXCD, nwg = gridDim.x / NXCD, wg = blockIdx.x / NXCD;
-    const int s_end = min(n_act, (x + 1) * per);
-    auto entry = [&](int r) { return x * per + r * nwg + ((r & 1) ? nwg - 1 - wg : wg); };
+    SpreadQueue sq(sent, queue, *nactive);
     // The source indices of each batch are loaded one batch ahead (the next
     // tile's first batch after a tile's last), so the visits hide that load.
-    int idx = entry(0);
-    int4 ent = idx < s_end ? sent[idx] : make_int4(0, 0, 0, 0);
-    int pf = idx < s_end && ent.z + lane < ent.w ? src_idx[ent.z + lane] : 0;
-    for (int r = 0; idx < s_end; ++r) {
-        // (slot, tile, first source, end of sources) of this and the next tile
-        const int nidx = entry(r + 1);
-        const int4 nent = nidx < s_end ? sent[nidx] : make_int4(0, 0, 0, 0);
+    int4 ent = sq.next();
+    int pf = ent.z + lane < ent.w ? src_idx[ent.z + lane] : 0;
+    while (ent.w > 0) {
+        const int4 nent = sq.next();
         const int a = ent.x;
         int lo[3];
         tile_coords(g, ent.y, lo);
@@ -737,7 +781,6 @@ k_spread_tiles(const int4* __restrict__ sent, const int32_t* __restrict__ nactiv
                 *reinterpret_cast<typename Vec4<T>::type*>(gs + c * TILE_CELLS + 4) = v1;
             }
         }
-        idx = nidx;
         ent = nent;
     }
 }
@@ -760,15 +803,13 @@ k_spread_tiles(const int4* __restrict__ sent, const int32_t* __restrict__ nactiv
 // whose stencil covers less of an 8-cell row; the rows are faster for the
 // 4-point kernel.  A block cell just outside the stencil reads a zero pad.
 // LDS stays near 6.5 KB so that 24 workgroups fit on a CU.
-// (FP32: registers capped so that 6 waves fit per SIMD, the residency that the
-// latency-bound visit chain wants.)
-template <typename T, int P, bool MASK = false>
-__global__ void __launch_bounds__(64)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 6 : 1, 8)))
+// (6 waves per SIMD: the residency that the latency-bound visit chain wants.)
+template <typename T, int P, bool MASK>
+__global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6, 8)))
 k_spread_blocks(const int4* __restrict__ sent, const int32_t* __restrict__ nactive,
                const int32_t* __restrict__ src_idx, Grid g, MarkerData<T> s,
                T* __restrict__ G, uint64_t* __restrict__ rmask, uint64_t* __restrict__ tmask,
-               int use_dv)
+               int use_dv, int32_t* __restrict__ queue)
 {
     constexpr int PW = P + 2;                              // weights per axis, zero padded
     constexpr int NW = 3 * PW + 3;                         // staged values per source
@@ -813,20 +854,13 @@ k_spread_blocks(const int4* __restrict__ sent, const int32_t* __restrict__ nacti
     };
     const int lane = threadIdx.x;
     const int lbx = lane & 3, lby = (lane >> 2) & 3, lbz = lane >> 4;
-    const int n_act = *nactive;
-    const int per = (n_act + NXCD - 1) / NXCD;
-    const int x = blockIdx.x % NXCD, nwg = gridDim.x / NXCD, wg = blockIdx.x / NXCD;
-    const int s_end = min(n_act, (x + 1) * per);
-    auto entry = [&](int r) { return x * per + r * nwg + ((r & 1) ? nwg - 1 - wg : wg); };
+    SpreadQueue sq(sent, queue, *nactive);
     // The source indices of each batch are loaded one batch ahead (the next
     // tile's first batch after a tile's last), so the visits hide that load.
-    int idx = entry(0);
-    int4 ent = idx < s_end ? sent[idx] : make_int4(0, 0, 0, 0);
-    int pf = idx < s_end && ent.z + lane < ent.w ? src_idx[ent.z + lane] : 0;
-    for (int r = 0; idx < s_end; ++r) {
-        // (slot, tile, first source, end of sources) of this and the next tile
-        const int nidx = entry(r + 1);
-        const int4 nent = nidx < s_end ? sent[nidx] : make_int4(0, 0, 0, 0);
+    int4 ent = sq.next();
+    int pf = ent.z + lane < ent.w ? src_idx[ent.z + lane] : 0;
+    while (ent.w > 0) {
+        const int4 nent = sq.next();
         const int a = ent.x;
         int lo[3];
         tile_coords(g, ent.y, lo);
@@ -1025,7 +1059,282 @@ k_spread_blocks(const int4* __restrict__ sent, const int32_t* __restrict__ nacti
                 *reinterpret_cast<typename Vec4<T>::type*>(gs + c * TILE_CELLS + 4) = v1;
             }
         }
-        idx = nidx;
         ent = nent;
+    }
+}
+
+// Matrix products D += A B of 16 x 4 by 4 x 16 values.  Operands: lane l holds
+// A[l % 16][l / 16] and B[l / 16][l % 16].  Result: register r of lane l holds
+// column l % 16 and row 4 (l / 16) + r (FP32) or l / 16 + 4 r (FP64).
+template <typename T>
+struct Mat;
+template <>
+struct Mat<float> {
+    typedef float acc __attribute__((ext_vector_type(4)));
+    static __device__ acc mac(float a, float b, acc c)
+    {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+    }
+};
+template <>
+struct Mat<double> {
+    typedef double acc __attribute__((ext_vector_type(4)));
+    static __device__ acc mac(double a, double b, acc c)
+    {
+        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    }
+};
+
+// Number of set bits of m below this lane's.
+__device__ inline int bits_below(uint64_t m)
+{
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// One wavefront per workgroup; the tile is stored to its G slot.
+//
+// Spreading a tile is the matrix product
+//   G[(x, c)][(y, z)] = sum over sources k of (w^x_k F_k)[(x, c)] (w^y_k w^z_k)[(y, z)]
+// formed per octant of 4^3 cells on the matrix cores: 12 of 16 rows (x, c), 16
+// columns (y, z), four sources an instruction.  A source of a tile reaches 1.27
+// (P = 4) or 1.2 (P = 3) of the tile's two halves along an axis on average,
+// about a quarter of its octants, and each octant takes only the sources that
+// reach it: sources are staged 64 at a time as records in LDS (per axis the
+// weight of each of the tile's 8 cells, zero outside the stencil, and F dV/h^3,
+// or F alone when use_dv is 0), and each octant's sources are listed in order.
+// Lists are padded with an all-zero record.  A record is 27 values, an odd
+// number, so the lanes that stage (one source each) and those that read (four
+// sources, four cells) fall on different banks.  The operands need x and y at
+// one lane-dependent place, c and z at another, so a group of four sources is
+// two paired LDS reads, two products and one matrix instruction: about 6 vector
+// instructions for 4 x 64 cells x 3.
+//
+// Bound by memory where there are many tiles: FP32 on spheres20000_512 counts
+// 4.2 GB a launch (886 us, 4.7 TB/s; sources gathered by every tile that they
+// reach; the block kernel takes 933 us), on spheres1000_256 0.30 GB (82 us, half
+// of it the G slots; the row kernel 103 us).  Where a wavefront has one tile the
+// chain of its batches counts: a level of spheres1000_256 in particle order 21.6
+// us against 31.5, spheres64_128 20 against 32.  FP64, spheres8_256: 18.8 us
+// against 21.0 with the rows.
+//
+// Every cell's sum is formed in one register in list order: bit-reproducible.
+// A source whose F is not finite would turn zero weights into NaN for its
+// whole octant; such sources are added apart, to the cells they reach only.
+// Records are loaded one batch ahead and source indices two, so the products
+// hide the loads.
+// (FP64: at least two wavefronts per SIMD, which keeps the sums out of the
+// accumulator registers and saves their copies; in FP32 the compiler's own
+// choice was the faster one.)
+template <typename T, int P, bool MASK = false>
+__global__ void __launch_bounds__(64)
+__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 1 : 2, 8)))
+k_spread_mfma(const int4* __restrict__ sent, const int32_t* __restrict__ nactive,
+               const int32_t* __restrict__ src_idx, Grid g, MarkerData<T> s,
+               T* __restrict__ G, uint64_t* __restrict__ rmask, uint64_t* __restrict__ tmask,
+               int use_dv, int32_t* __restrict__ queue)
+{
+    using V4 = typename Vec4<T>::type;
+    using Acc = typename Mat<T>::acc;
+    typedef T Fill __attribute__((ext_vector_type(16 / sizeof(T)), may_alias));
+    typedef uint32_t Pair32 __attribute__((may_alias));
+    constexpr int S = 3 * TILE + 3, WX = 0, WY = TILE, WZ = 2 * TILE, WF = 3 * TILE;
+    constexpr int FPL = (65 * S * (int)sizeof(T) + 1023) / 1024;   // 16-byte fills per lane
+    // 64 sources, one zero record, and a word per lane for what falls outside
+    constexpr int OUT = FPL * 1024 / (int)sizeof(T);
+    __shared__ __align__(16) T rec[OUT + 64];
+    __shared__ __align__(16) uint16_t list[8 * 64];                // [octant][k][group]: offsets
+    const int lane = threadIdx.x;
+    // place of this lane's x and y (ixy) and of its c and z (icz) in an octant
+    const int ixy = sizeof(T) == 4 ? lane & 3 : (lane >> 2) & 3;
+    const int icz = sizeof(T) == 4 ? (lane >> 2) & 3 : lane & 3;
+    const int kq = lane >> 4;                              // source of a group; c of the result
+    SpreadQueue sq(sent, queue, *nactive);
+    auto index = [&](int at, int end) { return at + lane < end ? src_idx[at + lane] : -1; };
+    V4 geo, fv;
+    int64_t rb = 0;
+    geo.x = geo.y = geo.z = geo.w = fv.x = fv.y = fv.z = fv.w = T(0);
+    auto load = [&](int i) {
+        if (i >= 0) {
+            geo = s.geo[i];
+            fv = s.f4[i];
+            rb = s.rb[i];
+        }
+    };
+    // this tile and the next two
+    int4 e0 = sq.next(), e1 = sq.next(), e2 = sq.next();
+    int pos = e0.z;
+    int cur = index(pos, e0.w);                            // sources of this batch
+    load(cur);
+    // first source and end of the batch after the one at `at` of tile a, where
+    // b follows a
+    int nat = pos + 64 < e0.w ? pos + 64 : e1.z, nend = pos + 64 < e0.w ? e0.w : e1.w;
+    int nxt = index(nat, nend);
+    Acc acc[8];
+#pragma unroll
+    for (int o = 0; o < 8; ++o)
+        acc[o] = Acc{T(0), T(0), T(0), T(0)};
+    int lo[3];
+    tile_coords(g, e0.y, lo);
+    while (e0.w > 0) {
+#pragma unroll
+        for (int q = 0; q < FPL; ++q)
+            reinterpret_cast<Fill*>(rec)[lane + 64 * q] = Fill(T(0));
+        {
+            typedef uint32_t Fill4 __attribute__((ext_vector_type(4), may_alias));
+            constexpr uint32_t z = 64 * S * sizeof(T);
+            reinterpret_cast<Fill4*>(list)[lane] = Fill4(z | z << 16);
+        }
+        bool lower[3] = {false, false, false}, upper[3] = {false, false, false}, odd = false;
+        if (cur >= 0) {
+            int rbs[3];
+            unpack_rb(rb, rbs);
+            T gw[3][P];
+            axis_weights_r<T, P>(geo.x, gw[0]);
+            axis_weights_r<T, P>(geo.y, gw[1]);
+            axis_weights_r<T, P>(geo.z, gw[2]);
+            const T sc = use_dv ? geo.w : T(1);
+            const T F0 = fv.x * sc, F1 = fv.y * sc, F2 = fv.z * sc;
+            odd = !(fabs(F0) + fabs(F1) + fabs(F2) < (T)__builtin_inf());
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                int b = rbs[ax] - lo[ax];
+                if (b < -(P - 1)) b += g.n[ax];
+                else if (b > TILE - 1) b -= g.n[ax];
+#pragma unroll
+                for (int o = 0; o < P; ++o)
+                    rec[(unsigned)(b + o) < (unsigned)TILE ? lane * S + TILE * ax + b + o
+                                                           : OUT + lane] = gw[ax][o];
+                lower[ax] = !odd && b < TILE / 2;
+                upper[ax] = !odd && b + P > TILE / 2;
+            }
+            rec[lane * S + WF] = F0;
+            rec[lane * S + WF + 1] = F1;
+            rec[lane * S + WF + 2] = F2;
+        }
+        const uint64_t odds = __ballot(odd && cur >= 0);
+        int cnt[8];
+#pragma unroll
+        for (int o = 0; o < 8; ++o) {
+            const bool in = (o & 1 ? upper[0] : lower[0]) && (o & 2 ? upper[1] : lower[1]) &&
+                            (o & 4 ? upper[2] : lower[2]);
+            const uint64_t m = __ballot(in);
+            const int rank = bits_below(m);
+            cnt[o] = __popcll(m);
+            if (in)
+                list[64 * o + 16 * (rank & 3) + (rank >> 2)] =
+                    (uint16_t)(lane * S * (int)sizeof(T));
+        }
+        __syncthreads();
+        // the next batch's records and the indices of the one after it
+        const bool last = pos + 64 >= e0.w;
+        load(nxt);
+        {
+            const int4 a = last ? e1 : e0, b = last ? e2 : e1;
+            cur = nxt;
+            nat += 64;
+            nend = a.w;
+            if (nat >= a.w) {
+                nat = b.z;
+                nend = b.w;
+            }
+            nxt = index(nat, nend);
+        }
+        // Groups gr and gr + 1 of octant o: list entries, operands, products.
+        struct Ops {
+            T wx[2], wy[2], wz[2], f[2];
+        };
+        auto entries = [&](int o, int gr) {
+            return *reinterpret_cast<const Pair32*>(list + 64 * o + 16 * kq + gr);
+        };
+        auto read = [&](int o, uint32_t e, Ops& v) {
+            const char* const base = reinterpret_cast<const char*>(rec);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const T* const p =
+                    reinterpret_cast<const T*>(base + (h ? e >> 16 : e & 0xffffu));
+                const T* const p1 = p + ixy;
+                const T* const p2 = p + icz;
+                v.wx[h] = p1[WX + 4 * (o & 1)];
+                v.wy[h] = p1[WY + 4 * ((o >> 1) & 1)];
+                v.wz[h] = p2[WZ + 4 * (o >> 2)];
+                v.f[h] = p2[WF];
+            }
+        };
+        auto mac = [&](int o, int h, const Ops& v) {
+            acc[o] = Mat<T>::mac(v.wx[h] * v.f[h], v.wy[h] * v.wz[h], acc[o]);
+        };
+#pragma unroll
+        for (int o = 0; o < 8; ++o)
+            for (int gr = 0; 4 * gr < cnt[o]; gr += 2) {
+                Ops v;
+                read(o, entries(o, gr), v);
+                mac(o, 0, v);
+                mac(o, 1, v);
+            }
+        for (uint64_t m = odds; m; m &= m - 1) {
+            const T* const q = rec + __builtin_ctzll(m) * S;
+#pragma unroll
+            for (int o = 0; o < 8; ++o) {
+                const T wyz = q[WY + 4 * ((o >> 1) & 1) + ixy] * q[WZ + 4 * (o >> 2) + icz];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const T w = q[WX + 4 * (o & 1) + i] * wyz;
+                    if (kq < 3 && w != T(0))
+                        acc[o][i] += q[WF + kq] * w;
+                }
+            }
+        }
+        __syncthreads();
+        if (!last) {
+            pos += 64;
+            continue;
+        }
+        // lane: column (y, z) = (ixy, icz) of each octant, c = kq (3: nothing),
+        // registers along x; with MASK, rows of zeros are not stored and their
+        // bit in the slot's row mask (kept by slot and by tile) is clear
+        T* const gs = G + (int64_t)e0.x * 3 * TILE_CELLS + kq * TILE_CELLS + TILE * ixy +
+                      TILE * TILE * icz;
+        uint64_t rm = 0;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {                      // (y, z) half
+            bool nz = true;
+            if constexpr (MASK) {
+                nz = false;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    nz = nz || acc[2 * h][i] != T(0) || acc[2 * h + 1][i] != T(0);
+                const uint64_t b = __ballot(nz && kq < 3);
+                const uint32_t rows = (uint32_t)(b | b >> 16 | b >> 32) & 0xffffu;
+                nz = (rows >> (lane & 15)) & 1;
+                // row y + 8 z of the tile <- column of the octant
+                const uint64_t all = __ballot(nz && kq == 0);
+#pragma unroll
+                for (int y = 0; y < 4; ++y)
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) {
+                        const int col = sizeof(T) == 4 ? y + 4 * z : z + 4 * y;
+                        rm |= ((all >> col) & 1)
+                              << (4 * (h & 1) + y + TILE * (4 * (h >> 1) + z));
+                    }
+            }
+            T* const at = gs + 4 * TILE * (h & 1) + 4 * TILE * TILE * (h >> 1);
+            if (nz && kq < 3) {
+                *reinterpret_cast<Acc*>(at) = acc[2 * h];
+                *reinterpret_cast<Acc*>(at + 4) = acc[2 * h + 1];
+            }
+            acc[2 * h] = acc[2 * h + 1] = Acc{T(0), T(0), T(0), T(0)};
+        }
+        if constexpr (MASK) {
+            if (lane == 0) {
+                rmask[e0.x] = rm;
+                tmask[e0.y] = rm;
+            }
+        }
+        e0 = e1;
+        e1 = e2;
+        e2 = sq.next();
+        pos = e0.z;
+        tile_coords(g, e0.y, lo);
     }
 }

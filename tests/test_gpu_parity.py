@@ -734,3 +734,31 @@ def test_bucket_source_list_overflow(dev, name, mk):
     so = b.src_offs.cpu().numpy()
     assert so[0] == 0 and so[-1] == cap and np.all(np.diff(so) >= 0)
     assert np.array_equal(b.tile_offs.cpu().numpy(), ref["tile_offs"])
+
+
+@pytest.mark.parametrize("delta", [3, 4])
+@pytest.mark.parametrize("bad", ["inf", "nan"])
+def test_non_finite_force_stays_in_its_stencils(dev, delta, bad):
+    """A particle whose forces are not finite spoils the cells that its stencils
+    reach and no others: the matrix-product spreading (FP64 plans) against the
+    plain path, one iteration, where zero weights meet infinite forces."""
+    import torch
+
+    import paper_2408_14140_amd as ibx
+    announce(f"non-finite force P={delta} {bad}")
+    wl = small_workload(32, 16, delta, 1, 1)
+    c = Case(wl, dev)
+    c.parts.up[0, 1] = float(bad)
+    b = ibx.bucket(c.dl, c.dm, delta)
+    u0 = c.u0_boxes(torch.float64)
+    got = {}
+    for path in (ibx.IB_PATH_PLAIN, ibx.IB_PATH_BATCHED):
+        plan = ibx.Plan(delta, torch.float64, path)
+        us, f, F = plan.multidirect_force(c.dl, c.parts, c.dm, b, 1, wl.dt, u0)
+        torch.cuda.synchronize()
+        got[path] = (c.to_global(f), F.cpu().numpy())
+    (f0, F0), (f1, F1) = got[ibx.IB_PATH_PLAIN], got[ibx.IB_PATH_BATCHED]
+    assert not np.isfinite(F0).all() and np.array_equal(np.isfinite(F0), np.isfinite(F1))
+    fin = np.isfinite(f0)
+    assert not fin.all() and np.array_equal(fin, np.isfinite(f1))
+    assert rel(f1[fin], f0[fin]) <= TOL64
