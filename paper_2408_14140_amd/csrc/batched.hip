@@ -26,6 +26,7 @@
 //            Result to the compact per-tile G slots.
 //   finalize f and ustar = u0 + dt G on every valid cell of the covered boxes,
 //            box-wide rows per workgroup.  No float atomics anywhere.
+#include "octants.h"
 #include "paths.h"
 
 namespace ibx {
@@ -77,41 +78,6 @@ __device__ inline void unpack_rb(int64_t v, int* rb)
 #pragma unroll
     for (int a = 0; a < 3; ++a)
         rb[a] = (int)((v >> (RB_BITS * a)) & RB_MASK) - RB_BIAS;
-}
-
-// The P weights of one axis from r = s - b - 1/2.  With d = r - 1 the
-// distances to the P stencil points are 1 + d, |d|, 1 - d (and 2 - d), each
-// on a fixed branch of the kernel, and all branches share one square root.
-// P = 4: r in [1, 2), phi = (3 - 2|x| + q)/8 or (5 - 2|x| - q')/8 with
-// q^2 = 1 + 4d - 4d^2; P = 3: r in [1/2, 3/2), q^2 = 1 - 3d^2.
-__device__ inline float root(float x)
-{
-    return __builtin_amdgcn_sqrtf(x);   // the hardware square root (1 ulp), x in [1/4, 2]
-}
-
-__device__ inline double root(double x)
-{
-    return sqrt(x);
-}
-
-template <typename T, int P>
-__device__ inline void axis_weights_r(T r, T* w)
-{
-    const T d = r - T(1);
-    if (P == 4) {
-        const T q = root(T(1) + T(4) * d * (T(1) - d)) * T(0.125);
-        const T a = T(0.375) - T(0.25) * d, b = T(0.125) + T(0.25) * d;
-        w[0] = a - q;
-        w[1] = a + q;
-        w[2] = b + q;
-        w[3] = b - q;
-    } else {
-        const T q = root(T(1) - T(3) * d * d);
-        const T q6 = q * T(1.0 / 6.0);
-        w[0] = T(1.0 / 3.0) - T(0.5) * d - q6;
-        w[1] = T(1.0 / 3.0) + T(1.0 / 3.0) * q;
-        w[P - 1] = T(1.0 / 3.0) + T(0.5) * d - q6;
-    }
 }
 
 // The same P weights and their derivatives with respect to r (= with respect

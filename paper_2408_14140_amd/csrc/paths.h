@@ -13,8 +13,6 @@ void sum_to(const double* v, int64_t n, double* part, double* out, bool do_sqrt,
 size_t sum_partials(int64_t n);
 size_t field_elems(const Grid& g);
 
-void plain_interp(const Grid& g, int P, ib_prec prec, const ib_markers* m, const void* u,
-                  void* U, hipStream_t st);
 void plain_spread(const Grid& g, int P, ib_prec prec, const ib_markers* m, const ib_buckets* b,
                   const void* F, void* f, double scale, int use_dv, hipStream_t st);
 

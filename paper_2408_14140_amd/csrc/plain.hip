@@ -5,7 +5,8 @@
 //   spread   one workgroup per 8^3 tile, one thread per cell, pulling the
 //            tile's source list in order (deterministic, no atomics)
 //   correct  one thread per covered cell: u^(m) = u0 + dt f^m
-#include "ibx_internal.h"
+// ib_interp and ib_spread run kernels of their own (k_interp_quads, k_spread_list).
+#include "octants.h"
 #include "paths.h"
 
 namespace ibx {
@@ -60,6 +61,142 @@ k_interp_plain(Grid g, int64_t nl, const double* __restrict__ x, const double* _
     U[3 * l + 0] = acc0;
     U[3 * l + 1] = acc1;
     U[3 * l + 2] = acc2;
+}
+
+// Workgroups are dealt to the 8 XCDs round-robin; the work that workgroup b of a
+// multiple of 8 takes, so that each XCD (and its L2) gets a contiguous eighth.
+__device__ inline unsigned xcd_block(unsigned b, unsigned blocks)
+{
+    return (b & 7) * (blocks >> 3) + (b >> 3);
+}
+
+// Value v of lane K of every four.
+template <int K>
+__device__ inline int quad_int(int v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, K * 0x55, 0xf, 0xf, true);
+}
+
+template <int K>
+__device__ inline float quad(float v)
+{
+    return __int_as_float(quad_int<K>(__float_as_int(v)));
+}
+
+template <int K>
+__device__ inline double quad(double v)
+{
+    return __hiloint2double(quad_int<K>(__double2hiint(v)), quad_int<K>(__double2loint(v)));
+}
+
+// Sum over the four lanes in a fixed order: (0 + 1) + (2 + 3).
+template <typename T>
+__device__ inline T quad_sum(T v)
+{
+    return (quad<0>(v) + quad<1>(v)) + (quad<2>(v) + quad<3>(v));
+}
+
+// Interpolation for its own sake (ib_interp): four lanes per marker.  Lane a < 3
+// finds the stencil along axis a (the four then share them); lane i sums the
+// cells of x position i (i = 3 idles when P = 3) over y and z, and the four sums
+// are weighted along x and added.  A row of the stencil is thus one run of
+// lanes, which the L1 takes as one access where a thread with a row of its own
+// takes one per cell: a stencil starts at any element of a row, and the L1 was
+// what bound such a kernel (244 us on spheres1000_256 FP32, 1.13 accesses a
+// cycle per CU).  A stencil lies in at most two boxes along an axis: the box
+// offsets are looked up first, so no load of a cell waits for another.  Looking
+// every cell up on its own with three integer divisions (k_interp_plain) takes
+// 1249 us there, this takes 196 (142 while u stays in the caches).
+template <typename T, int P>
+__global__ void __launch_bounds__(256)
+k_interp_quads(Grid g, int64_t nl, const double* __restrict__ x, const double* __restrict__ y,
+               const double* __restrict__ z, const T* __restrict__ u, T* __restrict__ U)
+{
+    const int64_t q = (int64_t)xcd_block(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x;
+    const int sub = (int)(q & 3);
+    const bool live = (q >> 2) < nl;
+    const int64_t l = live ? q >> 2 : nl - 1;     // lanes past the end repeat the last marker
+    // the stencil along this lane's axis (lane 3: the x axis again)
+    const int ax = sub == 3 ? 0 : sub;
+    const double X = ax == 0 ? x[l] : ax == 1 ? y[l] : z[l];
+    const double lo = ax == 0 ? g.lo[0] : ax == 1 ? g.lo[1] : g.lo[2];
+    const int n = ax == 0 ? g.n[0] : ax == 1 ? g.n[1] : g.n[2];
+    const int per = ax == 0 ? g.periodic[0] : ax == 1 ? g.periodic[1] : g.periodic[2];
+    T w[P];
+    const double s = __ddiv_rn(__dsub_rn(X, lo), g.h);       // grid_coord
+    const int b = axis_weights<T, P>(s, w);
+    int box[2] = {0, 0}, at[P], out = 0;                     // at: position << 1 | which box
+#pragma unroll
+    for (int o = 0; o < P; ++o) {
+        int c = b + o;
+        if (per) {
+            c = wrapi(c, n);
+        } else if (c < 0 || c >= n) {
+            out = 1;
+            c = 0;
+        }
+        const int bo = c / g.box;
+        if (o == 0)
+            box[0] = bo;
+        box[1] = bo;
+        at[o] = (c - bo * g.box + g.ngrow) << 1 | (bo != box[0]);
+    }
+    // this lane's x cell, and the rows' positions along y and z
+    int atx = quad_int<0>(at[0]);
+    T wx = quad<0>(w[0]);
+#pragma unroll
+    for (int o = 1; o < P; ++o) {
+        const int a0 = quad_int<0>(at[o]);
+        const T w0 = quad<0>(w[o]);
+        atx = sub == o ? a0 : atx;
+        wx = sub == o ? w0 : wx;
+    }
+    const bool mine = sub < P;
+    const int b0 = quad_int<0>(box[0]), b1 = quad_int<0>(box[1]);
+    const int bx = atx & 1 ? b1 : b0;
+    const int by[2] = {quad_int<1>(box[0]), quad_int<1>(box[1])};
+    const int bz[2] = {quad_int<2>(box[0]), quad_int<2>(box[1])};
+    const T* base[2][2];                                     // [z][y]
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int id = g.lut[bx + g.nb[0] * (by[j] + g.nb[1] * bz[k])];
+            out |= mine && id < 0;
+            base[k][j] = u + (int64_t)id * g.bstride + (atx >> 1);
+        }
+    out = quad_int<0>(out) | quad_int<1>(out) | quad_int<2>(out) | quad_int<3>(out);
+    T acc0 = 0, acc1 = 0, acc2 = 0;
+    int ay[P];
+    T wy[P];
+#pragma unroll
+    for (int j = 0; j < P; ++j) {
+        ay[j] = quad_int<1>(at[j]);
+        wy[j] = quad<1>(w[j]);
+    }
+#pragma unroll
+    for (int k = 0; k < P; ++k) {
+        const int az = quad_int<2>(at[k]);
+        const T wz = quad<2>(w[k]);
+        if (mine && !out) {
+#pragma unroll
+            for (int j = 0; j < P; ++j) {
+                const T* const b = az & 1 ? (ay[j] & 1 ? base[1][1] : base[1][0])
+                                          : (ay[j] & 1 ? base[0][1] : base[0][0]);
+                const T* const p = b + ((az >> 1) * g.ext + (ay[j] >> 1)) * g.ext;
+                const T wt = wy[j] * wz;
+                acc0 += p[0] * wt;
+                acc1 += p[g.cstride] * wt;
+                acc2 += p[2 * g.cstride] * wt;
+            }
+        }
+    }
+    acc0 = quad_sum(acc0 * wx);
+    acc1 = quad_sum(acc1 * wx);
+    acc2 = quad_sum(acc2 * wx);
+    const T v = sub == 0 ? acc0 : sub == 1 ? acc1 : acc2;
+    if (live && sub < 3)
+        U[3 * l + sub] = out ? (T)__builtin_nan("") : v;
 }
 
 template <typename T>
@@ -146,6 +283,81 @@ k_spread_plain(Grid g, const double* __restrict__ x, const double* __restrict__ 
     f[off] = acc0;
     f[off + g.cstride] = acc1;
     f[off + 2 * g.cstride] = acc2;
+}
+
+// The same sums by matrix products (octants.h), one wavefront per tile, from the
+// marker arrays themselves: the four stages of a source's gather (list, sorted
+// order, marker, particle) are waited for in turn, with up to 19 wavefronts per
+// CU to cover them.  Tiles go to the XCDs in contiguous eighths (workgroups are
+// dealt to them round-robin), so neighbours' sources and the pieces of a cache
+// line that x neighbours write meet in one L2.  With a raised flag (nullable)
+// every cell is NaN.  Forming every source's weights in every cell's thread took
+// 7224 us on spheres1000_256 FP32; this takes 178.
+template <typename T, int P>
+__global__ void __launch_bounds__(64)
+k_spread_list(Grid g, const double* __restrict__ x, const double* __restrict__ y,
+              const double* __restrict__ z, const int32_t* __restrict__ pid,
+              const double* __restrict__ dv, const int32_t* __restrict__ perm,
+              const int32_t* __restrict__ src_offs, const int32_t* __restrict__ src_idx,
+              const T* __restrict__ F, T* __restrict__ f, const int32_t* __restrict__ flag)
+{
+    using Oct = Octants<T, P, true>;
+    using Acc = typename Oct::Acc;
+    __shared__ __align__(16) typename Oct::Lds mem;
+    const int64_t t = xcd_block(blockIdx.x, gridDim.x);
+    if (t >= g.ntiles)
+        return;
+    const int ti = (int)t;
+    const int lo[3] = {ti % g.nt[0] * TILE, ti / g.nt[0] % g.nt[1] * TILE,
+                       ti / (g.nt[0] * g.nt[1]) * TILE};
+    const int64_t off = cell_offset(g, lo[0], lo[1], lo[2]);
+    if (off < 0)
+        return;  // whole tile lies in an uncovered box
+    Oct oct(mem);
+    const bool bad = flag && (flag[0] | flag[1]) != 0;
+    const T first = bad ? (T)__builtin_nan("") : T(0);
+    Acc acc[8];
+#pragma unroll
+    for (int o = 0; o < 8; ++o)
+        acc[o] = Acc{first, first, first, first};
+    const int s0 = src_offs[t], s1 = bad ? s0 : src_offs[t + 1];
+    for (int sb = s0; sb < s1; sb += 64) {
+        const int s = sb + oct.lane;
+        oct.clear();
+        typename Oct::Reach reach;
+        if (s < s1) {
+            const int64_t l = perm[src_idx[s]];
+            const double X[3] = {x[l], y[l], z[l]};
+            const T sc = (T)(dv[pid[l]] * g.inv_h3);
+            const T F0 = F[3 * l] * sc, F1 = F[3 * l + 1] * sc, F2 = F[3 * l + 2] * sc;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const double sa = grid_coord(g, a, X[a]);
+                const int b = stencil_base<P>(sa);
+                T w[P];
+                axis_weights_r<T, P>((T)(sa - (double)b - 0.5), w);
+                int q = g.periodic[a] ? wrapi(b, g.n[a]) - lo[a] : b - lo[a];
+                if (g.periodic[a] && q > TILE - 1)
+                    q -= g.n[a];
+                oct.put(reach, a, q, w, g.periodic[a] && g.n[a] == TILE);
+            }
+            oct.put_force(reach, F0, F1, F2);
+        }
+        oct.make_lists(reach);
+        __syncthreads();
+        oct.add(acc);
+        __syncthreads();
+    }
+    // lane: column (y, z) = (ixy, icz) of each octant, component kq, registers along x
+    if (oct.kq > 2)
+        return;
+    typedef T Row __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+    T* const at = f + off + oct.kq * g.cstride +
+                  ((int64_t)oct.icz * g.ext + oct.ixy) * g.ext;
+#pragma unroll
+    for (int o = 0; o < 8; ++o)
+        *reinterpret_cast<Row*>(at + ((int64_t)4 * (o >> 2) * g.ext + 4 * ((o >> 1) & 1)) * g.ext +
+                                4 * (o & 1)) = acc[o];
 }
 
 // Every valid cell of every covered box: u = u0 + dt f (f may be null: u = u0).
@@ -305,15 +517,6 @@ static void launch_spread(const Grid& g, int P, const ib_markers* m, const ib_bu
                                                         scale, use_dv);
 }
 
-void plain_interp(const Grid& g, int P, ib_prec prec, const ib_markers* m, const void* u,
-                  void* U, hipStream_t st)
-{
-    if (prec == IB_F64)
-        launch_interp<double>(g, P, m, (const double*)u, (double*)U, st);
-    else
-        launch_interp<float>(g, P, m, (const float*)u, (float*)U, st);
-}
-
 void plain_spread(const Grid& g, int P, ib_prec prec, const ib_markers* m, const ib_buckets* b,
                   const void* F, void* f, double scale, int use_dv, hipStream_t st)
 {
@@ -420,7 +623,22 @@ extern "C" int ib_interp(const ib_level* lv, const ib_markers* m, ib_delta delta
     if (!m || (delta != IB_DELTA3 && delta != IB_DELTA4) || (prec != IB_F32 && prec != IB_F64) ||
         m->nl < 0 || (m->nl > 0 && (!m->x || !m->y || !m->z || !u || !U)))
         return IB_EINVAL;
-    plain_interp(make_grid(lv), (int)delta, prec, m, u, U, (hipStream_t)stream);
+    if (m->nl == 0)
+        return IB_OK;
+    const Grid g = make_grid(lv);
+    const unsigned gb = (unsigned)((m->nl + 511) / 512 * 8);
+    hipStream_t st = (hipStream_t)stream;
+#define IBX_INTERP_QUADS(T, P) \
+    k_interp_quads<T, P><<<gb, 256, 0, st>>>(g, m->nl, m->x, m->y, m->z, (const T*)u, (T*)U)
+    if (prec == IB_F64 && delta == IB_DELTA3)
+        IBX_INTERP_QUADS(double, 3);
+    else if (prec == IB_F64)
+        IBX_INTERP_QUADS(double, 4);
+    else if (delta == IB_DELTA3)
+        IBX_INTERP_QUADS(float, 3);
+    else
+        IBX_INTERP_QUADS(float, 4);
+#undef IBX_INTERP_QUADS
     return launch_status();
 }
 
@@ -436,9 +654,21 @@ extern "C" int ib_spread(const ib_level* lv, const ib_markers* m, const ib_bucke
                        !b->src_idx)))
         return IB_EINVAL;
     const Grid g = make_grid(lv);
-    plain_spread(g, (int)delta, prec, m, b, F, f, 1.0, 1, (hipStream_t)stream);
-    PoisonSet ps;
-    ps.field[0] = f;
-    poison_if_flagged(b->flag, g, prec, ps, (hipStream_t)stream);
+    if (g.ntiles == 0)
+        return IB_OK;
+    const unsigned gt = (unsigned)(8 * ((g.ntiles + 7) / 8));
+    hipStream_t st = (hipStream_t)stream;
+#define IBX_SPREAD_LIST(T, P)                                                                   \
+    k_spread_list<T, P><<<gt, 64, 0, st>>>(g, m->x, m->y, m->z, m->pid, m->dv, b->perm,          \
+                                           b->src_offs, b->src_idx, (const T*)F, (T*)f, b->flag)
+    if (prec == IB_F64 && delta == IB_DELTA3)
+        IBX_SPREAD_LIST(double, 3);
+    else if (prec == IB_F64)
+        IBX_SPREAD_LIST(double, 4);
+    else if (delta == IB_DELTA3)
+        IBX_SPREAD_LIST(float, 3);
+    else
+        IBX_SPREAD_LIST(float, 4);
+#undef IBX_SPREAD_LIST
     return launch_status();
 }

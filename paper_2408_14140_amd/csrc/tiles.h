@@ -1063,52 +1063,9 @@ k_spread_blocks(const int4* __restrict__ sent, const int32_t* __restrict__ nacti
     }
 }
 
-// Matrix products D += A B of 16 x 4 by 4 x 16 values.  Operands: lane l holds
-// A[l % 16][l / 16] and B[l / 16][l % 16].  Result: register r of lane l holds
-// column l % 16 and row 4 (l / 16) + r (FP32) or l / 16 + 4 r (FP64).
-template <typename T>
-struct Mat;
-template <>
-struct Mat<float> {
-    typedef float acc __attribute__((ext_vector_type(4)));
-    static __device__ acc mac(float a, float b, acc c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-};
-template <>
-struct Mat<double> {
-    typedef double acc __attribute__((ext_vector_type(4)));
-    static __device__ acc mac(double a, double b, acc c)
-    {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-};
-
-// Number of set bits of m below this lane's.
-__device__ inline int bits_below(uint64_t m)
-{
-    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                     __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
-// One wavefront per workgroup; the tile is stored to its G slot.
-//
-// Spreading a tile is the matrix product
-//   G[(x, c)][(y, z)] = sum over sources k of (w^x_k F_k)[(x, c)] (w^y_k w^z_k)[(y, z)]
-// formed per octant of 4^3 cells on the matrix cores: 12 of 16 rows (x, c), 16
-// columns (y, z), four sources an instruction.  A source of a tile reaches 1.27
-// (P = 4) or 1.2 (P = 3) of the tile's two halves along an axis on average,
-// about a quarter of its octants, and each octant takes only the sources that
-// reach it: sources are staged 64 at a time as records in LDS (per axis the
-// weight of each of the tile's 8 cells, zero outside the stencil, and F dV/h^3,
-// or F alone when use_dv is 0), and each octant's sources are listed in order.
-// Lists are padded with an all-zero record.  A record is 27 values, an odd
-// number, so the lanes that stage (one source each) and those that read (four
-// sources, four cells) fall on different banks.  The operands need x and y at
-// one lane-dependent place, c and z at another, so a group of four sources is
-// two paired LDS reads, two products and one matrix instruction: about 6 vector
-// instructions for 4 x 64 cells x 3.
+// The tile's matrix products (octants.h) by one wavefront; the tile is stored to
+// its G slot.  Records are loaded one batch ahead and source indices two, so the
+// products hide the loads.
 //
 // Bound by memory where there are many tiles: FP32 on spheres20000_512 counts
 // 4.2 GB a launch (886 us, 4.7 TB/s; sources gathered by every tile that they
@@ -1117,12 +1074,6 @@ __device__ inline int bits_below(uint64_t m)
 // chain of its batches counts: a level of spheres1000_256 in particle order 21.6
 // us against 31.5, spheres64_128 20 against 32.  FP64, spheres8_256: 18.8 us
 // against 21.0 with the rows.
-//
-// Every cell's sum is formed in one register in list order: bit-reproducible.
-// A source whose F is not finite would turn zero weights into NaN for its
-// whole octant; such sources are added apart, to the cells they reach only.
-// Records are loaded one batch ahead and source indices two, so the products
-// hide the loads.
 // (FP64: at least two wavefronts per SIMD, which keeps the sums out of the
 // accumulator registers and saves their copies; in FP32 the compiler's own
 // choice was the faster one.)
@@ -1135,20 +1086,11 @@ k_spread_mfma(const int4* __restrict__ sent, const int32_t* __restrict__ nactive
                int use_dv, int32_t* __restrict__ queue)
 {
     using V4 = typename Vec4<T>::type;
-    using Acc = typename Mat<T>::acc;
-    typedef T Fill __attribute__((ext_vector_type(16 / sizeof(T)), may_alias));
-    typedef uint32_t Pair32 __attribute__((may_alias));
-    constexpr int S = 3 * TILE + 3, WX = 0, WY = TILE, WZ = 2 * TILE, WF = 3 * TILE;
-    constexpr int FPL = (65 * S * (int)sizeof(T) + 1023) / 1024;   // 16-byte fills per lane
-    // 64 sources, one zero record, and a word per lane for what falls outside
-    constexpr int OUT = FPL * 1024 / (int)sizeof(T);
-    __shared__ __align__(16) T rec[OUT + 64];
-    __shared__ __align__(16) uint16_t list[8 * 64];                // [octant][k][group]: offsets
-    const int lane = threadIdx.x;
-    // place of this lane's x and y (ixy) and of its c and z (icz) in an octant
-    const int ixy = sizeof(T) == 4 ? lane & 3 : (lane >> 2) & 3;
-    const int icz = sizeof(T) == 4 ? (lane >> 2) & 3 : lane & 3;
-    const int kq = lane >> 4;                              // source of a group; c of the result
+    using Oct = Octants<T, P, false>;
+    using Acc = typename Oct::Acc;
+    __shared__ __align__(16) typename Oct::Lds mem;
+    Oct oct(mem);
+    const int lane = threadIdx.x, ixy = oct.ixy, icz = oct.icz, kq = oct.kq;
     SpreadQueue sq(sent, queue, *nactive);
     auto index = [&](int at, int end) { return at + lane < end ? src_idx[at + lane] : -1; };
     V4 geo, fv;
@@ -1177,54 +1119,25 @@ k_spread_mfma(const int4* __restrict__ sent, const int32_t* __restrict__ nactive
     int lo[3];
     tile_coords(g, e0.y, lo);
     while (e0.w > 0) {
-#pragma unroll
-        for (int q = 0; q < FPL; ++q)
-            reinterpret_cast<Fill*>(rec)[lane + 64 * q] = Fill(T(0));
-        {
-            typedef uint32_t Fill4 __attribute__((ext_vector_type(4), may_alias));
-            constexpr uint32_t z = 64 * S * sizeof(T);
-            reinterpret_cast<Fill4*>(list)[lane] = Fill4(z | z << 16);
-        }
-        bool lower[3] = {false, false, false}, upper[3] = {false, false, false}, odd = false;
+        oct.clear();
+        typename Oct::Reach reach;
         if (cur >= 0) {
             int rbs[3];
             unpack_rb(rb, rbs);
-            T gw[3][P];
-            axis_weights_r<T, P>(geo.x, gw[0]);
-            axis_weights_r<T, P>(geo.y, gw[1]);
-            axis_weights_r<T, P>(geo.z, gw[2]);
-            const T sc = use_dv ? geo.w : T(1);
-            const T F0 = fv.x * sc, F1 = fv.y * sc, F2 = fv.z * sc;
-            odd = !(fabs(F0) + fabs(F1) + fabs(F2) < (T)__builtin_inf());
+            const T r[3] = {geo.x, geo.y, geo.z};
 #pragma unroll
             for (int ax = 0; ax < 3; ++ax) {
                 int b = rbs[ax] - lo[ax];
                 if (b < -(P - 1)) b += g.n[ax];
                 else if (b > TILE - 1) b -= g.n[ax];
-#pragma unroll
-                for (int o = 0; o < P; ++o)
-                    rec[(unsigned)(b + o) < (unsigned)TILE ? lane * S + TILE * ax + b + o
-                                                           : OUT + lane] = gw[ax][o];
-                lower[ax] = !odd && b < TILE / 2;
-                upper[ax] = !odd && b + P > TILE / 2;
+                T w[P];
+                axis_weights_r<T, P>(r[ax], w);
+                oct.put(reach, ax, b, w, false);
             }
-            rec[lane * S + WF] = F0;
-            rec[lane * S + WF + 1] = F1;
-            rec[lane * S + WF + 2] = F2;
+            const T sc = use_dv ? geo.w : T(1);
+            oct.put_force(reach, fv.x * sc, fv.y * sc, fv.z * sc);
         }
-        const uint64_t odds = __ballot(odd && cur >= 0);
-        int cnt[8];
-#pragma unroll
-        for (int o = 0; o < 8; ++o) {
-            const bool in = (o & 1 ? upper[0] : lower[0]) && (o & 2 ? upper[1] : lower[1]) &&
-                            (o & 4 ? upper[2] : lower[2]);
-            const uint64_t m = __ballot(in);
-            const int rank = bits_below(m);
-            cnt[o] = __popcll(m);
-            if (in)
-                list[64 * o + 16 * (rank & 3) + (rank >> 2)] =
-                    (uint16_t)(lane * S * (int)sizeof(T));
-        }
+        oct.make_lists(reach);
         __syncthreads();
         // the next batch's records and the indices of the one after it
         const bool last = pos + 64 >= e0.w;
@@ -1240,51 +1153,7 @@ k_spread_mfma(const int4* __restrict__ sent, const int32_t* __restrict__ nactive
             }
             nxt = index(nat, nend);
         }
-        // Groups gr and gr + 1 of octant o: list entries, operands, products.
-        struct Ops {
-            T wx[2], wy[2], wz[2], f[2];
-        };
-        auto entries = [&](int o, int gr) {
-            return *reinterpret_cast<const Pair32*>(list + 64 * o + 16 * kq + gr);
-        };
-        auto read = [&](int o, uint32_t e, Ops& v) {
-            const char* const base = reinterpret_cast<const char*>(rec);
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const T* const p =
-                    reinterpret_cast<const T*>(base + (h ? e >> 16 : e & 0xffffu));
-                const T* const p1 = p + ixy;
-                const T* const p2 = p + icz;
-                v.wx[h] = p1[WX + 4 * (o & 1)];
-                v.wy[h] = p1[WY + 4 * ((o >> 1) & 1)];
-                v.wz[h] = p2[WZ + 4 * (o >> 2)];
-                v.f[h] = p2[WF];
-            }
-        };
-        auto mac = [&](int o, int h, const Ops& v) {
-            acc[o] = Mat<T>::mac(v.wx[h] * v.f[h], v.wy[h] * v.wz[h], acc[o]);
-        };
-#pragma unroll
-        for (int o = 0; o < 8; ++o)
-            for (int gr = 0; 4 * gr < cnt[o]; gr += 2) {
-                Ops v;
-                read(o, entries(o, gr), v);
-                mac(o, 0, v);
-                mac(o, 1, v);
-            }
-        for (uint64_t m = odds; m; m &= m - 1) {
-            const T* const q = rec + __builtin_ctzll(m) * S;
-#pragma unroll
-            for (int o = 0; o < 8; ++o) {
-                const T wyz = q[WY + 4 * ((o >> 1) & 1) + ixy] * q[WZ + 4 * (o >> 2) + icz];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const T w = q[WX + 4 * (o & 1) + i] * wyz;
-                    if (kq < 3 && w != T(0))
-                        acc[o][i] += q[WF + kq] * w;
-                }
-            }
-        }
+        oct.add(acc);
         __syncthreads();
         if (!last) {
             pos += 64;

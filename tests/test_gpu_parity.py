@@ -762,3 +762,71 @@ def test_non_finite_force_stays_in_its_stencils(dev, delta, bad):
     fin = np.isfinite(f0)
     assert not fin.all() and np.array_equal(fin, np.isfinite(f1))
     assert rel(f1[fin], f0[fin]) <= TOL64
+
+
+def _one_tile(delta):
+    """An 8^3 grid: one tile per axis, every stencil wraps onto its own tile."""
+    return W.make_workload(f"one_tile_P{delta}", 8, 8, 0, delta, 1, np.array([3.1, 2.4]),
+                           centres=[[0.93, 0.41, 0.06], [0.3, 0.77, 0.55]], nmodes=6, K=2,
+                           cover_all=True)
+
+
+@pytest.mark.parametrize("name,mk", _SMALL_GRIDS + [("one_tile8_P4", lambda: _one_tile(4)),
+                                                    ("one_tile8_P3", lambda: _one_tile(3))],
+                         ids=[c[0] for c in _SMALL_GRIDS] + ["one_tile8_P4", "one_tile8_P3"])
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_operators_on_bounded_and_small_grids(dev, name, mk, dtype):
+    """The operators on grids where a stencil meets a wall, both sides of a
+    periodic seam in one tile, or its own tile again; the field one element off
+    its allocation, so that no vector access is aligned."""
+    import torch
+
+    import oracle as O
+    import paper_2408_14140_amd as ibx
+    announce(f"operators {name} {dtype}")
+    tdt = torch.float64 if dtype == "f64" else torch.float32
+    tol = TOL64 if dtype == "f64" else TOL32
+    wl = mk()
+    c = Case(wl, dev)
+    F = np.random.default_rng(8).normal(size=(c.m.nl, 3))
+    b = ibx.bucket(c.dl, c.dm, wl.delta)
+    u = c.u0_boxes(tdt)
+
+    def shifted(like):
+        return torch.full((like.numel() + 1,), 7.0, dtype=tdt, device=dev)[1:].view(like.shape)
+
+    us, f = shifted(u), shifted(u)
+    us.copy_(u)
+    U = ibx.interp(c.dl, c.dm, wl.delta, us)
+    ibx.spread(c.dl, c.dm, b, wl.delta, torch.as_tensor(F, device=dev).to(tdt), out=f)
+    torch.cuda.synchronize()
+    assert rel(U.cpu().numpy(), O.interp(c.g, wl.delta, c.m, wl.u0)) <= tol
+    assert c.field_rel(f, O.spread(c.g, wl.delta, c.m, F)) <= tol
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_interp_outside_the_covered_boxes_is_nan(dev, dtype):
+    """Markers whose stencils reach an uncovered box get NaN, their neighbours
+    in the same workgroup their value (41 markers: a last group of lanes that is
+    not full)."""
+    import torch
+
+    import oracle as O
+    import paper_2408_14140_amd as ibx
+    announce(f"interp outside {dtype}")
+    tdt = torch.float64 if dtype == "f64" else torch.float32
+    wl = small_workload(64, 16, 4, 3, 3, cover_all=False, k=5)
+    c = Case(wl, dev)
+    lev = wl.level
+    hole = np.argwhere(lev.lut.reshape(lev.nb[2], lev.nb[1], lev.nb[0]) < 0)
+    assert len(hole)
+    nl = 41
+    x, y, z = (np.array(a[:nl]) for a in (c.m.x, c.m.y, c.m.z))
+    bad = np.array([0, 17, 40])
+    x[bad], y[bad], z[bad] = ((hole[0][a] + 0.5) * lev.box * lev.h for a in (2, 1, 0))
+    m = ibx.markers_from(x, y, z, c.m.pid[:nl], c.m.dv, c.m.offs, dev)
+    U = ibx.interp(c.dl, m, 4, c.u0_boxes(tdt)).double().cpu().numpy()
+    ref = O.interp(c.g, 4, c.m, wl.u0)[:nl]
+    ok = np.setdiff1d(np.arange(nl), bad)
+    assert np.isnan(U[bad]).all()
+    assert rel(U[ok], ref[ok]) <= (TOL64 if dtype == "f64" else TOL32)
