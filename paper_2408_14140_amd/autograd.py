@@ -24,6 +24,7 @@ class MultidirectFunction(torch.autograd.Function):
         Fhist = torch.empty((max(ns, 1), m.nl, 3), dtype=u0.dtype, device=u0.device)
         ustar, f, F = plan.multidirect_force(level, parts, m, buckets, ns, dt,
                                              u0.detach().contiguous(), Fhist=Fhist)
+        ctx.set_materialize_grads(False)    # an unused output's gradient stays None
         ctx.save_for_backward(u0.detach(), Fhist)
         ctx.state = (plan, level, parts, m, buckets, ns, dt)
         return ustar, f, F

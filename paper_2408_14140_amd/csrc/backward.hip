@@ -24,33 +24,36 @@
 
 namespace ibx {
 
-// mode 0: a = 0; 1: a = b; 2: a += b; 3: a = u0 + dt b; 4: (a += b, c += dt b);
-// 5: (a += b, c = dt b)
+// mode 0: a = b, c = c0 + dt b (b and c0 nullable: 0; c nullable); 2: a += b;
+// 3: a = u0 + dt b; 5: (a += b, c = dt b)
 template <typename T, int MODE>
-__global__ void k_field_op(Grid g, T* __restrict__ a, const T* __restrict__ b,
-                           T* __restrict__ c, const T* __restrict__ u0, double dt)
+__global__ void __launch_bounds__(256)
+k_field_op(Grid g, T* __restrict__ a, const T* __restrict__ b, T* __restrict__ c,
+           const T* __restrict__ c0, const T* __restrict__ u0, double dt)
 {
     const int64_t per_box = (int64_t)g.box * g.box * g.box;
     const int64_t total = per_box * g.nbox;
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < total;
          q += (int64_t)gridDim.x * blockDim.x) {
         const int64_t bid = q / per_box;
-        const int64_t r = q - bid * per_box;
-        const int lx = (int)(r % g.box) + g.ngrow;
-        const int ly = (int)((r / g.box) % g.box) + g.ngrow;
-        const int lz = (int)(r / ((int64_t)g.box * g.box)) + g.ngrow;
-        const int64_t off = bid * g.bstride + ((int64_t)lz * g.ext + ly) * g.ext + lx;
+        const int r = (int)(q - bid * per_box);
+        const int row = r / g.box, lx = r - row * g.box;
+        const int lz = row / g.box, ly = row - lz * g.box;
+        const int64_t off = bid * g.bstride +
+                            ((int64_t)(lz + g.ngrow) * g.ext + ly + g.ngrow) * g.ext + lx + g.ngrow;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
             const int64_t o = off + k * g.cstride;
-            if (MODE == 0) a[o] = T(0);
-            if (MODE == 1) a[o] = b[o];
+            if (MODE == 0) {
+                const T v = b ? b[o] : T(0);
+                T w = c && c0 ? c0[o] : T(0);
+                a[o] = v;
+                w += (T)dt * v;
+                if (c)
+                    c[o] = w;
+            }
             if (MODE == 2) a[o] += b[o];
             if (MODE == 3) a[o] = u0[o] + (T)dt * b[o];
-            if (MODE == 4) {
-                a[o] += b[o];
-                c[o] += (T)dt * b[o];
-            }
             if (MODE == 5) {
                 a[o] += b[o];
                 c[o] = (T)dt * b[o];
@@ -230,19 +233,18 @@ k_particle_grads(int32_t np, const int64_t* __restrict__ offs, const double* __r
     }
 }
 
-__global__ void k_zero_d(int64_t n, double* a)
-{
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n;
-         q += (int64_t)gridDim.x * blockDim.x)
-        a[q] = 0.0;
-}
-
+// a_F = g_F (0 when null), a_Ud = 0, g_X = 0.
 template <typename T>
-__global__ void k_copy_or_zero(int64_t n, const T* __restrict__ src, T* __restrict__ dst)
+__global__ void __launch_bounds__(256)
+k_adjoint_init(int64_t n, const T* __restrict__ gF, T* __restrict__ aF, double* __restrict__ aUd,
+               double* __restrict__ gX)
 {
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n;
-         q += (int64_t)gridDim.x * blockDim.x)
-        dst[q] = src ? src[q] : T(0);
+         q += (int64_t)gridDim.x * blockDim.x) {
+        aF[q] = gF ? gF[q] : T(0);
+        aUd[q] = 0.0;
+        gX[q] = 0.0;
+    }
 }
 
 static unsigned grid_n(int64_t n)
@@ -255,12 +257,13 @@ size_t backward_workspace(const Grid& g, ib_prec prec, int64_t nl)
 {
     const size_t s = prec == IB_F64 ? 8 : 4;
     Carver cv(nullptr, 0);
-    for (int k = 0; k < 3; ++k)
+    const bool tiled = tile_spread_supported(g);
+    for (int k = 0; k < (tiled ? 2 : 3); ++k)
         cv.take<char>(s * field_elems(g));
     for (int k = 0; k < 3; ++k)
         cv.take<char>(s * 3 * nl);
     cv.take<double>(3 * nl);
-    if (tile_spread_supported(g))
+    if (tiled)
         cv.take<char>(tile_spread_workspace(g, prec, nl));
     return cv.used;
 }
@@ -275,14 +278,14 @@ static int run_backward(const Grid& g, int P, const BatchedCfg& cfg, const ib_pa
     const int64_t nl = m->nl;
     const ib_prec prec = sizeof(T) == 8 ? IB_F64 : IB_F32;
     Carver cv(ws, ws_bytes);
-    T* au = cv.take<T>(field_elems(g));
+    const bool tiled = tile_spread_supported(g);
+    T* au = tiled ? nullptr : cv.take<T>(field_elems(g));
     T* af = cv.take<T>(field_elems(g));
     T* tmp = cv.take<T>(field_elems(g));
     T* aF = cv.take<T>(3 * nl);
     T* Ub = cv.take<T>(3 * nl);
     T* Ui = cv.take<T>(3 * nl);
     double* aUd = cv.take<double>(3 * nl);
-    const bool tiled = tile_spread_supported(g);
     const size_t tsb = tiled ? tile_spread_workspace(g, prec, nl) : 0;
     void* tws = tiled ? cv.take<char>(tsb) : nullptr;
     if (!ws || !cv.ok())
@@ -294,27 +297,12 @@ static int run_backward(const Grid& g, int P, const BatchedCfg& cfg, const ib_pa
     }
     const unsigned gc = grid_n((int64_t)g.nbox * g.box * g.box * g.box);
     const unsigned gm = grid_n(nl);
-    k_field_op<T, 0><<<gc, 256, 0, st>>>(g, gu0, nullptr, nullptr, nullptr, dt);
-    if (gus)
-        k_field_op<T, 1><<<gc, 256, 0, st>>>(g, au, gus, nullptr, nullptr, dt);
-    else
-        k_field_op<T, 0><<<gc, 256, 0, st>>>(g, au, nullptr, nullptr, nullptr, dt);
-    if (gf)
-        k_field_op<T, 1><<<gc, 256, 0, st>>>(g, af, gf, nullptr, nullptr, dt);
-    else
-        k_field_op<T, 0><<<gc, 256, 0, st>>>(g, af, nullptr, nullptr, nullptr, dt);
-    if (nl > 0) {
-        k_copy_or_zero<T><<<gm, 256, 0, st>>>(3 * nl, gF, aF);
-        k_zero_d<<<gm, 256, 0, st>>>(3 * nl, aUd);
-        k_zero_d<<<gm, 256, 0, st>>>(3 * nl, gX);
-    }
+    // a_u of the last step is g_ustar: g_u0 takes it, and a_f = g_f + dt g_ustar
+    k_field_op<T, 0><<<gc, 256, 0, st>>>(g, gu0, gus, ns > 0 ? af : nullptr, gf, nullptr, dt);
+    if (nl > 0)
+        k_adjoint_init<T><<<gm, 256, 0, st>>>(3 * nl, gF, aF, aUd, gX);
     for (int mi = ns; mi >= 1; --mi) {
         const T* Fm = Fhist + (int64_t)(mi - 1) * 3 * nl;
-        // a_f holds g_f on the first step and nothing afterwards
-        if (mi == ns)
-            k_field_op<T, 4><<<gc, 256, 0, st>>>(g, gu0, au, af, nullptr, dt);
-        else
-            k_field_op<T, 5><<<gc, 256, 0, st>>>(g, gu0, au, af, nullptr, dt);
         if (nl > 0) {
             // U = J a_f and the position gradient of S^T with F^m, one gather
             if (tiled) {
@@ -324,8 +312,22 @@ static int run_backward(const Grid& g, int P, const BatchedCfg& cfg, const ib_pa
                     return rc;
             } else {
                 launch_interp_grad<T>(g, P, m, af, Ui, Fm, 1, gX, st);
+                k_marker_step<T><<<gm, 256, 0, st>>>(g, nl, dt, m->pid, m->dv, Ui, aF, aUd, Ub);
             }
-            k_marker_step<T><<<gm, 256, 0, st>>>(g, nl, dt, m->pid, m->dv, Ui, aF, aUd, Ub);
+        }
+        // Ubar, and with a_u = J^T Ubar the next step's g_u0 += a_u, a_f = dt a_u
+        // (a_f is not needed after the first step of the loop)
+        if (tiled) {
+            const int rc = tile_adjoint_step(g, P, prec, cfg, m, b, dt, Ui, aF, aUd, Ub, gu0,
+                                             mi > 1 ? af : nullptr, tws, tsb, st);
+            if (rc)
+                return rc;
+        } else {
+            plain_spread(g, P, prec, m, b, Ub, au, 1.0, 0, st);
+            if (mi > 1)
+                k_field_op<T, 5><<<gc, 256, 0, st>>>(g, gu0, au, af, nullptr, nullptr, dt);
+            else
+                k_field_op<T, 2><<<gc, 256, 0, st>>>(g, gu0, au, nullptr, nullptr, nullptr, dt);
         }
         const T* uprev = u0;
         if (mi > 1) {
@@ -336,7 +338,7 @@ static int run_backward(const Grid& g, int P, const BatchedCfg& cfg, const ib_pa
                     return rc;
             } else {
                 plain_spread(g, P, prec, m, b, Fp, tmp, 1.0, 1, st);
-                k_field_op<T, 3><<<gc, 256, 0, st>>>(g, tmp, tmp, nullptr, u0, dt);
+                k_field_op<T, 3><<<gc, 256, 0, st>>>(g, tmp, tmp, nullptr, nullptr, u0, dt);
             }
             uprev = tmp;
         }
@@ -348,15 +350,7 @@ static int run_backward(const Grid& g, int P, const BatchedCfg& cfg, const ib_pa
         } else if (nl > 0) {
             launch_interp_grad<T>(g, P, m, uprev, nullptr, Ub, 0, gX, st);
         }
-        if (tiled) {
-            const int rc = tile_spread(g, P, prec, cfg, m, b, Ub, 0, nullptr, dt, au, tws, tsb, st);
-            if (rc)
-                return rc;
-        } else {
-            plain_spread(g, P, prec, m, b, Ub, au, 1.0, 0, st);
-        }
     }
-    k_field_op<T, 2><<<gc, 256, 0, st>>>(g, gu0, au, nullptr, nullptr, dt);
     if (p->np > 0)
         k_particle_grads<<<(unsigned)p->np, 256, 0, st>>>(p->np, m->offs, m->x, m->y, m->z,
                                                           p->xc, p->om, aUd, gup, gom, gX);

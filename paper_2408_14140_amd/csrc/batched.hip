@@ -573,11 +573,11 @@ __device__ void finalize_poison(const Grid& g, T* ustar, T* f, T* Fp, int64_t nF
 }
 
 // Last step of Algorithm 1 on every valid cell of the covered boxes:
-// f = G^ns and ustar = u0 + dt G^ns, with G = 0 on tiles no marker reaches
-// (and everywhere when use_g is 0) and on the slot rows whose bit in the
-// tile's row mask (tilemask, indexed by tile) is clear.  One workgroup per
-// (box, row of tiles in y, z plane): box-wide x rows, so the box layout is
-// written in long runs.
+// f = fs G^ns (fs = 1 but for the adjoint) and ustar = u0 + dt G^ns, with G = 0
+// on tiles no marker reaches (and everywhere when use_g is 0) and on the slot
+// rows whose bit in the tile's row mask (tilemask, indexed by tile) is clear.
+// One workgroup per (box, row of tiles in y, z plane): box-wide x rows, so the
+// box layout is written in long runs.
 // In place (ustar == u0) only the cells whose force is not exactly zero are
 // read and rewritten (u0 + dt 0 = u0): inside the tiles that have a force
 // slot, most cells lie outside every stencil.  With f_acc, f += G^ns instead,
@@ -589,8 +589,8 @@ template <typename T, bool F_ACC, bool MASK>
 __global__ void __launch_bounds__(256)
 k_finalize(Grid g, const int32_t* __restrict__ slot, const T* __restrict__ G,
            const uint64_t* __restrict__ tilemask, const T* u0, T* ustar, T* __restrict__ f,
-           double dt, int use_g, int copy, const int32_t* __restrict__ flag, T* __restrict__ Fp,
-           int64_t nF)
+           double dt, T fs, int use_g, int copy, const int32_t* __restrict__ flag,
+           T* __restrict__ Fp, int64_t nF)
 {
     if (flag && (flag[0] | flag[1]) != 0) {
         finalize_poison(g, ustar, f, Fp, nF);
@@ -644,7 +644,7 @@ k_finalize(Grid g, const int32_t* __restrict__ slot, const T* __restrict__ G,
                 const int64_t o = off + c * g.cstride;
                 // streaming stores: nothing here is read again by this kernel
                 if (f && !F_ACC)
-                    __builtin_nontemporal_store(v[c], &f[o]);
+                    __builtin_nontemporal_store(fs * v[c], &f[o]);
                 else if (f && v[c] != T(0))
                     f[o] += v[c];
                 if (ustar && v[c] != T(0))
@@ -693,7 +693,7 @@ template <typename T, bool F_ACC, bool MASK, bool STREAM>
 __global__ void __launch_bounds__(256)
 k_finalize_pairs(Grid g, const int32_t* __restrict__ slot, const T* __restrict__ G,
                  const uint64_t* __restrict__ tilemask, const T* u0, T* ustar, T* __restrict__ f,
-                 double dt, int use_g, int copy, const int32_t* __restrict__ flag,
+                 double dt, T fs, int use_g, int copy, const int32_t* __restrict__ flag,
                  T* __restrict__ Fp, int64_t nF)
 {
     using V2 = typename Pair<T>::type;
@@ -761,7 +761,7 @@ k_finalize_pairs(Grid g, const int32_t* __restrict__ slot, const T* __restrict__
             for (int c = 0; c < 3; ++c) {
                 const int64_t o = off + c * g.cstride;
                 if (f && !F_ACC)
-                    put<STREAM, V2>(v[c], reinterpret_cast<V2*>(f + o));
+                    put<STREAM, V2>(fs * v[c], reinterpret_cast<V2*>(f + o));
                 else if (f && force[c])
                     *reinterpret_cast<V2*>(f + o) = w[c] + v[c];
                 if (ustar && force[c])
@@ -777,27 +777,29 @@ k_finalize_pairs(Grid g, const int32_t* __restrict__ slot, const T* __restrict__
 template <typename T, bool F_ACC, bool MASK>
 static void finalize_kernel(bool pairs, unsigned grid, unsigned gp, hipStream_t st, const Grid& g,
                             const int32_t* slot, const T* G, const uint64_t* tilemask,
-                            const T* u0, T* ustar, T* f, double dt, int use_g, int copy,
-                            const int32_t* flag, T* Fp, int64_t nF)
+                            const T* u0, T* ustar, T* f, double dt, T fs, int use_g, int copy,
+                            bool stream, const int32_t* flag, T* Fp, int64_t nF)
 {
-    if (pairs && (sizeof(T) == 8 || !copy))
+    if (pairs && stream)
         k_finalize_pairs<T, F_ACC, MASK, true><<<gp, 256, 0, st>>>(
-            g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF);
+            g, slot, G, tilemask, u0, ustar, f, dt, fs, use_g, copy, flag, Fp, nF);
     else if (pairs)
         k_finalize_pairs<T, F_ACC, MASK, false><<<gp, 256, 0, st>>>(
-            g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF);
+            g, slot, G, tilemask, u0, ustar, f, dt, fs, use_g, copy, flag, Fp, nF);
     else
         k_finalize<T, F_ACC, MASK><<<grid, 256, 0, st>>>(g, slot, G, tilemask, u0, ustar, f, dt,
-                                                         use_g, copy, flag, Fp, nF);
+                                                         fs, use_g, copy, flag, Fp, nF);
 }
 
 // With flag, the kernel also stands in for the flag check of the outputs
-// (ustar, f and Fp[0 .. nF)).
+// (ustar, f and Fp[0 .. nF)).  adjoint: f = fs G instead of G, and its stores
+// are not streamed in FP32, as the next kernel reads it.
 template <typename T>
 static void launch_finalize(unsigned grid, hipStream_t st, const Grid& g, const int32_t* slot,
                             const T* G, const uint64_t* tilemask, const T* u0, T* ustar, T* f,
                             double dt, int use_g, int f_acc, int masks,
-                            const int32_t* flag = nullptr, T* Fp = nullptr, int64_t nF = 0)
+                            const int32_t* flag = nullptr, T* Fp = nullptr, int64_t nF = 0,
+                            bool adjoint = false, double fs = 1.0)
 {
     const int copy = ustar && ustar != u0;
     // pairs of cells: rows start on even elements when ngrow is even, and the
@@ -807,18 +809,19 @@ static void launch_finalize(unsigned grid, hipStream_t st, const Grid& g, const 
                        !((uintptr_t)ustar & am) && !((uintptr_t)f & am);
     const int64_t items = (int64_t)g.nbox * (g.box / TILE) * (g.box / 2);
     const unsigned gp = (unsigned)(items < 65535 ? (items > 0 ? items : 1) : 65535);
+    const bool stream = sizeof(T) == 8 || (!copy && !adjoint);
+#define IBX_FINALIZE(ACC, MASK)                                                                \
+    finalize_kernel<T, ACC, MASK>(pairs, grid, gp, st, g, slot, G, tilemask, u0, ustar, f, dt,  \
+                                  adjoint ? (T)fs : T(1), use_g, copy, stream, flag, Fp, nF)
     if (f_acc && masks)
-        finalize_kernel<T, true, true>(pairs, grid, gp, st, g, slot, G, tilemask, u0, ustar, f,
-                                       dt, use_g, copy, flag, Fp, nF);
+        IBX_FINALIZE(true, true);
     else if (f_acc)
-        finalize_kernel<T, true, false>(pairs, grid, gp, st, g, slot, G, tilemask, u0, ustar, f,
-                                        dt, use_g, copy, flag, Fp, nF);
+        IBX_FINALIZE(true, false);
     else if (masks)
-        finalize_kernel<T, false, true>(pairs, grid, gp, st, g, slot, G, tilemask, u0, ustar, f,
-                                        dt, use_g, copy, flag, Fp, nF);
+        IBX_FINALIZE(false, true);
     else
-        finalize_kernel<T, false, false>(pairs, grid, gp, st, g, slot, G, tilemask, u0, ustar, f,
-                                         dt, use_g, copy, flag, Fp, nF);
+        IBX_FINALIZE(false, false);
+#undef IBX_FINALIZE
 }
 
 template <typename T>
@@ -1151,9 +1154,10 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
     records_and_lists<T, P>(g, cfg, p, m, b, w, st);
     double* e2 = resid ? w.e2 : nullptr;
     IBX_PROF_BEGIN(PK_INTERP_U0);
-    // the last interpolation of the loop also writes F in marker order
+    // the interpolations write the force history, and the last one F, in marker
+    // order (the last entry of the history is copied with F's order)
     launch_interp<T, P, 0>(cfg, st, g, nl, dt, w.items, w.nitems, u0, w.G, w.rmask, w.nb_u, w.s,
-                           e2, w.queue, ns == 1 ? F : nullptr, b->perm);
+                           e2, w.queue, ns == 1 ? F : Fhist, b->perm);
     IBX_PROF_END();
     if (resid)
         sum_to(w.e2, nl, w.part, resid + 0, true, st);
@@ -1165,22 +1169,21 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
         poison_outputs(g, b, ustar, f, F, resid, Fhist, nl, ns, st);
         return launch_status();
     }
-    if (Fhist)
-        k_unsort<T><<<gm, 256, 0, st>>>(nl, b->perm, w.s.f4, Fhist);
     for (int mi = 2; mi <= ns; ++mi) {
         IBX_PROF_BEGIN(PK_SPREAD);
         launch_spread<T, P>(cfg, st, g, w, b, 1);
         IBX_PROF_END();
         IBX_PROF_BEGIN(PK_INTERP_G);
         launch_interp<T, P, 1>(cfg, st, g, nl, dt, w.items, w.nitems, u0, w.G, w.rmask, w.nb_g,
-                               w.s, e2, w.queue, mi == ns ? F : nullptr, b->perm);
+                               w.s, e2, w.queue,
+                               mi == ns ? F : Fhist ? Fhist + (int64_t)(mi - 1) * 3 * nl : nullptr,
+                               b->perm);
         IBX_PROF_END();
         if (resid)
             sum_to(w.e2, nl, w.part, resid + (mi - 1), true, st);
-        if (Fhist)
-            k_unsort<T><<<gm, 256, 0, st>>>(nl, b->perm, w.s.f4,
-                                            Fhist + (int64_t)(mi - 1) * 3 * nl);
     }
+    if (Fhist)
+        k_unsort<T><<<gm, 256, 0, st>>>(nl, b->perm, w.s.f4, Fhist + (int64_t)(ns - 1) * 3 * nl);
     IBX_PROF_BEGIN(PK_SPREAD_FINAL);
     launch_spread<T, P>(cfg, st, g, w, b, 1);
     IBX_PROF_END();
@@ -1316,6 +1319,82 @@ int tile_spread(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg, const
             spread_t<float, 4>(g, cfg, m, b, (const float*)v, use_dv, (const float*)u0, dt,
                                (float*)out, ws, ws_bytes, st);
     }
+    return launch_status();
+}
+
+// One step of the adjoint on the markers, in bucket order: a_F += (dV/h^3) Ui,
+// a_Ud += a_F/dt, Ubar = -a_F/dt, which also goes to f4 for the spreading.
+template <typename T>
+__global__ void __launch_bounds__(256)
+k_adjoint_markers(int64_t nl, double dt, double inv_h3, const int32_t* __restrict__ perm,
+                  const int32_t* __restrict__ pid, const double* __restrict__ dv,
+                  const T* __restrict__ Ui, T* __restrict__ aF, double* __restrict__ aUd,
+                  T* __restrict__ Ub, typename Vec4<T>::type* __restrict__ f4,
+                  int32_t* __restrict__ queue)
+{
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < NXCD * NQ)
+        queue[i * QSTRIDE] = 0;
+    if (i >= nl)
+        return;
+    const int64_t l = perm[i];
+    const T sc = (T)(dv[pid[l]] * inv_h3);
+    const T idt = (T)(1.0 / dt);
+    T ub[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const T a = aF[3 * l + c] + sc * Ui[3 * l + c];
+        aF[3 * l + c] = a;
+        aUd[3 * l + c] += (double)a * (1.0 / dt);
+        ub[c] = -a * idt;
+        Ub[3 * l + c] = ub[c];
+    }
+    typename Vec4<T>::type q;
+    q.x = ub[0];
+    q.y = ub[1];
+    q.z = ub[2];
+    q.w = T(0);
+    f4[i] = q;
+}
+
+template <typename T, int P>
+static void adjoint_step_t(const Grid& g, const BatchedCfg& cfg, const ib_markers* m,
+                           const ib_buckets* b, double dt, const T* Ui, T* aF, double* aUd, T* Ub,
+                           T* gu0, T* af, void* ws, size_t bytes, hipStream_t st)
+{
+    size_t need = 0;
+    const int64_t nl = m->nl;
+    BatchedWs<T> w = carve_batched<T>(g, nl, cfg.bw, ws, bytes, &need);
+    const int64_t nfin = (int64_t)g.nbox * (g.box / TILE) * g.box;
+    const unsigned gfin = (unsigned)(nfin < 65535 ? (nfin > 0 ? nfin : 1) : 65535);
+    if (nl > 0) {
+        k_adjoint_markers<T><<<(unsigned)((nl + 255) / 256), 256, 0, st>>>(
+            nl, dt, g.inv_h3, b->perm, m->pid, m->dv, Ui, aF, aUd, Ub, w.s.f4, w.queue);
+        launch_spread<T, P>(cfg, st, g, w, b, 0);
+    }
+    launch_finalize<T>(gfin, st, g, w.slot, w.G, w.tmask, gu0, gu0, af, 1.0, nl > 0, 0, cfg.masks,
+                       nullptr, nullptr, 0, true, dt);
+}
+
+int tile_adjoint_step(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,
+                      const ib_markers* m, const ib_buckets* b, double dt, const void* Ui,
+                      void* aF, double* aUd, void* Ub, void* gu0, void* af, void* ws,
+                      size_t ws_bytes, hipStream_t st)
+{
+    if (ws_bytes < tile_spread_workspace(g, prec, m->nl))
+        return IB_EWORKSPACE;
+#define IBX_ADJOINT_STEP(T, P)                                                                 \
+    adjoint_step_t<T, P>(g, cfg, m, b, dt, (const T*)Ui, (T*)aF, aUd, (T*)Ub, (T*)gu0, (T*)af, ws, \
+                         ws_bytes, st)
+    if (prec == IB_F64 && P == 3)
+        IBX_ADJOINT_STEP(double, 3);
+    else if (prec == IB_F64)
+        IBX_ADJOINT_STEP(double, 4);
+    else if (P == 3)
+        IBX_ADJOINT_STEP(float, 3);
+    else
+        IBX_ADJOINT_STEP(float, 4);
+#undef IBX_ADJOINT_STEP
     return launch_status();
 }
 

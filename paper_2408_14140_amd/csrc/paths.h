@@ -51,6 +51,13 @@ int tile_spread_setup(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,
 int tile_spread(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg, const ib_markers* m,
                 const ib_buckets* b, const void* v, int use_dv, const void* u0, double dt,
                 void* out, void* ws, size_t ws_bytes, hipStream_t st);
+// One step of the adjoint with the same set-up: a_F += (dV/h^3) Ui, a_Ud += a_F/dt
+// and Ub = -a_F/dt on the markers (marker order), then with G = J^T Ub the fields
+// gu0 += G and af = dt G (af nullable) on every valid covered cell, in one pass.
+int tile_adjoint_step(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,
+                      const ib_markers* m, const ib_buckets* b, double dt, const void* Ui,
+                      void* aF, double* aUd, void* Ub, void* gu0, void* af, void* ws,
+                      size_t ws_bytes, hipStream_t st);
 // With the same set-up: U = J fld (U nullable, marker order) and
 // gX += sc sum over the stencil of (fld . v_l) grad_X w_l, sc = dV/h^3
 // (use_dv) or 1, for a field fld in the box layout and v [nl][3].

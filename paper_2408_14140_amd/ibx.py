@@ -527,10 +527,11 @@ class Plan:
         lc = level.c
         nb = int(_bwd_ws(self._h, C.byref(lc), m.nl))
         ws = torch.empty(max(nb, 1), dtype=torch.uint8, device=dev)
-        g_u0 = torch.zeros_like(u0)
-        g_up = torch.zeros((parts.np, 3), dtype=torch.float64, device=dev)
-        g_om = torch.zeros((parts.np, 3), dtype=torch.float64, device=dev)
-        g_X = torch.zeros((m.nl, 3), dtype=torch.float64, device=dev)
+        # the library writes all but the ghost cells of g_u0
+        g_u0 = torch.zeros_like(u0) if level.ngrow else torch.empty_like(u0)
+        g_up = torch.empty((parts.np, 3), dtype=torch.float64, device=dev)
+        g_om = torch.empty((parts.np, 3), dtype=torch.float64, device=dev)
+        g_X = torch.empty((m.nl, 3), dtype=torch.float64, device=dev)
         pc, mc, bc = parts.c, m.c, b.c
         _check(_backward(self._h, C.byref(lc), C.byref(pc), C.byref(mc), C.byref(bc), int(ns),
                          float(dt), _ptr(u0), _ptr(Fhist), _ptr(g_ustar), _ptr(g_f), _ptr(g_F),

@@ -184,3 +184,44 @@ def test_adjoint_matches_central_differences_on_gpu(dev):
                              eps)
         an = sum(float((g_all[k] * v[k]).sum().item()) for k in v)
         assert abs(fd - an) <= bound, (fd, an, bound)
+
+
+@pytest.mark.parametrize("n,ns,delta,ngrow,dtype", [(32, 3, 4, 2, "f32"), (32, 1, 3, 2, "f64"),
+                                                    (32, 2, 4, 1, "f32"), (32, 2, 3, 2, "f32"),
+                                                    (8, 2, 3, 2, "f64"), (32, 0, 4, 2, "f32")])
+def test_missing_gradients_count_as_zeros(dev, n, ns, delta, ngrow, dtype):
+    """A gradient that is not given is a field of zeros, bit for bit; each entry
+    of the force history is the force of a loop of that many steps; and with no
+    step at all the gradient of u0 is that of ustar."""
+    import torch
+
+    import paper_2408_14140_amd as ibx
+    announce(f"adjoint without gradients n={n} ns={ns} P={delta} ngrow={ngrow} {dtype}")
+    wl = W.make_workload(f"grad_missing_{n}", n, min(n, 16), ngrow, delta, max(ns, 1),
+                         np.array([3.2] if n == 8 else [6.3, 7.7]), seed=21, nmodes=4, K=2,
+                         cover_all=True)
+    c = Case(wl, dev)
+    tdt = torch.float64 if dtype == "f64" else torch.float32
+    plan = ibx.Plan(wl.delta, tdt, 0)
+    b = ibx.bucket(c.dl, c.dm, wl.delta)
+    u0 = torch.as_tensor(W.to_boxes(wl.u0, c.lev, fill=0.0), device=dev).to(tdt)
+    Fhist = torch.full((max(ns, 1), c.dm.nl, 3), np.nan, dtype=tdt, device=dev)
+    _, f, F = plan.multidirect_force(c.dl, c.parts, c.dm, b, ns, wl.dt, u0, Fhist=Fhist)
+    for k in range(1, ns + 1):
+        _, _, Fk = plan.multidirect_force(c.dl, c.parts, c.dm, b, k, wl.dt, u0)
+        assert torch.equal(Fk, Fhist[k - 1])
+    rng = np.random.default_rng(9)
+    full = [torch.as_tensor(rng.normal(size=t.shape), device=dev).to(tdt) for t in (u0, f, F)]
+    zero = [torch.zeros_like(t) for t in full]
+    for k in range(3):
+        given = [full[q] if q == k else None for q in range(3)]
+        padded = [full[q] if q == k else zero[q] for q in range(3)]
+        a = plan.backward(c.dl, c.parts, c.dm, b, ns, wl.dt, u0, Fhist, *given)
+        z = plan.backward(c.dl, c.parts, c.dm, b, ns, wl.dt, u0, Fhist, *padded)
+        for x, y in zip(a, z):
+            assert torch.equal(x, y)
+        assert all(torch.isfinite(x).all() for x in a)
+        if ns == 0:
+            want = _valid(c.lev, full[0]) if k == 0 else torch.zeros_like(_valid(c.lev, u0))
+            assert torch.equal(_valid(c.lev, a[0]), want)
+            assert all((x == 0).all() for x in a[1:])
