@@ -866,7 +866,7 @@ struct BatchedWs {
     uint64_t* rmask;   // per slot: bit r set when row r of the slot is not all zeros
     uint64_t* tmask;   // the same per tile (stale on tiles without a slot)
     void* scan;
-    int64_t max_items;
+    int64_t nl, max_items;
     int64_t *nb_u, *nb_g;   // [item][9 NBX] element offsets of the neighbouring tiles
 };
 
@@ -884,6 +884,7 @@ static BatchedWs<T> carve_batched(const Grid& g, int64_t nl, int bw, void* ws, s
     w.s.d = cv.take<T>(3 * nl);
     w.e2 = cv.take<double>(nl);
     w.part = cv.take<double>(sum_partials(nl));
+    w.nl = nl;
     w.max_items = T_ + nl / bw + 1;
     w.items = cv.take<Item>(w.max_items);
     w.item_cnt = cv.take<int32_t>(T_);
@@ -989,12 +990,29 @@ static void launch_interp(const BatchedCfg& cfg, hipStream_t st, const Grid& g, 
                                         s, e2, Fout, perm, vin, gX, use_dv, queue);
 }
 
-// The tile spreading by kernel K.
-template <auto K, typename T>
+// Wavefronts that share a tile in the spreading.  One, unless the call's tiles
+// leave the chip idle: with W of them a workgroup takes W times the staging memory,
+// so that 3 (W = 4) or 7 (W = 2) tiles fit on a CU at once.  How many tiles have
+// markers is known on the device only; the host has their number on the grid, and
+// that of the markers, 27 a tile or more.  Loops of five steps on 256^3 (256 CUs),
+// spheres of 16 cells, W = 1, 2, 4 in us: 24 spheres, 19 K markers, 185, 158, 144;
+// 96, 77 K, 410, 379, 428; 160, 129 K, 495, 499, 587; 320, 621, 671, 841 (4-point
+// kernel; the 3-point one 151, 131, 120; 357, 336, 369; 445, 438, 497; 532, 559,
+// 690).  Small spheres cross at the same marker counts, clumps of overlapping
+// spheres, with fewer tiles, later.
+static int spread_waves(const BatchedCfg& cfg, const Grid& g, int64_t nl)
+{
+    if (nl <= 128 * (int64_t)cfg.ncu || g.ntiles <= 3 * (int64_t)cfg.ncu)
+        return 4;
+    return nl <= 512 * (int64_t)cfg.ncu || g.ntiles <= 7 * (int64_t)cfg.ncu ? 2 : 1;
+}
+
+// The tile spreading by kernel K, W wavefronts a workgroup.
+template <auto K, int W = 1, typename T>
 static void spread_with(const BatchedCfg& cfg, hipStream_t st, const Grid& g,
                         const BatchedWs<T>& w, const ib_buckets* b, int use_dv)
 {
-    K<<<resident_grid<K, 64>(cfg.ncu, cfg.wgs_s), 64, 0, st>>>(
+    K<<<resident_grid<K, 64 * W>(cfg.ncu, cfg.wgs_s), 64 * W, 0, st>>>(
         w.sent, w.nactive, b->src_idx, g, w.s, w.G, w.rmask, w.tmask, use_dv, w.queue);
 }
 
@@ -1004,6 +1022,11 @@ static void spread_kernel(const BatchedCfg& cfg, hipStream_t st, const Grid& g,
 {
     if constexpr (sizeof(T) == 4) {
         if (!cfg.products) {
+            const int waves = spread_waves(cfg, g, w.nl);
+            if (waves == 4)
+                return spread_with<k_spread_waves<T, P, MASK, 4>, 4>(cfg, st, g, w, b, use_dv);
+            if (waves == 2)
+                return spread_with<k_spread_waves<T, P, MASK, 2>, 2>(cfg, st, g, w, b, use_dv);
             // one 2 x 2 x 2 block per lane for the 3-point kernel, one row per
             // lane for the 4-point one (the faster layout for each width)
             if constexpr (P == 3)

@@ -1063,6 +1063,326 @@ k_spread_blocks(const int4* __restrict__ sent, const int32_t* __restrict__ nacti
     }
 }
 
+// The same sums by W wavefronts a tile, for calls with fewer tiles than the chip
+// has room for wavefronts: there the time of a launch is one wavefront's chain
+// through the batches of its tile.  The W wavefronts stage W batches at once, each
+// as k_spread_tiles (P = 4) or k_spread_blocks (P = 3) does, with the same caps
+// and pieces, and form each batch's pieces side by side.  What has to stay in
+// order, the visits below the cap and the adding of the pieces, batch after batch,
+// is split over the cells: each wavefront holds 8 / W of a lane's 8 cells.  Every
+// cell's sum has the terms and the order of the kernels above: the same bits.
+// A launch with one wavefront a tile and here, in us: one sphere on 64^3, 14.0 and
+// 9.0 (W = 4); 60 spheres in the channel 96 x 160 x 64, 18.6 and 10.4 (W = 4); 64
+// spheres on 128^3, 27.6 and 21.2 (W = 2; 24.2 with 4, whose 43 KB of LDS let three
+// workgroups run on a CU).
+template <typename T, int P, int W>
+struct SpreadLanes {
+    static constexpr bool ROWS = P == 4;
+    static constexpr int NX = ROWS ? TILE : P + 2;          // staged x, and y or z, weights
+    static constexpr int NY = ROWS ? P : P + 2;
+    static constexpr int NW = NX + 2 * NY + 3;
+    static constexpr int NBUF = NW * 64;
+    static constexpr int MAXP = NBUF / (3 * TILE) < 64 ? NBUF / (3 * TILE) : 64;
+    struct __align__(16) Batch {
+        T piece[MAXP * 3 * TILE];       // sums of the pieces, [piece][cell][c]
+        T w[NBUF];                      // staged weights and forces
+        uint64_t rest[64];              // a lane's sources
+        int2 sb[64];
+        int32_t np[64];                 // its pieces: count | first << 8
+        int32_t owner[MAXP];            // piece -> lane | its number there << 8
+        int32_t K;
+    };
+    static constexpr int SY = NX * 64, SZ = SY + NY * 64, SF = SZ + NY * 64;
+
+    // Stages this lane's source (in: it has one) and returns the lane's sources.
+    static __device__ uint64_t stage(Batch& m, int lane, bool in, int i, const Grid& g,
+                                     const int (&lo)[3], const MarkerData<T>& s, int use_dv)
+    {
+        int b[3] = {64, 64, 64};        // no cell for lanes past the list
+        if (in) {
+            const typename Vec4<T>::type gq = s.geo[i];
+            const typename Vec4<T>::type Fv = s.f4[i];
+            int rb[3];
+            unpack_rb(s.rb[i], rb);
+            T gw[3][P];
+            axis_weights_r<T, P>(gq.x, gw[0]);
+            axis_weights_r<T, P>(gq.y, gw[1]);
+            axis_weights_r<T, P>(gq.z, gw[2]);
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                int v = rb[ax] - lo[ax];
+                if (v < -(P - 1)) v += g.n[ax];
+                else if (v > TILE - 1) v -= g.n[ax];
+                b[ax] = v;
+            }
+            if (ROWS) {
+#pragma unroll
+                for (int xx = 0; xx < TILE; ++xx)
+                    m.w[xx * 64 + lane] = T(0);
+#pragma unroll
+                for (int o = 0; o < P; ++o)
+                    if ((unsigned)(b[0] + o) < (unsigned)TILE)
+                        m.w[(b[0] + o) * 64 + lane] = gw[0][o];
+#pragma unroll
+                for (int o = 0; o < P; ++o) {
+                    m.w[SY + o * 64 + lane] = gw[1][o];
+                    m.w[SZ + o * 64 + lane] = gw[2][o];
+                }
+                m.sb[lane] = make_int2(lane - 64 * b[1], lane - 64 * b[2]);
+            } else {
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax) {
+                    T* sa = m.w + ax * SY;
+                    sa[lane] = T(0);
+#pragma unroll
+                    for (int o = 0; o < P; ++o)
+                        sa[(o + 1) * 64 + lane] = gw[ax][o];
+                    sa[(P + 1) * 64 + lane] = T(0);
+                }
+                const int ox = lane - 64 * (b[0] - 1), oy = lane - 64 * (b[1] - 1);
+                m.sb[lane] = make_int2((int)(((unsigned)ox & 0xffffu) | ((unsigned)oy << 16)),
+                                       lane - 64 * (b[2] - 1));
+            }
+            const T sc = use_dv ? gq.w : T(1);
+            m.w[SF + lane] = Fv.x * sc;
+            m.w[SF + 64 + lane] = Fv.y * sc;
+            m.w[SF + 128 + lane] = Fv.z * sc;
+        }
+        if (ROWS) {
+            const int ly = lane & 7, lz = lane >> 3;
+            uint64_t my = 0, mz = 0;
+#pragma unroll
+            for (int k = 0; k < TILE; ++k) {
+                const uint64_t yk = __ballot((unsigned)(k - b[1]) < (unsigned)P);
+                const uint64_t zk = __ballot((unsigned)(k - b[2]) < (unsigned)P);
+                my = ly == k ? yk : my;
+                mz = lz == k ? zk : mz;
+            }
+            return my & mz;
+        }
+        uint64_t mx = 0, my = 0, mz = 0;
+#pragma unroll
+        for (int cb = 0; cb < TILE / 2; ++cb) {
+            const uint64_t xk = __ballot((unsigned)(2 * cb - b[0] + 1) < (unsigned)(P + 1));
+            const uint64_t yk = __ballot((unsigned)(2 * cb - b[1] + 1) < (unsigned)(P + 1));
+            const uint64_t zk = __ballot((unsigned)(2 * cb - b[2] + 1) < (unsigned)(P + 1));
+            mx = (lane & 3) == cb ? xk : mx;
+            my = ((lane >> 2) & 3) == cb ? yk : my;
+            mz = lane >> 4 == cb ? zk : mz;
+        }
+        return mx & my & mz;
+    }
+
+    // Adds source k to cells `first` .. first + N - 1 of lane `own`: along x of its
+    // row, or x, then y, then z of its block.
+    template <int N>
+    static __device__ void visit(const Batch& m, int own, int first, int k, T (&a)[N][3])
+    {
+        const int2 o = m.sb[k];
+        const T f0 = m.w[SF + k], f1 = m.w[SF + 64 + k], f2 = m.w[SF + 128 + k];
+        if (ROWS) {
+            const T wyz = m.w[SY + (own & 7) * 64 + o.x] * m.w[SZ + (own >> 3) * 64 + o.y];
+            const T c0 = f0 * wyz, c1 = f1 * wyz, c2 = f2 * wyz;
+            const T* px = m.w + 64 * first + k;
+#pragma unroll
+            for (int x = 0; x < N; ++x) {
+                const T wv = px[64 * x];
+                a[x][0] += c0 * wv;
+                a[x][1] += c1 * wv;
+                a[x][2] += c2 * wv;
+            }
+        } else {
+            const int ox = (int)(int16_t)(o.x & 0xffff), oy = o.x >> 16, oz = o.y;
+            const T* px = m.w + 128 * (own & 3) + ox;
+            const T* py = m.w + SY + 128 * ((own >> 2) & 3) + oy;
+            const T* pz = m.w + SZ + 128 * (own >> 4) + oz;
+            if (N < 8)
+                pz += 64 * (first >> 2);
+            if (N < 4)
+                py += 64 * ((first >> 1) & 1);
+            T t[N / 2];
+#pragma unroll
+            for (int r = 0; r < N / 2; ++r)
+                t[r] = py[64 * (r & 1)] * pz[64 * (r >> 1)];
+#pragma unroll
+            for (int xi = 0; xi < 2; ++xi) {
+                const T wx = px[64 * xi];
+                const T u0 = f0 * wx, u1 = f1 * wx, u2 = f2 * wx;
+#pragma unroll
+                for (int r = 0; r < N / 2; ++r) {
+                    a[2 * r + xi][0] += u0 * t[r];
+                    a[2 * r + xi][1] += u1 * t[r];
+                    a[2 * r + xi][2] += u2 * t[r];
+                }
+            }
+        }
+    }
+};
+
+template <typename T, int P, bool MASK, int W>
+__global__ void __launch_bounds__(64 * W)
+k_spread_waves(const int4* __restrict__ sent, const int32_t* __restrict__ nactive,
+               const int32_t* __restrict__ src_idx, Grid g, MarkerData<T> s,
+               T* __restrict__ G, uint64_t* __restrict__ rmask, uint64_t* __restrict__ tmask,
+               int use_dv, int32_t* __restrict__ queue)
+{
+    using L = SpreadLanes<T, P, W>;
+    constexpr int NC = TILE / W;                            // cells of a lane in a wavefront
+    __shared__ typename L::Batch bat[W];
+    __shared__ uint64_t rows[W];
+    __shared__ int4 entry;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    SpreadQueue sq(sent, queue, *nactive);
+    auto next = [&] {                   // the entry of every wavefront, from the first one's queue
+        if (wv == 0) {
+            const int4 e = sq.next();
+            if (lane == 0)
+                entry = e;
+        }
+    };
+    next();
+    __syncthreads();
+    int4 ent = entry;
+    int pf = ent.z + (int)threadIdx.x < ent.w ? src_idx[ent.z + threadIdx.x] : 0;
+    __syncthreads();
+    while (ent.w > 0) {
+        next();
+        int lo[3];
+        tile_coords(g, ent.y, lo);
+        T acc[NC][3];
+#pragma unroll
+        for (int q = 0; q < NC; ++q)
+            acc[q][0] = acc[q][1] = acc[q][2] = T(0);
+        int4 nent = ent;
+        for (int s0 = ent.z; s0 < ent.w; s0 += 64 * W) {
+            typename L::Batch& mine = bat[wv];
+            const bool in = s0 + (int)threadIdx.x < ent.w;
+            const uint64_t M = L::stage(mine, lane, in, pf, g, lo, s, use_dv);
+            const int n = __popcll(M);
+            const int nmax = wave_max(n);
+            int K = nmax;
+            if (nmax > 1) {
+                K = max(1, (wave_sum(n) + 63 + L::MAXP) / (64 + L::MAXP));
+                while (K < nmax && wave_sum(n > K ? small_div(n - 1, K) : 0) > L::MAXP)
+                    ++K;
+            }
+            const int np = n > K ? small_div(n - 1, K) : 0;
+            const int ps = wave_exclusive_sum(np);
+            const int NP = wave_sum(np);
+            mine.rest[lane] = M;
+            mine.np[lane] = np | ps << 8;
+            for (int q = 0; q < np; ++q)
+                mine.owner[ps + q] = lane | q << 8;
+            if (lane == 0)
+                mine.K = K;
+            __syncthreads();
+            nent = entry;
+            const bool more = s0 + 64 * W < ent.w;
+            const int n0 = (more ? s0 + 64 * W : nent.z) + (int)threadIdx.x;
+            pf = n0 < (more ? ent.w : nent.w) ? src_idx[n0] : 0;
+            if (lane < NP) {
+                const int own = mine.owner[lane] & 255, q = mine.owner[lane] >> 8;
+                uint64_t m = drop_low_bits(mine.rest[own], (q + 1) * K);
+                T a[TILE][3];
+#pragma unroll
+                for (int x = 0; x < TILE; ++x)
+                    a[x][0] = a[x][1] = a[x][2] = T(0);
+                for (int tt = 0; tt < K && m; ++tt) {
+                    const int k = __builtin_ctzll(m);
+                    m &= m - 1;
+                    L::visit(mine, own, 0, k, a);
+                }
+#pragma unroll
+                for (int x = 0; x < TILE; ++x)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c)
+                        mine.piece[lane * 3 * TILE + 3 * x + c] = a[x][c];
+            }
+            for (int j = 0; j < W; ++j) {
+                const typename L::Batch& bj = bat[j];
+                uint64_t m = bj.rest[lane];
+                const int Kj = bj.K;
+                for (int tt = 0; tt < Kj && m; ++tt) {
+                    const int k = __builtin_ctzll(m);
+                    m &= m - 1;
+                    L::visit(bj, lane, NC * wv, k, acc);
+                }
+                if (j == 0)
+                    __syncthreads();                        // the pieces are there
+                const int npj = bj.np[lane] & 255, psj = bj.np[lane] >> 8;
+                for (int q = 0; q < npj; ++q) {
+                    const T* pp = bj.piece + (psj + q) * 3 * TILE + 3 * NC * wv;
+#pragma unroll
+                    for (int x = 0; x < NC; ++x)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c)
+                            acc[x][c] += pp[3 * x + c];
+                }
+            }
+            __syncthreads();
+        }
+        uint64_t rm = ~0ull;
+        if constexpr (MASK) {
+            uint64_t some = 0;
+            if (L::ROWS) {
+                bool nz = false;
+#pragma unroll
+                for (int x = 0; x < NC; ++x)
+                    nz = nz || acc[x][0] != T(0) || acc[x][1] != T(0) || acc[x][2] != T(0);
+                some = __ballot(nz);
+            } else {
+                // row (y, z) is bit y + 8 z, held by the four lanes of its blocks
+#pragma unroll
+                for (int r = 0; r < NC / 2; ++r) {
+                    bool nz = false;
+#pragma unroll
+                    for (int x = 2 * r; x < 2 * r + 2; ++x)
+                        nz = nz || acc[x][0] != T(0) || acc[x][1] != T(0) || acc[x][2] != T(0);
+                    const uint64_t bl = __ballot(nz);
+                    const int at = NC * wv / 2 + r;         // y & 1 | (z & 1) << 1 of these rows
+                    const int ry = lane & 7, rz = lane >> 3;
+                    some |= __ballot(((ry & 1) | (rz & 1) << 1) == at &&
+                                     ((bl >> (4 * (ry >> 1) + 16 * (rz >> 1))) & 15) != 0);
+                }
+            }
+            if (lane == 0)
+                rows[wv] = some;
+            __syncthreads();
+            rm = 0;
+#pragma unroll
+            for (int j = 0; j < W; ++j)
+                rm |= rows[j];
+            if (threadIdx.x == 0) {
+                rmask[ent.x] = rm;
+                tmask[ent.y] = rm;
+            }
+        }
+        T* gs = G + (int64_t)ent.x * 3 * TILE_CELLS;
+        if (L::ROWS) {
+            if ((rm >> lane) & 1)
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+#pragma unroll
+                    for (int x = 0; x < NC; ++x)
+                        gs[c * TILE_CELLS + TILE * lane + NC * wv + x] = acc[x][c];
+        } else {
+#pragma unroll
+            for (int r = 0; r < NC / 2; ++r) {
+                const int at = NC * wv / 2 + r;
+                const int row = 2 * ((lane >> 2) & 3) + (at & 1) + TILE * (2 * (lane >> 4) + (at >> 1));
+                if ((rm >> row) & 1)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c)
+#pragma unroll
+                        for (int x = 0; x < 2; ++x)
+                            gs[c * TILE_CELLS + TILE * row + 2 * (lane & 3) + x] = acc[2 * r + x][c];
+            }
+        }
+        ent = nent;
+    }
+}
+
 // The tile's matrix products (octants.h) by one wavefront; the tile is stored to
 // its G slot.  Records are loaded one batch ahead and source indices two, so the
 // products hide the loads.

@@ -830,3 +830,44 @@ def test_interp_outside_the_covered_boxes_is_nan(dev, dtype):
     ok = np.setdiff1d(np.arange(nl), bad)
     assert np.isnan(U[bad]).all()
     assert rel(U[ok], ref[ok]) <= (TOL64 if dtype == "f64" else TOL32)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("masks", [False, True], ids=["", "masks"])
+@pytest.mark.parametrize("delta", [3, 4])
+def test_few_and_many_markers_spread_the_same_bits(dev, delta, masks, dtype):
+    """The spreading takes four, two or one wavefronts a tile by the number of
+    markers: a clump of overlapping spheres (tiles with many batches of sources)
+    gives the same bits on its cells whatever is placed far from it."""
+    import oracle as O
+    import torch
+
+    import paper_2408_14140_amd as ibx
+    announce(f"spread by marker count P={delta} masks={masks} {dtype}")
+    n, rng = 128, np.random.default_rng(31)
+    near = 0.25 + np.clip(rng.normal(0.0, 0.05, (12, 3)), -0.1, 0.1)
+    far = np.concatenate([rng.uniform(0.1, 0.9, (220, 2)), rng.uniform(0.62, 0.9, (220, 1))], 1)
+    up, om = rng.normal(0.0, 0.1, (232, 3)), rng.normal(0.0, 1.0, (232, 3))
+    u0 = rng.normal(size=(3, n, n, n))
+    tdt = torch.float32 if dtype == "f32" else torch.float64
+    got = []
+    for k in (0, 60, 220):
+        xc = np.concatenate([near, far[:k]])
+        d = np.full(len(xc), 16.0 / n)
+        lev = W.make_workload("bits", n, 32, 2, delta, 2, d * n, centres=xc, cover_all=True,
+                              with_field=False).level
+        m = O.build_markers(xc, d, lev.h)
+        dl = ibx.device_level(lev, dev)
+        dm = ibx.markers_from(m.x, m.y, m.z, m.pid, m.dv, m.offs, dev)
+        plan = ibx.Plan(delta, tdt, 2, row_masks=masks)
+        b = ibx.bucket(dl, dm, delta)
+        u = torch.as_tensor(W.to_boxes(u0, lev, fill=0.0), device=dev).to(tdt)
+        parts = ibx.particles(xc, d, up[:len(xc)], om[:len(xc)], dev)
+        _, f, F = plan.multidirect_force(dl, parts, dm, b, 2, 0.5 / n, u)
+        own = int(m.offs[12])
+        got.append((dm.nl, W.from_boxes(f.double().cpu().numpy(), lev)[:, :60], F[:own].cpu()))
+    assert got[0][0] <= 128 * 256 < got[1][0] <= 512 * 256 < got[2][0]
+    assert np.abs(got[0][1]).max() > 0
+    for _, f, F in got[1:]:
+        assert np.array_equal(f, got[0][1])
+        assert torch.equal(F, got[0][2])
