@@ -999,12 +999,15 @@ static void launch_interp(const BatchedCfg& cfg, hipStream_t st, const Grid& g, 
 // 96, 77 K, 410, 379, 428; 160, 129 K, 495, 499, 587; 320, 621, 671, 841 (4-point
 // kernel; the 3-point one 151, 131, 120; 357, 336, 369; 445, 438, 497; 532, 559,
 // 690).  Small spheres cross at the same marker counts, clumps of overlapping
-// spheres, with fewer tiles, later.
-static int spread_waves(const BatchedCfg& cfg, const Grid& g, int64_t nl)
+// spheres, with fewer tiles, later.  The matrix products, whose wavefronts do more
+// at a time, cross two against one earlier: FP64, 4-point, 24 spheres 265, 247,
+// 235; 48, 39 K markers, 442, 414, 417; 96, 588, 596, 630.
+static int spread_waves(const BatchedCfg& cfg, const Grid& g, int64_t nl, bool products)
 {
-    if (nl <= 128 * (int64_t)cfg.ncu || g.ntiles <= 3 * (int64_t)cfg.ncu)
+    const int64_t cu = cfg.ncu;
+    if (nl <= 128 * cu || g.ntiles <= 3 * cu)
         return 4;
-    return nl <= 512 * (int64_t)cfg.ncu || g.ntiles <= 7 * (int64_t)cfg.ncu ? 2 : 1;
+    return nl <= (products ? 256 : 512) * cu || g.ntiles <= 7 * cu ? 2 : 1;
 }
 
 // The tile spreading by kernel K, W wavefronts a workgroup.
@@ -1022,7 +1025,7 @@ static void spread_kernel(const BatchedCfg& cfg, hipStream_t st, const Grid& g,
 {
     if constexpr (sizeof(T) == 4) {
         if (!cfg.products) {
-            const int waves = spread_waves(cfg, g, w.nl);
+            const int waves = spread_waves(cfg, g, w.nl, false);
             if (waves == 4)
                 return spread_with<k_spread_waves<T, P, MASK, 4>, 4>(cfg, st, g, w, b, use_dv);
             if (waves == 2)
@@ -1038,6 +1041,11 @@ static void spread_kernel(const BatchedCfg& cfg, hipStream_t st, const Grid& g,
             return;
         }
     }
+    const int waves = spread_waves(cfg, g, w.nl, true);
+    if (waves == 4)
+        return spread_with<k_spread_mfma_waves<T, P, MASK, 4>, 4>(cfg, st, g, w, b, use_dv);
+    if (waves == 2)
+        return spread_with<k_spread_mfma_waves<T, P, MASK, 2>, 2>(cfg, st, g, w, b, use_dv);
     spread_with<k_spread_mfma<T, P, MASK>>(cfg, st, g, w, b, use_dv);
 }
 

@@ -109,7 +109,7 @@ struct Octants {
     int cnt[8];            // sources of each octant
     uint64_t odds;         // staged sources whose F is not finite
 
-    __device__ explicit Octants(Lds& m) : rec(m.rec), list(m.list), lane(threadIdx.x)
+    __device__ explicit Octants(Lds& m, int ln = threadIdx.x) : rec(m.rec), list(m.list), lane(ln)
     {
         ixy = sizeof(T) == 4 ? lane & 3 : (lane >> 2) & 3;
         icz = sizeof(T) == 4 ? (lane >> 2) & 3 : lane & 3;
@@ -228,6 +228,37 @@ struct Octants {
                     if (kq < 3 && w != T(0))
                         acc[o][i] += q[WF + kq] * w;
                 }
+            }
+        }
+    }
+
+    // The same for octant o, with n listed sources.
+    __device__ void add_one(int o, int n, Acc& acc)
+    {
+        typedef uint32_t Pair32 __attribute__((may_alias));
+        const char* const base = reinterpret_cast<const char*>(rec);
+        const int x = WX + 4 * (o & 1), y = WY + 4 * ((o >> 1) & 1) + ixy;
+        const int z = WZ + 4 * (o >> 2) + icz;
+        for (int gr = 0; 4 * gr < n; gr += 2) {
+            const uint32_t e = *reinterpret_cast<const Pair32*>(list + 64 * o + 16 * kq + gr);
+            T a[2], b[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const T* const p = reinterpret_cast<const T*>(base + (h ? e >> 16 : e & 0xffffu));
+                a[h] = p[x + ixy] * p[WF + icz];
+                b[h] = p[y] * p[z];
+            }
+            acc = Mat<T>::mac(a[0], b[0], acc);
+            acc = Mat<T>::mac(a[1], b[1], acc);
+        }
+        for (uint64_t m = odds; m; m &= m - 1) {
+            const T* const q = rec + __builtin_ctzll(m) * S;
+            const T wyz = q[y] * q[z];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const T w = q[x + i] * wyz;
+                if (kq < 3 && w != T(0))
+                    acc[i] += q[WF + kq] * w;
             }
         }
     }

@@ -1527,3 +1527,142 @@ k_spread_mfma(const int4* __restrict__ sent, const int32_t* __restrict__ nactive
         tile_coords(g, e0.y, lo);
     }
 }
+
+// The same products by W wavefronts a tile, where there are few tiles (spread_waves
+// in batched.hip): each stages a batch, then forms 8 / W of the octants from all W
+// batches in order.  Every cell's sum has the order of k_spread_mfma: the same bits.
+template <typename T, int P, bool MASK, int W>
+__global__ void __launch_bounds__(64 * W)
+k_spread_mfma_waves(const int4* __restrict__ sent, const int32_t* __restrict__ nactive,
+                    const int32_t* __restrict__ src_idx, Grid g, MarkerData<T> s,
+                    T* __restrict__ G, uint64_t* __restrict__ rmask,
+                    uint64_t* __restrict__ tmask, int use_dv, int32_t* __restrict__ queue)
+{
+    using Oct = Octants<T, P, false>;
+    using Acc = typename Oct::Acc;
+    constexpr int NO = 8 / W;                               // octants of a wavefront
+    __shared__ __align__(16) typename Oct::Lds mem[W];
+    __shared__ uint64_t odds[W], rows[W];
+    __shared__ int32_t cnt[W][8];
+    __shared__ int4 entry;
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    Oct oct(mem[wv], lane);
+    const int ixy = oct.ixy, icz = oct.icz, kq = oct.kq;
+    SpreadQueue sq(sent, queue, *nactive);
+    auto next = [&] {                   // the entry of every wavefront, from the first one's queue
+        if (wv == 0) {
+            const int4 e = sq.next();
+            if (lane == 0)
+                entry = e;
+        }
+    };
+    next();
+    __syncthreads();
+    int4 ent = entry;
+    int pf = ent.z + (int)threadIdx.x < ent.w ? src_idx[ent.z + threadIdx.x] : 0;
+    __syncthreads();
+    while (ent.w > 0) {
+        next();
+        int lo[3];
+        tile_coords(g, ent.y, lo);
+        Acc acc[NO];
+#pragma unroll
+        for (int o = 0; o < NO; ++o)
+            acc[o] = Acc{T(0), T(0), T(0), T(0)};
+        int4 nent = ent;
+        for (int s0 = ent.z; s0 < ent.w; s0 += 64 * W) {
+            oct.clear();
+            typename Oct::Reach reach;
+            if (s0 + (int)threadIdx.x < ent.w) {
+                const typename Vec4<T>::type geo = s.geo[pf], fv = s.f4[pf];
+                int rbs[3];
+                unpack_rb(s.rb[pf], rbs);
+                const T r[3] = {geo.x, geo.y, geo.z};
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax) {
+                    int b = rbs[ax] - lo[ax];
+                    if (b < -(P - 1)) b += g.n[ax];
+                    else if (b > TILE - 1) b -= g.n[ax];
+                    T w[P];
+                    axis_weights_r<T, P>(r[ax], w);
+                    oct.put(reach, ax, b, w, false);
+                }
+                const T sc = use_dv ? geo.w : T(1);
+                oct.put_force(reach, fv.x * sc, fv.y * sc, fv.z * sc);
+            }
+            oct.make_lists(reach);
+            if (lane == 0) {
+                odds[wv] = oct.odds;
+#pragma unroll
+                for (int o = 0; o < 8; ++o)
+                    cnt[wv][o] = oct.cnt[o];
+            }
+            __syncthreads();
+            nent = entry;
+            const bool more = s0 + 64 * W < ent.w;
+            const int n0 = (more ? s0 + 64 * W : nent.z) + (int)threadIdx.x;
+            pf = n0 < (more ? ent.w : nent.w) ? src_idx[n0] : 0;
+            for (int j = 0; j < W && s0 + 64 * j < ent.w; ++j) {
+                Oct batch(mem[j], lane);
+                batch.odds = odds[j];
+#pragma unroll
+                for (int o = 0; o < NO; ++o)
+                    batch.add_one(NO * wv + o, cnt[j][NO * wv + o], acc[o]);
+            }
+            __syncthreads();
+        }
+        // as k_spread_mfma: lane, column (y, z) = (ixy, icz) of each octant, c = kq
+        bool nz[NO];
+        uint64_t some = 0;
+#pragma unroll
+        for (int o = 0; o < NO; ++o)
+            nz[o] = true;
+        if constexpr (MASK) {
+#pragma unroll
+            for (int o = 0; o < NO; ++o) {
+                const int h = (NO * wv + o) >> 1;           // (y, z) half
+                bool v = false;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    v = v || acc[o][i] != T(0);
+                const uint64_t b = __ballot(v && kq < 3);
+                const uint32_t cols = (uint32_t)(b | b >> 16 | b >> 32 | b >> 48) & 0xffffu;
+#pragma unroll
+                for (int y = 0; y < 4; ++y)
+#pragma unroll
+                    for (int z = 0; z < 4; ++z) {
+                        const int col = sizeof(T) == 4 ? y + 4 * z : z + 4 * y;
+                        some |= (uint64_t)((cols >> col) & 1)
+                                << (4 * (h & 1) + y + TILE * (4 * (h >> 1) + z));
+                    }
+            }
+            if (lane == 0)
+                rows[wv] = some;
+            __syncthreads();
+            uint64_t rm = 0;
+#pragma unroll
+            for (int j = 0; j < W; ++j)
+                rm |= rows[j];
+            if (threadIdx.x == 0) {
+                rmask[ent.x] = rm;
+                tmask[ent.y] = rm;
+            }
+#pragma unroll
+            for (int o = 0; o < NO; ++o) {
+                const int h = (NO * wv + o) >> 1;
+                nz[o] = (rm >> (4 * (h & 1) + ixy + TILE * (4 * (h >> 1) + icz))) & 1;
+            }
+        }
+        T* const gs = G + (int64_t)ent.x * 3 * TILE_CELLS + kq * TILE_CELLS + TILE * ixy +
+                      TILE * TILE * icz;
+#pragma unroll
+        for (int o = 0; o < NO; ++o) {
+            const int q = NO * wv + o, h = q >> 1;
+            if (nz[o] && kq < 3)
+                *reinterpret_cast<Acc*>(gs + 4 * TILE * (h & 1) + 4 * TILE * TILE * (h >> 1) +
+                                        4 * (q & 1)) = acc[o];
+        }
+        ent = nent;
+    }
+}
