@@ -101,7 +101,8 @@ __device__ inline void item_base(const Grid& g, int t, int k, const int32_t* __r
 //         Fout[l] = J field (if Fout) and gX[l] += sc sum over the stencil of
 //         (field . vin_l) grad_X w_l, sc = dV/h^3 (use_dv) or 1, in marker
 //         order (the weights' derivatives from the same shared root).
-// e2 (nullable) receives dV |U^d - J u^(m)|^2 per marker.
+// e2 (nullable) receives the sum of dV |U^d - J u^(m)|^2 over the markers of each
+// item, by a fixed tree.
 // (FP32 with the row masks, 256-marker items of one tile: registers capped at
 // the unmasked kernel's seven waves per SIMD.)
 template <typename T, int P, int MODE, int BW, bool MASK = false, int TXW = TILE>
@@ -135,6 +136,7 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
     __shared__ __align__(16) T fld[3 * PL];
     __shared__ int64_t nb[NNB];
     __shared__ uint64_t nbm[NNB];       // tile slots: rows of each neighbour's slot not all zero
+    __shared__ double esum[BW / 64];
     const int n_items = *nitems;
     const double h3 = g.h * g.h * g.h;
     const int tid = threadIdx.x;
@@ -420,9 +422,9 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
             gX[3 * l + 1] += sc * (double)gr1;
             gX[3 * l + 2] += sc * (double)gr2;
         }
+        double err = 0.0;
         if (MODE != 3 && mine && sub == 0) {
             const T acc[3] = {acc0, acc1, acc2};
-            double err = 0.0;
             const T idt = (T)(1.0 / dt);
             T nf[3];
 #pragma unroll
@@ -458,10 +460,23 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
                 Fout[3 * l + 1] = fv.y;
                 Fout[3 * l + 2] = fv.z;
             }
-            if (e2)
-                e2[i] = (double)rs * h3 * err;
+        }
+        if (MODE != 3 && e2) {
+            double v = (double)rs * h3 * err;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1)
+                v += __shfl_down(v, o);
+            if ((tid & 63) == 0)
+                esum[tid >> 6] = v;
         }
         __syncthreads();
+        if (MODE != 3 && e2 && tid == 0) {
+            double v = 0.0;
+#pragma unroll
+            for (int k = 0; k < BW / 64; ++k)
+                v += esum[k];
+            e2[it] = v;
+        }
     }
 }
 

@@ -871,3 +871,24 @@ def test_few_and_many_markers_spread_the_same_bits(dev, delta, masks, dtype):
     for _, f, F in got[1:]:
         assert np.array_equal(f, got[0][1])
         assert torch.equal(F, got[0][2])
+
+
+@pytest.mark.parametrize("dtype,ns,width", [("f64", 6, 64), ("f64", 7, 128), ("f32", 8, 0),
+                                            ("f64", 15, 0), ("f64", 16, 256)])
+def test_residuals_of_long_loops(dev, dtype, ns, width):
+    """Residuals are summed eight at a time, and the rest at the end."""
+    import oracle as O
+    import torch
+    announce(f"residuals ns={ns} width={width} {dtype}")
+    wl = small_workload(32, 16, 4, 3, 5)
+    c = Case(wl, dev)
+    ref = O.multidirect(c.g, wl.delta, ns, wl.dt, c.m, wl.xc, wl.up, wl.om, wl.u0)["resid"]
+    kw = {"bucket_width": width} if width else {}
+    runs = [_run(c, dtype, 2, ns=ns, **kw)[3].cpu().numpy() for _ in range(2)]
+    tol = TOL64 if dtype == "f64" else TOL32
+    bound = resid_bounds(c.g, wl.delta, c.m, wl.xc, wl.up, wl.om, wl.u0, ref, tol)
+    assert len(ref) == ns + 1 and np.all(np.abs(runs[0] - ref) <= bound)
+    assert np.array_equal(runs[0], runs[1])
+    none = _run(c, dtype, 2, ns=ns, resid=False, **kw)
+    with_r = _run(c, dtype, 2, ns=ns, **kw)
+    assert torch.equal(none[2], with_r[2])
