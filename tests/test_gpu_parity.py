@@ -892,3 +892,32 @@ def test_residuals_of_long_loops(dev, dtype, ns, width):
     none = _run(c, dtype, 2, ns=ns, resid=False, **kw)
     with_r = _run(c, dtype, 2, ns=ns, **kw)
     assert torch.equal(none[2], with_r[2])
+
+
+@pytest.mark.parametrize("n", [64, 16])
+@pytest.mark.parametrize("nl", [1, 63, 64, 1023, 1024, 1025, 2047, 2048, 2049])
+def test_small_buckets_are_stable(dev, nl, n):
+    """Up to 2048 markers are sorted by one workgroup: the same stable order by tile
+    as the passes' on either side of its sizes."""
+    import torch
+
+    import paper_2408_14140_amd as ibx
+    announce(f"bucket nl={nl} n={n}")
+    rng = np.random.default_rng(nl)
+    lev = W.make_workload("sort", n, n, 2, 4, 1, np.array([6.0]), nmodes=1, K=1, cover_all=True,
+                          with_field=False).level
+    x, y, z = rng.uniform(-0.3, 1.3, (3, nl))
+    dm = ibx.markers_from(x, y, z, np.zeros(nl, np.int32), np.ones(1), np.array([0, nl]), dev)
+    b = ibx.bucket(ibx.device_level(lev, dev), dm, 4)
+    tile = b.tileid.long()
+    order = torch.argsort(tile, stable=True)
+    assert torch.equal(b.perm.long(), order)
+    bounds = torch.searchsorted(tile[order], torch.arange(n ** 3 // 512 + 1, device=dev))
+    assert torch.equal(b.tile_offs.long(), bounds)
+    per_tile = (b.src_offs[1:] - b.src_offs[:-1]).sum()
+    idx = b.src_idx[:int(per_tile)]
+    assert int(idx.min()) >= 0 and int(idx.max()) < nl
+    for t in torch.unique(tile)[:8].tolist():
+        lst = b.src_idx[int(b.src_offs[t]):int(b.src_offs[t + 1])].long()
+        own = torch.nonzero(tile[order] == t).flatten()
+        assert torch.equal(lst, torch.sort(lst).values) and torch.isin(own, lst).all()
