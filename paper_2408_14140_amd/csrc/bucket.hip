@@ -211,8 +211,12 @@ void scan_exclusive2(const int32_t* in0, int32_t* out0, const int32_t* in1, int3
 // ------------------------------------------------------------------ radix sort
 
 constexpr int RS_THREADS = 256;
-constexpr int RS_ROUNDS = 8;
-constexpr int RS_TILE = RS_THREADS * RS_ROUNDS;
+// Elements of a workgroup and thread: fewer for fewer elements, so that a pass fills
+// the chip (124 K elements in tiles of 2048: 61 workgroups).
+__host__ __device__ inline int rs_rounds(int64_t n_max)
+{
+    return n_max <= (1 << 17) ? 1 : n_max <= (1 << 19) ? 2 : n_max <= (1 << 21) ? 4 : 8;
+}
 constexpr int RS_WAVES = RS_THREADS / 64;
 
 __device__ inline int64_t live_count(int64_t n_max, const int32_t* n_dev)
@@ -223,6 +227,7 @@ __device__ inline int64_t live_count(int64_t n_max, const int32_t* n_dev)
     return v < n_max ? v : n_max;
 }
 
+template <int ROUNDS>
 __global__ void __launch_bounds__(RS_THREADS)
 k_radix_hist(const int32_t* keys, int64_t n_max, const int32_t* n_dev, int shift,
              int32_t* hist, int nblocks)
@@ -232,8 +237,9 @@ k_radix_hist(const int32_t* keys, int64_t n_max, const int32_t* n_dev, int shift
     const int64_t n = live_count(n_max, n_dev);
     h[t] = 0;
     __syncthreads();
-    for (int r = 0; r < RS_ROUNDS; ++r) {
-        int64_t j = (int64_t)blockIdx.x * RS_TILE + r * RS_THREADS + t;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        int64_t j = ((int64_t)blockIdx.x * ROUNDS + r) * RS_THREADS + t;
         if (j < n)
             atomicAdd(&h[(keys[j] >> shift) & 255], 1);
     }
@@ -285,6 +291,7 @@ k_radix_rowscan(int32_t* hist, int nblocks, int32_t* rowtot)
 // Stable scatter: elements keep their input order within each digit.  Ranks
 // inside a wave come from ballot matching on the 8 digit bits; ranks across
 // the block's waves and rounds from per-digit counters in LDS.
+template <int ROUNDS>
 __global__ void __launch_bounds__(RS_THREADS)
 k_radix_scatter(const int32_t* kin, const int32_t* vin, int32_t* kout, int32_t* vout,
                 int64_t n_max, const int32_t* n_dev, int shift, const int32_t* hist_scan,
@@ -295,7 +302,7 @@ k_radix_scatter(const int32_t* kin, const int32_t* vin, int32_t* kout, int32_t* 
     const int t = threadIdx.x;
     const int wave = t >> 6, lane = t & 63;
     const int64_t n = live_count(n_max, n_dev);
-    if ((int64_t)blockIdx.x * RS_TILE >= n)
+    if ((int64_t)blockIdx.x * ROUNDS * RS_THREADS >= n)
         return;                             // whole block past the live count
     // digit offsets: exclusive scan of the digit totals, in every block
     const int32_t tot = rowtot[t];
@@ -315,8 +322,8 @@ k_radix_scatter(const int32_t* kin, const int32_t* vin, int32_t* kout, int32_t* 
         wc[w][t] = 0;
     __syncthreads();
     const uint64_t lt = (lane == 0) ? 0ull : ((~0ull) >> (64 - lane));
-    for (int r = 0; r < RS_ROUNDS; ++r) {
-        const int64_t j = (int64_t)blockIdx.x * RS_TILE + r * RS_THREADS + t;
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int64_t j = ((int64_t)blockIdx.x * ROUNDS + r) * RS_THREADS + t;
         const bool valid = j < n;
         const int32_t k = valid ? kin[j] : 0;
         const int32_t v = valid ? vin[j] : 0;
@@ -437,12 +444,32 @@ k_sort_small(int32_t* __restrict__ keys, int32_t* __restrict__ vals, int n, int 
     }
 }
 
-static int64_t rs_blocks(int64_t n_max) { return (n_max + RS_TILE - 1) / RS_TILE; }
+static int64_t rs_blocks(int64_t n_max)
+{
+    const int64_t tile = (int64_t)RS_THREADS * rs_rounds(n_max);
+    return (n_max + tile - 1) / tile;
+}
 
+// Enough for every sort of up to n_max elements (fewer can take more workgroups).
 size_t radix_workspace(int64_t n_max)
 {
     int64_t nb = rs_blocks(n_max > 0 ? n_max : 1);
+    for (int64_t n = 1 << 17; n < n_max && n <= 1 << 21; n <<= 2)
+        nb = nb > rs_blocks(n) ? nb : rs_blocks(n);
     return align_up(sizeof(int32_t) * 256 * nb) + align_up(sizeof(int32_t) * 256);
+}
+
+// One pass: the stable order by the digit at `shift`.
+template <int ROUNDS>
+static void radix_pass(const int32_t* ka, const int32_t* va, int32_t* kb, int32_t* vb,
+                       int64_t n_max, const int32_t* n_dev, int shift, int32_t* hist,
+                       int32_t* rowtot, int64_t nb, hipStream_t st)
+{
+    k_radix_hist<ROUNDS><<<(unsigned)nb, RS_THREADS, 0, st>>>(ka, n_max, n_dev, shift, hist,
+                                                              (int)nb);
+    k_radix_rowscan<<<256, RS_THREADS, 0, st>>>(hist, (int)nb, rowtot);
+    k_radix_scatter<ROUNDS><<<(unsigned)nb, RS_THREADS, 0, st>>>(ka, va, kb, vb, n_max, n_dev,
+                                                                 shift, hist, rowtot, (int)nb);
 }
 
 void radix_sort_pairs(int32_t* keys, int32_t* vals, int32_t* tk, int32_t* tv, int64_t n_max,
@@ -465,11 +492,12 @@ void radix_sort_pairs(int32_t* keys, int32_t* vals, int32_t* tk, int32_t* tv, in
     int32_t *ka = keys, *va = vals, *kb = tk, *vb = tv;
     const int passes = (bits + 7) / 8;
     for (int p = 0; p < passes; ++p) {
-        const int shift = 8 * p;
-        k_radix_hist<<<(unsigned)nb, RS_THREADS, 0, st>>>(ka, n_max, n_dev, shift, hist, (int)nb);
-        k_radix_rowscan<<<256, RS_THREADS, 0, st>>>(hist, (int)nb, rowtot);
-        k_radix_scatter<<<(unsigned)nb, RS_THREADS, 0, st>>>(ka, va, kb, vb, n_max, n_dev, shift,
-                                                             hist, rowtot, (int)nb);
+        switch (rs_rounds(n_max)) {
+        case 1: radix_pass<1>(ka, va, kb, vb, n_max, n_dev, 8 * p, hist, rowtot, nb, st); break;
+        case 2: radix_pass<2>(ka, va, kb, vb, n_max, n_dev, 8 * p, hist, rowtot, nb, st); break;
+        case 4: radix_pass<4>(ka, va, kb, vb, n_max, n_dev, 8 * p, hist, rowtot, nb, st); break;
+        default: radix_pass<8>(ka, va, kb, vb, n_max, n_dev, 8 * p, hist, rowtot, nb, st);
+        }
         int32_t* t0 = ka; ka = kb; kb = t0;
         t0 = va; va = vb; vb = t0;
     }

@@ -921,3 +921,24 @@ def test_small_buckets_are_stable(dev, nl, n):
         lst = b.src_idx[int(b.src_offs[t]):int(b.src_offs[t + 1])].long()
         own = torch.nonzero(tile[order] == t).flatten()
         assert torch.equal(lst, torch.sort(lst).values) and torch.isin(own, lst).all()
+
+
+@pytest.mark.parametrize("nl", [131072, 131073, 524288, 524289, 2097153])
+def test_buckets_are_stable_at_every_pass_size(dev, nl):
+    """The sort's passes take 1, 2, 4 or 8 elements a thread by the number of
+    markers: the stable order by tile on both sides of each change."""
+    import torch
+
+    import paper_2408_14140_amd as ibx
+    announce(f"bucket nl={nl}")
+    rng = np.random.default_rng(nl)
+    lev = W.make_workload("sort", 128, 32, 2, 3, 1, np.array([6.0]), nmodes=1, K=1,
+                          cover_all=True, with_field=False).level
+    x, y, z = rng.uniform(0.0, 1.0, (3, nl))
+    dm = ibx.markers_from(x, y, z, np.zeros(nl, np.int32), np.ones(1), np.array([0, nl]), dev)
+    b = ibx.bucket(ibx.device_level(lev, dev), dm, 3)
+    tile = b.tileid.long()
+    order = torch.argsort(tile, stable=True)
+    assert torch.equal(b.perm.long(), order)
+    assert torch.equal(b.tile_offs.long(),
+                       torch.searchsorted(tile[order], torch.arange(4097, device=dev)))
