@@ -14,12 +14,14 @@
 // S and J are adjoint (Sec. 2): J^T is spreading without dV and S^T is
 // interpolation weighted by dV/h^3.  grad w uses the kernel derivative.
 // Fields are recomputed, never stored.  The two spreads of every step (the
-// recomputed u^(m-1) and J^T Ubar) run on the forward loop's tile kernel,
+// recomputed u^(m-1) and J^T Ubar) run on the forward loop's tile kernels,
 // with its marker records and work lists formed once per call (grids of at
 // least 16 cells per axis; the plain per-cell kernel otherwise), and so do
 // J a_f and the position gradients (the tile interpolation in its adjoint
-// mode, J a_f and its gradient in one pass over a_f; four lanes per marker
-// gathering from global memory otherwise).
+// modes, J a_f and its gradient in one pass over a_f; four lanes per marker
+// gathering from global memory otherwise).  On the tile kernels u^(m-1) and,
+// after the first step, a_f = dt a_u exist as tile slots only, and the
+// interpolation forms them from the slots as it stages a tile.
 #include "paths.h"
 
 namespace ibx {
@@ -257,14 +259,14 @@ size_t backward_workspace(const Grid& g, ib_prec prec, int64_t nl)
 {
     const size_t s = prec == IB_F64 ? 8 : 4;
     Carver cv(nullptr, 0);
-    const bool tiled = tile_spread_supported(g);
-    for (int k = 0; k < (tiled ? 2 : 3); ++k)
+    const bool tiled = tile_adjoint_supported(g);
+    for (int k = 0; k < (tiled ? 1 : 3); ++k)
         cv.take<char>(s * field_elems(g));
     for (int k = 0; k < 3; ++k)
         cv.take<char>(s * 3 * nl);
     cv.take<double>(3 * nl);
     if (tiled)
-        cv.take<char>(tile_spread_workspace(g, prec, nl));
+        cv.take<char>(tile_adjoint_workspace(g, prec, nl));
     return cv.used;
 }
 
@@ -278,20 +280,20 @@ static int run_backward(const Grid& g, int P, const BatchedCfg& cfg, const ib_pa
     const int64_t nl = m->nl;
     const ib_prec prec = sizeof(T) == 8 ? IB_F64 : IB_F32;
     Carver cv(ws, ws_bytes);
-    const bool tiled = tile_spread_supported(g);
+    const bool tiled = tile_adjoint_supported(g);
     T* au = tiled ? nullptr : cv.take<T>(field_elems(g));
     T* af = cv.take<T>(field_elems(g));
-    T* tmp = cv.take<T>(field_elems(g));
+    T* tmp = tiled ? nullptr : cv.take<T>(field_elems(g));
     T* aF = cv.take<T>(3 * nl);
     T* Ub = cv.take<T>(3 * nl);
     T* Ui = cv.take<T>(3 * nl);
     double* aUd = cv.take<double>(3 * nl);
-    const size_t tsb = tiled ? tile_spread_workspace(g, prec, nl) : 0;
+    const size_t tsb = tiled ? tile_adjoint_workspace(g, prec, nl) : 0;
     void* tws = tiled ? cv.take<char>(tsb) : nullptr;
     if (!ws || !cv.ok())
         return IB_EWORKSPACE;
     if (tiled) {
-        const int rc = tile_spread_setup(g, P, prec, cfg, p, m, b, tws, tsb, st);
+        const int rc = tile_adjoint_setup(g, P, prec, cfg, p, m, b, tws, tsb, st);
         if (rc)
             return rc;
     }
@@ -303,53 +305,34 @@ static int run_backward(const Grid& g, int P, const BatchedCfg& cfg, const ib_pa
         k_adjoint_init<T><<<gm, 256, 0, st>>>(3 * nl, gF, aF, aUd, gX);
     for (int mi = ns; mi >= 1; --mi) {
         const T* Fm = Fhist + (int64_t)(mi - 1) * 3 * nl;
+        const T* Fp = mi > 1 ? Fhist + (int64_t)(mi - 2) * 3 * nl : nullptr;
+        if (tiled) {
+            const int rc = tile_adjoint_step(g, P, prec, cfg, m, b, dt, mi == ns ? af : nullptr,
+                                             Fm, Fp, u0, Ui, aF, aUd, Ub, gu0, gX, tws, tsb, st);
+            if (rc)
+                return rc;
+            continue;
+        }
         if (nl > 0) {
             // U = J a_f and the position gradient of S^T with F^m, one gather
-            if (tiled) {
-                const int rc = tile_interp_grad(g, P, prec, cfg, m, b, af, Fm, Ui, 1, gX, tws,
-                                                tsb, st);
-                if (rc)
-                    return rc;
-            } else {
-                launch_interp_grad<T>(g, P, m, af, Ui, Fm, 1, gX, st);
-                k_marker_step<T><<<gm, 256, 0, st>>>(g, nl, dt, m->pid, m->dv, Ui, aF, aUd, Ub);
-            }
+            launch_interp_grad<T>(g, P, m, af, Ui, Fm, 1, gX, st);
+            k_marker_step<T><<<gm, 256, 0, st>>>(g, nl, dt, m->pid, m->dv, Ui, aF, aUd, Ub);
         }
-        // Ubar, and with a_u = J^T Ubar the next step's g_u0 += a_u, a_f = dt a_u
-        // (a_f is not needed after the first step of the loop)
-        if (tiled) {
-            const int rc = tile_adjoint_step(g, P, prec, cfg, m, b, dt, Ui, aF, aUd, Ub, gu0,
-                                             mi > 1 ? af : nullptr, tws, tsb, st);
-            if (rc)
-                return rc;
-        } else {
-            plain_spread(g, P, prec, m, b, Ub, au, 1.0, 0, st);
-            if (mi > 1)
-                k_field_op<T, 5><<<gc, 256, 0, st>>>(g, gu0, au, af, nullptr, nullptr, dt);
-            else
-                k_field_op<T, 2><<<gc, 256, 0, st>>>(g, gu0, au, nullptr, nullptr, nullptr, dt);
-        }
+        // a_u = J^T Ubar: the next step's g_u0 += a_u, a_f = dt a_u (a_f is not
+        // needed after the first step of the loop)
+        plain_spread(g, P, prec, m, b, Ub, au, 1.0, 0, st);
+        if (mi > 1)
+            k_field_op<T, 5><<<gc, 256, 0, st>>>(g, gu0, au, af, nullptr, nullptr, dt);
+        else
+            k_field_op<T, 2><<<gc, 256, 0, st>>>(g, gu0, au, nullptr, nullptr, nullptr, dt);
         const T* uprev = u0;
-        if (mi > 1) {
-            const T* Fp = Fhist + (int64_t)(mi - 2) * 3 * nl;
-            if (tiled) {
-                const int rc = tile_spread(g, P, prec, cfg, m, b, Fp, 1, u0, dt, tmp, tws, tsb, st);
-                if (rc)
-                    return rc;
-            } else {
-                plain_spread(g, P, prec, m, b, Fp, tmp, 1.0, 1, st);
-                k_field_op<T, 3><<<gc, 256, 0, st>>>(g, tmp, tmp, nullptr, nullptr, u0, dt);
-            }
+        if (Fp) {
+            plain_spread(g, P, prec, m, b, Fp, tmp, 1.0, 1, st);
+            k_field_op<T, 3><<<gc, 256, 0, st>>>(g, tmp, tmp, nullptr, nullptr, u0, dt);
             uprev = tmp;
         }
-        if (nl > 0 && tiled) {
-            const int rc = tile_interp_grad(g, P, prec, cfg, m, b, uprev, Ub, nullptr, 0, gX, tws,
-                                            tsb, st);
-            if (rc)
-                return rc;
-        } else if (nl > 0) {
+        if (nl > 0)
             launch_interp_grad<T>(g, P, m, uprev, nullptr, Ub, 0, gX, st);
-        }
     }
     if (p->np > 0)
         k_particle_grads<<<(unsigned)p->np, 256, 0, st>>>(p->np, m->offs, m->x, m->y, m->z,

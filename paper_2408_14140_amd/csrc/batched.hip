@@ -573,11 +573,11 @@ __device__ void finalize_poison(const Grid& g, T* ustar, T* f, T* Fp, int64_t nF
 }
 
 // Last step of Algorithm 1 on every valid cell of the covered boxes:
-// f = fs G^ns (fs = 1 but for the adjoint) and ustar = u0 + dt G^ns, with G = 0
-// on tiles no marker reaches (and everywhere when use_g is 0) and on the slot
-// rows whose bit in the tile's row mask (tilemask, indexed by tile) is clear.
-// One workgroup per (box, row of tiles in y, z plane): box-wide x rows, so the
-// box layout is written in long runs.
+// f = G^ns and ustar = u0 + dt G^ns, with G = 0 on tiles no marker reaches
+// (and everywhere when use_g is 0) and on the slot rows whose bit in the
+// tile's row mask (tilemask, indexed by tile) is clear.  One workgroup per
+// (box, row of tiles in y, z plane): box-wide x rows, so the box layout is
+// written in long runs.
 // In place (ustar == u0) only the cells whose force is not exactly zero are
 // read and rewritten (u0 + dt 0 = u0): inside the tiles that have a force
 // slot, most cells lie outside every stencil.  With f_acc, f += G^ns instead,
@@ -589,8 +589,8 @@ template <typename T, bool F_ACC, bool MASK>
 __global__ void __launch_bounds__(256)
 k_finalize(Grid g, const int32_t* __restrict__ slot, const T* __restrict__ G,
            const uint64_t* __restrict__ tilemask, const T* u0, T* ustar, T* __restrict__ f,
-           double dt, T fs, int use_g, int copy, const int32_t* __restrict__ flag,
-           T* __restrict__ Fp, int64_t nF)
+           double dt, int use_g, int copy, const int32_t* __restrict__ flag, T* __restrict__ Fp,
+           int64_t nF)
 {
     if (flag && (flag[0] | flag[1]) != 0) {
         finalize_poison(g, ustar, f, Fp, nF);
@@ -644,7 +644,7 @@ k_finalize(Grid g, const int32_t* __restrict__ slot, const T* __restrict__ G,
                 const int64_t o = off + c * g.cstride;
                 // streaming stores: nothing here is read again by this kernel
                 if (f && !F_ACC)
-                    __builtin_nontemporal_store(fs * v[c], &f[o]);
+                    __builtin_nontemporal_store(v[c], &f[o]);
                 else if (f && v[c] != T(0))
                     f[o] += v[c];
                 if (ustar && v[c] != T(0))
@@ -693,7 +693,7 @@ template <typename T, bool F_ACC, bool MASK, bool STREAM>
 __global__ void __launch_bounds__(256)
 k_finalize_pairs(Grid g, const int32_t* __restrict__ slot, const T* __restrict__ G,
                  const uint64_t* __restrict__ tilemask, const T* u0, T* ustar, T* __restrict__ f,
-                 double dt, T fs, int use_g, int copy, const int32_t* __restrict__ flag,
+                 double dt, int use_g, int copy, const int32_t* __restrict__ flag,
                  T* __restrict__ Fp, int64_t nF)
 {
     using V2 = typename Pair<T>::type;
@@ -761,7 +761,7 @@ k_finalize_pairs(Grid g, const int32_t* __restrict__ slot, const T* __restrict__
             for (int c = 0; c < 3; ++c) {
                 const int64_t o = off + c * g.cstride;
                 if (f && !F_ACC)
-                    put<STREAM, V2>(fs * v[c], reinterpret_cast<V2*>(f + o));
+                    put<STREAM, V2>(v[c], reinterpret_cast<V2*>(f + o));
                 else if (f && force[c])
                     *reinterpret_cast<V2*>(f + o) = w[c] + v[c];
                 if (ustar && force[c])
@@ -777,29 +777,27 @@ k_finalize_pairs(Grid g, const int32_t* __restrict__ slot, const T* __restrict__
 template <typename T, bool F_ACC, bool MASK>
 static void finalize_kernel(bool pairs, unsigned grid, unsigned gp, hipStream_t st, const Grid& g,
                             const int32_t* slot, const T* G, const uint64_t* tilemask,
-                            const T* u0, T* ustar, T* f, double dt, T fs, int use_g, int copy,
-                            bool stream, const int32_t* flag, T* Fp, int64_t nF)
+                            const T* u0, T* ustar, T* f, double dt, int use_g, int copy,
+                            const int32_t* flag, T* Fp, int64_t nF)
 {
-    if (pairs && stream)
+    if (pairs && (sizeof(T) == 8 || !copy))
         k_finalize_pairs<T, F_ACC, MASK, true><<<gp, 256, 0, st>>>(
-            g, slot, G, tilemask, u0, ustar, f, dt, fs, use_g, copy, flag, Fp, nF);
+            g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF);
     else if (pairs)
         k_finalize_pairs<T, F_ACC, MASK, false><<<gp, 256, 0, st>>>(
-            g, slot, G, tilemask, u0, ustar, f, dt, fs, use_g, copy, flag, Fp, nF);
+            g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF);
     else
         k_finalize<T, F_ACC, MASK><<<grid, 256, 0, st>>>(g, slot, G, tilemask, u0, ustar, f, dt,
-                                                         fs, use_g, copy, flag, Fp, nF);
+                                                         use_g, copy, flag, Fp, nF);
 }
 
 // With flag, the kernel also stands in for the flag check of the outputs
-// (ustar, f and Fp[0 .. nF)).  adjoint: f = fs G instead of G, and its stores
-// are not streamed in FP32, as the next kernel reads it.
+// (ustar, f and Fp[0 .. nF)).
 template <typename T>
 static void launch_finalize(unsigned grid, hipStream_t st, const Grid& g, const int32_t* slot,
                             const T* G, const uint64_t* tilemask, const T* u0, T* ustar, T* f,
                             double dt, int use_g, int f_acc, int masks,
-                            const int32_t* flag = nullptr, T* Fp = nullptr, int64_t nF = 0,
-                            bool adjoint = false, double fs = 1.0)
+                            const int32_t* flag = nullptr, T* Fp = nullptr, int64_t nF = 0)
 {
     const int copy = ustar && ustar != u0;
     // pairs of cells: rows start on even elements when ngrow is even, and the
@@ -809,10 +807,9 @@ static void launch_finalize(unsigned grid, hipStream_t st, const Grid& g, const 
                        !((uintptr_t)ustar & am) && !((uintptr_t)f & am);
     const int64_t items = (int64_t)g.nbox * (g.box / TILE) * (g.box / 2);
     const unsigned gp = (unsigned)(items < 65535 ? (items > 0 ? items : 1) : 65535);
-    const bool stream = sizeof(T) == 8 || (!copy && !adjoint);
 #define IBX_FINALIZE(ACC, MASK)                                                                \
     finalize_kernel<T, ACC, MASK>(pairs, grid, gp, st, g, slot, G, tilemask, u0, ustar, f, dt,  \
-                                  adjoint ? (T)fs : T(1), use_g, copy, stream, flag, Fp, nF)
+                                  use_g, copy, flag, Fp, nF)
     if (f_acc && masks)
         IBX_FINALIZE(true, true);
     else if (f_acc)
@@ -916,11 +913,13 @@ static void interp_kernel(const BatchedCfg& cfg, hipStream_t st, const Grid& g, 
                           double dt, const Item* items, const int32_t* nitems, const T* u0,
                           const T* G, const uint64_t* rmask, const int64_t* nbase,
                           const MarkerData<T>& s, double* e2, T* Fout, const int32_t* perm,
-                          const T* vin, double* gX, int use_dv, int32_t* queue)
+                          const T* vin, double* gX, int use_dv, int32_t* queue,
+                              const int64_t* nbase_u)
 {
     constexpr auto K = k_interp_tiles<T, P, MODE, BW, MASK, TXW>;
     K<<<resident_grid<K, BW>(cfg.ncu, 0), BW, 0, st>>>(g, nl, dt, items, nitems, u0, G, nbase, s,
-                                                       e2, Fout, perm, vin, gX, use_dv, rmask, queue);
+                                                       e2, Fout, perm, vin, gX, use_dv, rmask, queue,
+                                                       nbase_u);
 }
 
 template <typename T, int P, int MODE, bool MASK, int TXW>
@@ -928,19 +927,20 @@ static void launch_interp_txw(const BatchedCfg& cfg, hipStream_t st, const Grid&
                               double dt, const Item* items, const int32_t* nitems, const T* u0,
                               const T* G, const uint64_t* rmask, const int64_t* nbase,
                               const MarkerData<T>& s, double* e2, T* Fout, const int32_t* perm,
-                              const T* vin, double* gX, int use_dv, int32_t* queue)
+                              const T* vin, double* gX, int use_dv, int32_t* queue,
+                              const int64_t* nbase_u)
 {
     if (cfg.bw == 64)
         interp_kernel<T, P, MODE, MASK, TXW, 64>(cfg, st, g, nl, dt, items, nitems, u0, G, rmask,
-                                                 nbase, s, e2, Fout, perm, vin, gX, use_dv, queue);
+                                                 nbase, s, e2, Fout, perm, vin, gX, use_dv, queue, nbase_u);
     else if (cfg.bw == 128)
         interp_kernel<T, P, MODE, MASK, TXW, 128>(cfg, st, g, nl, dt, items, nitems, u0, G,
                                                   rmask, nbase, s, e2, Fout, perm, vin, gX,
-                                                  use_dv, queue);
+                                                  use_dv, queue, nbase_u);
     else
         interp_kernel<T, P, MODE, MASK, TXW, 256>(cfg, st, g, nl, dt, items, nitems, u0, G,
                                                   rmask, nbase, s, e2, Fout, perm, vin, gX,
-                                                  use_dv, queue);
+                                                  use_dv, queue, nbase_u);
 }
 
 // Work tiles of two x neighbours are compiled for FP32 only (their halo in
@@ -956,18 +956,19 @@ static void launch_interp_bw(const BatchedCfg& cfg, hipStream_t st, const Grid& 
                              double dt, const Item* items, const int32_t* nitems, const T* u0,
                              const T* G, const uint64_t* rmask, const int64_t* nbase,
                              const MarkerData<T>& s, double* e2, T* Fout, const int32_t* perm,
-                             const T* vin, double* gX, int use_dv, int32_t* queue)
+                             const T* vin, double* gX, int use_dv, int32_t* queue,
+                              const int64_t* nbase_u)
 {
     if constexpr (sizeof(T) == 4) {
         if (pair_items<T>(cfg)) {
             launch_interp_txw<T, P, MODE, MASK, 2 * TILE>(cfg, st, g, nl, dt, items, nitems, u0,
                                                           G, rmask, nbase, s, e2, Fout, perm,
-                                                          vin, gX, use_dv, queue);
+                                                          vin, gX, use_dv, queue, nbase_u);
             return;
         }
     }
     launch_interp_txw<T, P, MODE, MASK, TILE>(cfg, st, g, nl, dt, items, nitems, u0, G, rmask,
-                                              nbase, s, e2, Fout, perm, vin, gX, use_dv, queue);
+                                              nbase, s, e2, Fout, perm, vin, gX, use_dv, queue, nbase_u);
 }
 
 // Interpolation from the G slots (modes 1, 2) uses the slot row masks when the
@@ -978,17 +979,18 @@ static void launch_interp(const BatchedCfg& cfg, hipStream_t st, const Grid& g, 
                           const T* G, const uint64_t* rmask, const int64_t* nbase,
                           const MarkerData<T>& s, double* e2, int32_t* queue, T* Fout = nullptr,
                           const int32_t* perm = nullptr, const T* vin = nullptr,
-                          double* gX = nullptr, int use_dv = 0)
+                          double* gX = nullptr, int use_dv = 0,
+                          const int64_t* nbase_u = nullptr)
 {
-    if constexpr (MODE == 1 || MODE == 2) {
+    if constexpr (MODE == 1 || MODE == 2 || MODE >= 4) {
         if (cfg.masks) {
             launch_interp_bw<T, P, MODE, true>(cfg, st, g, nl, dt, items, nitems, u0, G, rmask,
-                                               nbase, s, e2, Fout, perm, vin, gX, use_dv, queue);
+                                               nbase, s, e2, Fout, perm, vin, gX, use_dv, queue, nbase_u);
             return;
         }
     }
     launch_interp_bw<T, P, MODE, false>(cfg, st, g, nl, dt, items, nitems, u0, G, rmask, nbase,
-                                        s, e2, Fout, perm, vin, gX, use_dv, queue);
+                                        s, e2, Fout, perm, vin, gX, use_dv, queue, nbase_u);
 }
 
 // Wavefronts that share a tile in the spreading.  One, unless the call's tiles
@@ -1286,33 +1288,13 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
     return launch_status();
 }
 
-// ------------------------------------------------------------------ spreading outside the loop
+// ------------------------------------------------------------------ the adjoint
 
-// The spreads of the adjoint (the recomputed u^(m-1) = u0 + dt S F^(m-1) and
-// the transpose of interpolation, J^T Ubar) run on the loop's tile kernel:
-// tile_spread_setup forms the marker records and work lists once per call,
-// then each tile_spread puts its marker vector into bucket order, spreads it
-// into the G slots and writes the field.
+// The adjoint's spreads (the recomputed u^(m-1) = u0 + dt S F^(m-1) and the
+// transpose of interpolation, J^T Ubar) and interpolations run on the loop's tile
+// kernels: tile_adjoint_setup forms the marker records and work lists once per call.
 
-template <typename T>
-__global__ void k_sort_vec(int64_t nl, const int32_t* __restrict__ perm, const T* __restrict__ v,
-                           typename Vec4<T>::type* __restrict__ f4, int32_t* __restrict__ queue)
-{
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < NXCD * NQ)
-        queue[i * QSTRIDE] = 0;       // the spreading that follows takes its tiles from these counters
-    if (i >= nl)
-        return;
-    const int64_t l = perm[i];
-    typename Vec4<T>::type q;
-    q.x = v[3 * l];
-    q.y = v[3 * l + 1];
-    q.z = v[3 * l + 2];
-    q.w = T(0);
-    f4[i] = q;
-}
-
-bool tile_spread_supported(const Grid& g)
+bool tile_adjoint_supported(const Grid& g)
 {
     for (int a = 0; a < 3; ++a)
         if (g.n[a] < 2 * TILE || g.n[a] > (int)RB_MASK - RB_BIAS)
@@ -1320,7 +1302,7 @@ bool tile_spread_supported(const Grid& g)
     return g.box <= 64 * TILE;
 }
 
-size_t tile_spread_workspace(const Grid& g, ib_prec prec, int64_t nl)
+size_t tile_adjoint_workspace(const Grid& g, ib_prec prec, int64_t nl)
 {
     BatchedCfg c{};
     c.bw = 64;
@@ -1337,11 +1319,11 @@ static void setup_t(const Grid& g, const BatchedCfg& cfg, const ib_particles* p,
     records_and_lists<T, P>(g, cfg, p, m, b, w, st);
 }
 
-int tile_spread_setup(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,
+int tile_adjoint_setup(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,
                       const ib_particles* p, const ib_markers* m, const ib_buckets* b, void* ws,
                       size_t ws_bytes, hipStream_t st)
 {
-    if (ws_bytes < tile_spread_workspace(g, prec, m->nl) || m->nl == 0)
+    if (ws_bytes < tile_adjoint_workspace(g, prec, m->nl) || m->nl == 0)
         return m->nl == 0 ? IB_OK : IB_EWORKSPACE;
     BatchedCfg c = cfg;
     c.prof = nullptr;
@@ -1354,67 +1336,21 @@ int tile_spread_setup(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,
     return launch_status();
 }
 
-template <typename T, int P>
-static void spread_t(const Grid& g, const BatchedCfg& cfg, const ib_markers* m,
-                     const ib_buckets* b, const T* v, int use_dv, const T* u0, double dt, T* out,
-                     void* ws, size_t bytes, hipStream_t st)
-{
-    size_t need = 0;
-    const int64_t nl = m->nl;
-    BatchedWs<T> w = carve_batched<T>(g, nl, cfg.bw, ws, bytes, &need);
-    const int64_t nfin = (int64_t)g.nbox * (g.box / TILE) * g.box;
-    const unsigned gfin = (unsigned)(nfin < 65535 ? (nfin > 0 ? nfin : 1) : 65535);
-    if (nl > 0) {
-        k_sort_vec<T><<<(unsigned)((nl + 255) / 256), 256, 0, st>>>(nl, b->perm, v, w.s.f4,
-                                                                    w.queue);
-        launch_spread<T, P>(cfg, st, g, w, b, use_dv);
-    }
-    // u0 given: out = u0 + dt G; else out = G (zero where no marker reaches)
-    if (u0)
-        launch_finalize<T>(gfin, st, g, w.slot, w.G, w.tmask, u0, out, nullptr, dt, nl > 0, 0,
-                          cfg.masks);
-    else
-        launch_finalize<T>(gfin, st, g, w.slot, w.G, w.tmask, nullptr, nullptr, out, dt, nl > 0, 0,
-                          cfg.masks);
-}
-
-int tile_spread(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg, const ib_markers* m,
-                const ib_buckets* b, const void* v, int use_dv, const void* u0, double dt,
-                void* out, void* ws, size_t ws_bytes, hipStream_t st)
-{
-    if (ws_bytes < tile_spread_workspace(g, prec, m->nl))
-        return IB_EWORKSPACE;
-    if (prec == IB_F64) {
-        if (P == 3)
-            spread_t<double, 3>(g, cfg, m, b, (const double*)v, use_dv, (const double*)u0, dt,
-                                (double*)out, ws, ws_bytes, st);
-        else
-            spread_t<double, 4>(g, cfg, m, b, (const double*)v, use_dv, (const double*)u0, dt,
-                                (double*)out, ws, ws_bytes, st);
-    } else {
-        if (P == 3)
-            spread_t<float, 3>(g, cfg, m, b, (const float*)v, use_dv, (const float*)u0, dt,
-                               (float*)out, ws, ws_bytes, st);
-        else
-            spread_t<float, 4>(g, cfg, m, b, (const float*)v, use_dv, (const float*)u0, dt,
-                               (float*)out, ws, ws_bytes, st);
-    }
-    return launch_status();
-}
-
 // One step of the adjoint on the markers, in bucket order: a_F += (dV/h^3) Ui,
-// a_Ud += a_F/dt, Ubar = -a_F/dt, which also goes to f4 for the spreading.
+// a_Ud += a_F/dt, Ubar = -a_F/dt.  Ubar and F^(m-1) (Fp, if any) also go into the
+// records of the two spreadings that follow.
 template <typename T>
 __global__ void __launch_bounds__(256)
 k_adjoint_markers(int64_t nl, double dt, double inv_h3, const int32_t* __restrict__ perm,
                   const int32_t* __restrict__ pid, const double* __restrict__ dv,
                   const T* __restrict__ Ui, T* __restrict__ aF, double* __restrict__ aUd,
-                  T* __restrict__ Ub, typename Vec4<T>::type* __restrict__ f4,
+                  T* __restrict__ Ub, typename Vec4<T>::type* __restrict__ ub4,
+                  const T* __restrict__ Fp, typename Vec4<T>::type* __restrict__ f4,
                   int32_t* __restrict__ queue)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i < NXCD * NQ)
-        queue[i * QSTRIDE] = 0;
+        queue[i * QSTRIDE] = 0;         // the spreading that follows takes its tiles from these
     if (i >= nl)
         return;
     const int64_t l = perm[i];
@@ -1434,38 +1370,67 @@ k_adjoint_markers(int64_t nl, double dt, double inv_h3, const int32_t* __restric
     q.y = ub[1];
     q.z = ub[2];
     q.w = T(0);
-    f4[i] = q;
+    ub4[i] = q;
+    if (Fp) {
+        q.x = Fp[3 * l];
+        q.y = Fp[3 * l + 1];
+        q.z = Fp[3 * l + 2];
+        f4[i] = q;
+    }
 }
 
 template <typename T, int P>
 static void adjoint_step_t(const Grid& g, const BatchedCfg& cfg, const ib_markers* m,
-                           const ib_buckets* b, double dt, const T* Ui, T* aF, double* aUd, T* Ub,
-                           T* gu0, T* af, void* ws, size_t bytes, hipStream_t st)
+                           const ib_buckets* b, double dt, const T* af, const T* Fm, const T* Fp,
+                           const T* u0, T* Ui, T* aF, double* aUd, T* Ub, T* gu0, double* gX,
+                           void* ws, size_t bytes, hipStream_t st)
 {
     size_t need = 0;
     const int64_t nl = m->nl;
     BatchedWs<T> w = carve_batched<T>(g, nl, cfg.bw, ws, bytes, &need);
+    // the records of Ubar: the loop's U^d and D, 3 nl each, are free here
+    static_assert(sizeof(typename Vec4<T>::type) == 4 * sizeof(T), "4 nl values in 6 nl");
+    typename Vec4<T>::type* const ub4 = reinterpret_cast<typename Vec4<T>::type*>(w.s.ud);
     const int64_t nfin = (int64_t)g.nbox * (g.box / TILE) * g.box;
     const unsigned gfin = (unsigned)(nfin < 65535 ? (nfin > 0 ? nfin : 1) : 65535);
-    if (nl > 0) {
-        k_adjoint_markers<T><<<(unsigned)((nl + 255) / 256), 256, 0, st>>>(
-            nl, dt, g.inv_h3, b->perm, m->pid, m->dv, Ui, aF, aUd, Ub, w.s.f4, w.queue);
-        launch_spread<T, P>(cfg, st, g, w, b, 0);
+    // Ui = J a_f and the position gradient of S^T with F^m; a_f = dt G after the first step
+    if (af)
+        launch_interp<T, P, 3>(cfg, st, g, nl, 0.0, w.items, w.nitems, af, nullptr, nullptr,
+                               w.nb_u, w.s, nullptr, w.queue, Ui, b->perm, Fm, gX, 1);
+    else
+        launch_interp<T, P, 4>(cfg, st, g, nl, dt, w.items, w.nitems, nullptr, w.G, w.rmask,
+                               w.nb_g, w.s, nullptr, w.queue, Ui, b->perm, Fm, gX, 1);
+    k_adjoint_markers<T><<<(unsigned)((nl + 255) / 256), 256, 0, st>>>(
+        nl, dt, g.inv_h3, b->perm, m->pid, m->dv, Ui, aF, aUd, Ub, ub4, Fp, w.s.f4, w.queue);
+    // the position gradient of J with u^(m-1) = u0 + dt S F^(m-1)
+    if (Fp) {
+        launch_spread<T, P>(cfg, st, g, w, b, 1);
+        launch_interp<T, P, 5>(cfg, st, g, nl, dt, w.items, w.nitems, u0, w.G, w.rmask, w.nb_g,
+                               w.s, nullptr, w.queue, nullptr, b->perm, Ub, gX, 0, w.nb_u);
+    } else {
+        launch_interp<T, P, 3>(cfg, st, g, nl, 0.0, w.items, w.nitems, u0, nullptr, nullptr,
+                               w.nb_u, w.s, nullptr, w.queue, nullptr, b->perm, Ub, gX, 0);
     }
-    launch_finalize<T>(gfin, st, g, w.slot, w.G, w.tmask, gu0, gu0, af, 1.0, nl > 0, 0, cfg.masks,
-                       nullptr, nullptr, 0, true, dt);
+    // G = J^T Ubar = a_u, which the next step takes from the slots
+    w.s.f4 = ub4;
+    launch_spread<T, P>(cfg, st, g, w, b, 0);
+    launch_finalize<T>(gfin, st, g, w.slot, w.G, w.tmask, gu0, gu0, nullptr, 1.0, 1, 0,
+                       cfg.masks);
 }
 
 int tile_adjoint_step(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,
-                      const ib_markers* m, const ib_buckets* b, double dt, const void* Ui,
-                      void* aF, double* aUd, void* Ub, void* gu0, void* af, void* ws,
-                      size_t ws_bytes, hipStream_t st)
+                      const ib_markers* m, const ib_buckets* b, double dt, const void* af,
+                      const void* Fm, const void* Fp, const void* u0, void* Ui, void* aF,
+                      double* aUd, void* Ub, void* gu0, double* gX, void* ws, size_t ws_bytes,
+                      hipStream_t st)
 {
-    if (ws_bytes < tile_spread_workspace(g, prec, m->nl))
+    if (ws_bytes < tile_adjoint_workspace(g, prec, m->nl))
         return IB_EWORKSPACE;
+    if (m->nl == 0)
+        return IB_OK;
 #define IBX_ADJOINT_STEP(T, P)                                                                 \
-    adjoint_step_t<T, P>(g, cfg, m, b, dt, (const T*)Ui, (T*)aF, aUd, (T*)Ub, (T*)gu0, (T*)af, ws, \
-                         ws_bytes, st)
+    adjoint_step_t<T, P>(g, cfg, m, b, dt, (const T*)af, (const T*)Fm, (const T*)Fp,           \
+                         (const T*)u0, (T*)Ui, (T*)aF, aUd, (T*)Ub, (T*)gu0, gX, ws, ws_bytes, st)
     if (prec == IB_F64 && P == 3)
         IBX_ADJOINT_STEP(double, 3);
     else if (prec == IB_F64)
@@ -1475,43 +1440,6 @@ int tile_adjoint_step(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,
     else
         IBX_ADJOINT_STEP(float, 4);
 #undef IBX_ADJOINT_STEP
-    return launch_status();
-}
-
-template <typename T, int P>
-static void interp_grad_t(const Grid& g, const BatchedCfg& cfg, const ib_markers* m,
-                          const ib_buckets* b, const T* fld, const T* v, T* U, int use_dv,
-                          double* gX, void* ws, size_t bytes, hipStream_t st)
-{
-    size_t need = 0;
-    BatchedWs<T> w = carve_batched<T>(g, m->nl, cfg.bw, ws, bytes, &need);
-    launch_interp<T, P, 3>(cfg, st, g, m->nl, 0.0, w.items, w.nitems, fld, nullptr, nullptr,
-                           w.nb_u, w.s, nullptr, w.queue, U, b->perm, v, gX, use_dv);
-}
-
-int tile_interp_grad(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,
-                     const ib_markers* m, const ib_buckets* b, const void* fld, const void* v,
-                     void* U, int use_dv, double* gX, void* ws, size_t ws_bytes, hipStream_t st)
-{
-    if (ws_bytes < tile_spread_workspace(g, prec, m->nl))
-        return IB_EWORKSPACE;
-    if (m->nl == 0)
-        return IB_OK;
-    if (prec == IB_F64) {
-        if (P == 3)
-            interp_grad_t<double, 3>(g, cfg, m, b, (const double*)fld, (const double*)v,
-                                     (double*)U, use_dv, gX, ws, ws_bytes, st);
-        else
-            interp_grad_t<double, 4>(g, cfg, m, b, (const double*)fld, (const double*)v,
-                                     (double*)U, use_dv, gX, ws, ws_bytes, st);
-    } else {
-        if (P == 3)
-            interp_grad_t<float, 3>(g, cfg, m, b, (const float*)fld, (const float*)v,
-                                    (float*)U, use_dv, gX, ws, ws_bytes, st);
-        else
-            interp_grad_t<float, 4>(g, cfg, m, b, (const float*)fld, (const float*)v,
-                                    (float*)U, use_dv, gX, ws, ws_bytes, st);
-    }
     return launch_status();
 }
 

@@ -38,32 +38,25 @@ int batched_multidirect(const Grid& g, int P, ib_prec prec, const BatchedCfg& cf
                         double dt, const void* u0, void* ustar, void* f, void* F, double* resid,
                         void* Fhist, void* ws, size_t ws_bytes, hipStream_t st, int f_acc = 0);
 
-// Spreading with the loop's tile kernel outside the loop (the adjoint):
-// records and work lists once per call, then out = S v (use_dv: with dV/h^3,
-// else without) on every valid covered cell, or out = u0 + dt S v when u0 is
-// given.  v: [nl][3] in marker order.  Grids with fewer than 16 cells on an
-// axis, or boxes above 512, are not supported (tile_spread_supported).
-bool tile_spread_supported(const Grid& g);
-size_t tile_spread_workspace(const Grid& g, ib_prec prec, int64_t nl);
-int tile_spread_setup(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,
-                      const ib_particles* p, const ib_markers* m, const ib_buckets* b, void* ws,
-                      size_t ws_bytes, hipStream_t st);
-int tile_spread(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg, const ib_markers* m,
-                const ib_buckets* b, const void* v, int use_dv, const void* u0, double dt,
-                void* out, void* ws, size_t ws_bytes, hipStream_t st);
-// One step of the adjoint with the same set-up: a_F += (dV/h^3) Ui, a_Ud += a_F/dt
-// and Ub = -a_F/dt on the markers (marker order), then with G = J^T Ub the fields
-// gu0 += G and af = dt G (af nullable) on every valid covered cell, in one pass.
+// The adjoint on the loop's tile kernels: records and work lists once per call,
+// then a step at a time.  Grids with fewer than 16 cells on an axis, or boxes above
+// 512, are not supported (tile_adjoint_supported).
+bool tile_adjoint_supported(const Grid& g);
+size_t tile_adjoint_workspace(const Grid& g, ib_prec prec, int64_t nl);
+int tile_adjoint_setup(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,
+                       const ib_particles* p, const ib_markers* m, const ib_buckets* b, void* ws,
+                       size_t ws_bytes, hipStream_t st);
+// One step m of the reverse sweep (backward.hip), steps in order from ns: Ui = J a_f,
+// a_F += (dV/h^3) Ui, a_Ud += a_F/dt, Ub = -a_F/dt, gu0 += a_u = J^T Ub on every
+// valid covered cell, and gX += both position gradients.  af (the field, box layout)
+// is given for the first step; later ones take a_f = dt a_u from the step before,
+// which the workspace holds.  Fm = F^m, Fp = F^(m-1) (null for m = 1); marker
+// arrays [nl][3] in marker order.
 int tile_adjoint_step(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,
-                      const ib_markers* m, const ib_buckets* b, double dt, const void* Ui,
-                      void* aF, double* aUd, void* Ub, void* gu0, void* af, void* ws,
-                      size_t ws_bytes, hipStream_t st);
-// With the same set-up: U = J fld (U nullable, marker order) and
-// gX += sc sum over the stencil of (fld . v_l) grad_X w_l, sc = dV/h^3
-// (use_dv) or 1, for a field fld in the box layout and v [nl][3].
-int tile_interp_grad(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,
-                     const ib_markers* m, const ib_buckets* b, const void* fld, const void* v,
-                     void* U, int use_dv, double* gX, void* ws, size_t ws_bytes, hipStream_t st);
+                      const ib_markers* m, const ib_buckets* b, double dt, const void* af,
+                      const void* Fm, const void* Fp, const void* u0, void* Ui, void* aF,
+                      double* aUd, void* Ub, void* gu0, double* gX, void* ws, size_t ws_bytes,
+                      hipStream_t st);
 
 // Particle-by-particle order of the loop, run level by level (sequential.hip).
 constexpr int SEQ_MAX_LEVELS = 4096;

@@ -97,10 +97,12 @@ __device__ inline void item_base(const Grid& g, int t, int k, const int32_t* __r
 // mode 0: field = u0 (box layout): D = (U^d - J u0)/dt, F = D.
 // mode 1: field = G (slots): F += D - J G.
 // mode 2: field = G (slots): residual only.
-// mode 3: field = u0 (any field in the box layout), for the adjoint:
-//         Fout[l] = J field (if Fout) and gX[l] += sc sum over the stencil of
-//         (field . vin_l) grad_X w_l, sc = dV/h^3 (use_dv) or 1, in marker
-//         order (the weights' derivatives from the same shared root).
+// modes 3, 4, 5, for the adjoint: Fout[l] = J field (if Fout) and gX[l] += sc sum
+//         over the stencil of (field . vin_l) grad_X w_l, sc = dV/h^3 (use_dv)
+//         or 1, in marker order (the weights' derivatives from the same shared
+//         root).  field = u0 (mode 3, any field in the box layout), dt G (4) or
+//         u0 + dt G (5), formed as the tiles are staged: as passes over the
+//         fields of spheres64_128 they took 13 us each, four a call of three steps.
 // e2 (nullable) receives the sum of dV |U^d - J u^(m)|^2 over the markers of each
 // item, by a fixed tree.
 // (FP32 with the row masks, 256-marker items of one tile: registers capped at
@@ -108,18 +110,20 @@ __device__ inline void item_base(const Grid& g, int t, int k, const int32_t* __r
 template <typename T, int P, int MODE, int BW, bool MASK = false, int TXW = TILE>
 __global__ void __launch_bounds__(BW)
 __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && BW == 256 && TXW == TILE
-                                        ? (MASK ? 7 : MODE == 0 ? 5 : 1) : 1, 8)))
+                                        ? (MODE >= 3 ? 1 : MASK ? 7 : MODE == 0 ? 5 : 1) : 1, 8)))
 k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
                const int32_t* __restrict__ nitems, const T* __restrict__ u0,
                const T* __restrict__ G, const int64_t* __restrict__ nbase, MarkerData<T> s,
                double* __restrict__ e2, T* __restrict__ Fout, const int32_t* __restrict__ perm,
                const T* __restrict__ vin, double* __restrict__ gX, int use_dv,
-               const uint64_t* __restrict__ rmask, int32_t* __restrict__ queue)
+               const uint64_t* __restrict__ rmask, int32_t* __restrict__ queue,
+               const int64_t* __restrict__ nbase_u)
 {
+    constexpr bool ADJ = MODE >= 3, BOTH = MODE == 5;   // BOTH: nbase for G, nbase_u for u0
     // the spreading that follows takes its tiles from these counters
-    if (MODE < 2 && blockIdx.x == 0 && threadIdx.x < NXCD * NQ)
+    if (MODE != 2 && blockIdx.x == 0 && threadIdx.x < NXCD * NQ)
         queue[threadIdx.x * QSTRIDE] = 0;
-    constexpr bool BOX = MODE == 0 || MODE == 3;   // field in the box layout
+    constexpr bool BOX = MODE == 0 || MODE == 3 || BOTH;   // field in the box layout
     constexpr int gh = Halo<P>::g, R = Halo<P>::R;
     // The work tile is TXW x 8 x 8 cells: one tile, or two x neighbours
     // (TXW = 16).  LDS holds its halo as rows [c][jz][jy] of pitch RP with
@@ -135,6 +139,7 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
     using T2 = typename Vec2<T>::type;
     __shared__ __align__(16) T fld[3 * PL];
     __shared__ int64_t nb[NNB];
+    __shared__ int64_t nb_u[BOTH ? NNB : 1];
     __shared__ uint64_t nbm[NNB];       // tile slots: rows of each neighbour's slot not all zero
     __shared__ double esum[BW / 64];
     const int n_items = *nitems;
@@ -148,6 +153,10 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
     // two elements (box extents and component strides are then even)
     const bool pairs = BOX && (g.ngrow & 1) == 0 && !((uintptr_t)src & (2 * sizeof(T) - 1));
     const Slab sl = xcd_slab(n_items);
+    // whether neighbour sel's slot holds its row (y, z)
+    auto in_slot = [&](int sel, int y, int z) {
+        return nb[sel] >= 0 && (!MASK || ((nbm[sel] >> (y + TILE * z)) & 1));
+    };
     // The neighbour offsets of each item are loaded one item ahead (two with
     // the row masks, whose loads follow them one item ahead), so the staging
     // and compute of an item hide those loads.
@@ -156,7 +165,10 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
     };
     int64_t pnb = sl.begin < sl.end && tid < NNB ? nbase[(int64_t)sl.begin * NNB + tid] : 0;
     uint64_t pm = 0ull;
-    int64_t qnb = 0;
+    int64_t qnb = 0, pnu = 0;
+    if (BOTH && sl.begin < sl.end && tid < NNB)
+        pnu = nbase_u[(int64_t)sl.begin * NNB + tid];
+    const T tdt = (T)dt;
     if constexpr (MASK) {
         if (tid < NNB && sl.begin < sl.end)
             pm = row_mask(pnb);
@@ -168,8 +180,12 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
             nb[tid] = pnb;
             if constexpr (MASK)
                 nbm[tid] = pm;
+            if (BOTH)
+                nb_u[tid] = pnu;
         }
         __syncthreads();
+        if (BOTH && tid < NNB && it + sl.stride < sl.end)
+            pnu = nbase_u[(int64_t)(it + sl.stride) * NNB + tid];
         if constexpr (MASK) {
             if (tid < NNB) {
                 pnb = qnb;
@@ -205,7 +221,7 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
             const typename Vec4<T>::type gq = s.geo[i];
             int rb[3];
             unpack_rb(s.rb[i], rb);
-            if (MODE == 3) {
+            if (ADJ) {
                 axis_weights_rd<T, P>(gq.x, w[0], dw[0]);
                 axis_weights_rd<T, P>(gq.y, w[1], dw[1]);
                 axis_weights_rd<T, P>(gq.z, w[2], dw[2]);
@@ -222,7 +238,7 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
             for (int a = 0; a < 3; ++a)
                 lb[a] = rb[a] - lo[a] + gh;
             rs = gq.w;
-            if (sub == 0 && MODE != 3) {
+            if (sub == 0 && !ADJ) {
 #pragma unroll
                 for (int c = 0; c < 3; ++c)
                     dd[c] = MODE == 0 ? s.ud[c * nl + i] : s.d[c * nl + i];
@@ -244,7 +260,7 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
                     const int xo = 2 * px - 2;   // x of the pair's first cell from lo
                     const int sel = ((xo + TILE) >> 3) + NBX * (((jy - gh + TILE) >> 3) +
                                                                 3 * ((jz - gh + TILE) >> 3));
-                    const int64_t b = nb[sel];
+                    const int64_t b = BOTH ? nb_u[sel] : nb[sel];
                     T2 v0, v1, v2;
                     v0.x = v0.y = v1.x = v1.y = v2.x = v2.y = T(0);
                     if (b >= 0) {
@@ -253,6 +269,19 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
                         v0 = *reinterpret_cast<const T2*>(p);
                         v1 = *reinterpret_cast<const T2*>(p + comp);
                         v2 = *reinterpret_cast<const T2*>(p + 2 * comp);
+                    }
+                    if (BOTH && in_slot(sel, (jy - gh) & 7, (jz - gh) & 7)) {
+                        const T* p = G + nb[sel] + (xo & 7) + TILE * ((jy - gh) & 7) +
+                                     TILE * TILE * ((jz - gh) & 7);
+                        const T2 g0 = *reinterpret_cast<const T2*>(p);
+                        const T2 g1 = *reinterpret_cast<const T2*>(p + TILE_CELLS);
+                        const T2 g2 = *reinterpret_cast<const T2*>(p + 2 * TILE_CELLS);
+                        v0.x = v0.x + tdt * g0.x;
+                        v0.y = v0.y + tdt * g0.y;
+                        v1.x = v1.x + tdt * g1.x;
+                        v1.y = v1.y + tdt * g1.y;
+                        v2.x = v2.x + tdt * g2.x;
+                        v2.y = v2.y + tdt * g2.y;
                     }
                     const int at = (jz * R + jy) * RP + 2 * px;
                     *reinterpret_cast<T2*>(fld + at) = v0;
@@ -271,7 +300,7 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
                     const int jx = q % RX, jy = (q / RX) % R, jz = q / (RX * R);
                     const int sel = ((jx - gh + TILE) >> 3) + NBX * (((jy - gh + TILE) >> 3) +
                                                                     3 * ((jz - gh + TILE) >> 3));
-                    const int64_t b = nb[sel];
+                    const int64_t b = BOTH ? nb_u[sel] : nb[sel];
                     T v0 = T(0), v1 = T(0), v2 = T(0);
                     if (b >= 0) {
                         const int64_t off = b + ((jx - gh) & 7) + (int64_t)sy * ((jy - gh) & 7) +
@@ -279,6 +308,13 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
                         v0 = src[off];
                         v1 = src[off + comp];
                         v2 = src[off + 2 * comp];
+                    }
+                    if (BOTH && in_slot(sel, (jy - gh) & 7, (jz - gh) & 7)) {
+                        const T* p = G + nb[sel] + ((jx - gh) & 7) + TILE * ((jy - gh) & 7) +
+                                     TILE * TILE * ((jz - gh) & 7);
+                        v0 = v0 + tdt * p[0];
+                        v1 = v1 + tdt * p[TILE_CELLS];
+                        v2 = v2 + tdt * p[2 * TILE_CELLS];
                     }
                     const int at = (jz * R + jy) * RP + XO + jx;
                     fld[at] = v0;
@@ -337,6 +373,17 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
                 vl.x = bl >= 0 ? src[bl + roff + TILE - 1] : T(0);
                 vr.x = br >= 0 ? src[br + roff] : T(0);
             }
+            if (MODE == 4) {
+#pragma unroll
+                for (int k = 0; k < TXW / 2; ++k) {
+                    v[k].x = tdt * v[k].x;
+                    v[k].y = tdt * v[k].y;
+                }
+                vl.x = tdt * vl.x;
+                vl.y = tdt * vl.y;
+                vr.x = tdt * vr.x;
+                vr.y = tdt * vr.y;
+            }
 #pragma unroll
             for (int k = 0; k < TXW / 2; ++k)
                 *reinterpret_cast<T2*>(row + 2 + 2 * k) = v[k];
@@ -360,11 +407,11 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
                 const int k = sub + (n << lg);
                 if (!ok || k >= P)
                     continue;
-                T wz = w[2][0], dwz = MODE == 3 ? dw[2][0] : T(0);
+                T wz = w[2][0], dwz = ADJ ? dw[2][0] : T(0);
 #pragma unroll
                 for (int o = 1; o < P; ++o) {
                     wz = k == o ? w[2][o] : wz;
-                    if (MODE == 3)
+                    if (ADJ)
                         dwz = k == o ? dw[2][o] : dwz;
                 }
 #pragma unroll
@@ -379,7 +426,7 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
                         acc0 += f0 * wt;
                         acc1 += f1 * wt;
                         acc2 += f2 * wt;
-                        if (MODE == 3) {
+                        if (ADJ) {
                             const T dot = f0 * vv[0] + f1 * vv[1] + f2 * vv[2];
                             gr0 += dot * dw[0][q] * wyz;
                             gr1 += dot * w[0][q] * dw[1][j] * wz;
@@ -393,7 +440,7 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
             acc0 += __shfl_xor(acc0, 1);
             acc1 += __shfl_xor(acc1, 1);
             acc2 += __shfl_xor(acc2, 1);
-            if (MODE == 3) {
+            if (ADJ) {
                 gr0 += __shfl_xor(gr0, 1);
                 gr1 += __shfl_xor(gr1, 1);
                 gr2 += __shfl_xor(gr2, 1);
@@ -403,13 +450,13 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
             acc0 += __shfl_xor(acc0, 2);
             acc1 += __shfl_xor(acc1, 2);
             acc2 += __shfl_xor(acc2, 2);
-            if (MODE == 3) {
+            if (ADJ) {
                 gr0 += __shfl_xor(gr0, 2);
                 gr1 += __shfl_xor(gr1, 2);
                 gr2 += __shfl_xor(gr2, 2);
             }
         }
-        if (MODE == 3 && mine && sub == 0) {
+        if (ADJ && mine && sub == 0) {
             const int64_t l = perm[i];
             if (Fout) {
                 Fout[3 * l + 0] = acc0;
@@ -423,7 +470,7 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
             gX[3 * l + 2] += sc * (double)gr2;
         }
         double err = 0.0;
-        if (MODE != 3 && mine && sub == 0) {
+        if (!ADJ && mine && sub == 0) {
             const T acc[3] = {acc0, acc1, acc2};
             const T idt = (T)(1.0 / dt);
             T nf[3];
@@ -461,7 +508,7 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
                 Fout[3 * l + 2] = fv.z;
             }
         }
-        if (MODE != 3 && e2) {
+        if (!ADJ && e2) {
             double v = (double)rs * h3 * err;
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1)
@@ -470,7 +517,7 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
                 esum[tid >> 6] = v;
         }
         __syncthreads();
-        if (MODE != 3 && e2 && tid == 0) {
+        if (!ADJ && e2 && tid == 0) {
             double v = 0.0;
 #pragma unroll
             for (int k = 0; k < BW / 64; ++k)

@@ -225,3 +225,24 @@ def test_missing_gradients_count_as_zeros(dev, n, ns, delta, ngrow, dtype):
             want = _valid(c.lev, full[0]) if k == 0 else torch.zeros_like(_valid(c.lev, u0))
             assert torch.equal(_valid(c.lev, a[0]), want)
             assert all((x == 0).all() for x in a[1:])
+
+
+@pytest.mark.parametrize("delta,dtype,masks", [(3, "f32", False), (4, "f32", True),
+                                               (4, "f64", False)])
+def test_adjoint_does_not_depend_on_the_ghost_width(dev, delta, dtype, masks):
+    """The adjoint's interpolations stage fields in pairs of cells with an even
+    ghost width and cell by cell with an odd one: the same bits."""
+    import torch
+    announce(f"adjoint ghost width P={delta} {dtype} masks={masks}")
+    out = []
+    for ngrow in (0, 1, 2, 3):
+        wl = W.make_workload("grad_ghost", 32, 16, ngrow, delta, 3, np.array([6.3, 7.7]),
+                             seed=13, nmodes=8, K=4, cover_all=True)
+        c = Case(wl, dev)
+        gus = np.random.default_rng(14).normal(size=(c.lev.nbox, 3, 16, 16, 16))
+        wts = np.random.default_rng(15).normal(size=(wl.npart, 3))
+        L, gu0, gup, gom, gX = _grads(c, dtype, 2, wts, with_ustar=gus, row_masks=masks)
+        out.append((_valid(c.lev, gu0), gup, gom, gX))
+    for o in out[1:]:
+        for x, y in zip(out[0], o):
+            assert torch.equal(x, y)
