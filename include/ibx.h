@@ -153,7 +153,7 @@ int ib_bucket(const ib_level* lv, const ib_markers* m, ib_delta delta, const ib_
 /* ---------------------------------------------------------------------- */
 /* a4  Velocity interpolation, Algorithm 1 first sub-step:                  */
 /*     U_l = sum_x u(x) delta_h(x - X_l) h^3.                               */
-/* u: field in the box layout; U: device [nl][3].  One thread per marker,   */
+/* u: field in the box layout; U: device [nl][3].  Four lanes per marker,   */
 /* FP64 or FP32 arithmetic as prec.  A marker whose stencil reaches a cell  */
 /* off a bounded axis or in an uncovered box gets U = NaN.                  */
 /* ---------------------------------------------------------------------- */
