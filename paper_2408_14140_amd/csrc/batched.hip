@@ -572,91 +572,6 @@ __device__ void finalize_poison(const Grid& g, T* ustar, T* f, T* Fp, int64_t nF
         Fp[i] = nan;
 }
 
-// Last step of Algorithm 1 on every valid cell of the covered boxes:
-// f = G^ns and ustar = u0 + dt G^ns, with G = 0 on tiles no marker reaches
-// (and everywhere when use_g is 0) and on the slot rows whose bit in the
-// tile's row mask (tilemask, indexed by tile) is clear.  One workgroup per
-// (box, row of tiles in y, z plane): box-wide x rows, so the box layout is
-// written in long runs.
-// In place (ustar == u0) only the cells whose force is not exactly zero are
-// read and rewritten (u0 + dt 0 = u0): inside the tiles that have a force
-// slot, most cells lie outside every stencil.  With f_acc, f += G^ns instead,
-// on the same cells.  ustar may be null (f only).  A separate ustar takes u0
-// on the cells without force (copy).  With flag (nullable) raised (a flagged
-// bucket set), f and ustar are NaN on every such cell instead, and so is
-// Fp[0 .. nF) (the marker forces, written before this kernel).
-template <typename T, bool F_ACC, bool MASK>
-__global__ void __launch_bounds__(256)
-k_finalize(Grid g, const int32_t* __restrict__ slot, const T* __restrict__ G,
-           const uint64_t* __restrict__ tilemask, const T* u0, T* ustar, T* __restrict__ f,
-           double dt, int use_g, int copy, const int32_t* __restrict__ flag, T* __restrict__ Fp,
-           int64_t nF)
-{
-    if (flag && (flag[0] | flag[1]) != 0) {
-        finalize_poison(g, ustar, f, Fp, nF);
-        return;
-    }
-    __shared__ int tslot[64];                 // G slot of each tile along the row
-    __shared__ uint64_t tmask[64];            // and its row mask
-    const int B = g.box;
-    const int nty = B / TILE, ntx = B / TILE;
-    const int64_t items = (int64_t)g.nbox * nty * B;
-    const T tdt = (T)dt;
-    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
-        const int bid = (int)(it / ((int64_t)nty * B));
-        const int rem = (int)(it - (int64_t)bid * nty * B);
-        const int ty = rem / B, lz = rem - ty * B;
-        const int bx0 = g.box_lo[3 * bid], by0 = g.box_lo[3 * bid + 1], bz0 = g.box_lo[3 * bid + 2];
-        const int cz = bz0 + lz, cyt = (by0 >> 3) + ty;
-        for (int k = threadIdx.x; k < ntx; k += blockDim.x) {
-            const int64_t tk = (bx0 >> 3) + k + g.nt[0] * (cyt + g.nt[1] * (cz >> 3));
-            tslot[k] = use_g ? slot[tk] : -1;
-            if (MASK)
-                tmask[k] = use_g ? tilemask[tk] : 0ull;
-        }
-        __syncthreads();
-        for (int q = threadIdx.x; q < TILE * B; q += blockDim.x) {
-            const int yy = q / B, lx = q - yy * B;
-            const int ly = ty * TILE + yy;
-            const int s =
-                !MASK || (tmask[lx >> 3] >> (yy + TILE * (cz & 7))) & 1 ? tslot[lx >> 3] : -1;
-            const int64_t off = (int64_t)bid * g.bstride +
-                                ((int64_t)(lz + g.ngrow) * g.ext + (ly + g.ngrow)) * g.ext +
-                                (lx + g.ngrow);
-            const int64_t go =
-                (int64_t)s * 3 * TILE_CELLS + (lx & 7) + TILE * (yy + TILE * (cz & 7));
-            // every load before the first store: the stores may alias u0, so
-            // a load behind one would wait for it
-            T v[3], a[3];
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                v[c] = s >= 0 ? G[go + c * TILE_CELLS] : T(0);
-                if (copy)
-                    a[c] = u0[off + c * g.cstride];
-            }
-            if (ustar && !copy) {
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    a[c] = v[c] != T(0) ? u0[off + c * g.cstride] : T(0);
-            }
-#pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const int64_t o = off + c * g.cstride;
-                // streaming stores: nothing here is read again by this kernel
-                if (f && !F_ACC)
-                    __builtin_nontemporal_store(v[c], &f[o]);
-                else if (f && v[c] != T(0))
-                    f[o] += v[c];
-                if (ustar && v[c] != T(0))
-                    __builtin_nontemporal_store(a[c] + tdt * v[c], &ustar[o]);
-                else if (copy)
-                    __builtin_nontemporal_store(a[c], &ustar[o]);
-            }
-        }
-        __syncthreads();
-    }
-}
-
 template <typename T>
 struct Pair;
 template <>
@@ -686,15 +601,101 @@ __device__ inline void put(V v, V* p)
         *p = v;
 }
 
+// Last step of Algorithm 1 on every valid cell of the covered boxes:
+// f = G^ns and ustar = u0 + dt G^ns, with G = 0 on tiles no marker reaches
+// (and everywhere when use_g is 0) and on the slot rows whose bit in the
+// tile's row mask (tilemask, indexed by tile) is clear.  One workgroup per
+// (box, row of tiles in y, z plane): box-wide x rows, so the box layout is
+// written in long runs.  (As many z planes as give each thread a cell.)
+// In place (ustar == u0) only the cells whose force is not exactly zero are
+// read and rewritten (u0 + dt 0 = u0): inside the tiles that have a force
+// slot, most cells lie outside every stencil.  With f_acc, f += G^ns instead,
+// on the same cells.  ustar may be null (f only).  A separate ustar takes u0
+// on the cells without force (copy).  With flag (nullable) raised (a flagged
+// bucket set), f and ustar are NaN on every such cell instead, and so is
+// Fp[0 .. nF) (the marker forces, written before this kernel).
+template <typename T, bool F_ACC, bool MASK, bool STREAM>
+__global__ void __launch_bounds__(256)
+k_finalize(Grid g, const int32_t* __restrict__ slot, const T* __restrict__ G,
+           const uint64_t* __restrict__ tilemask, const T* u0, T* ustar, T* __restrict__ f,
+           double dt, int use_g, int copy, const int32_t* __restrict__ flag, T* __restrict__ Fp,
+           int64_t nF, int planes)
+{
+    if (flag && (flag[0] | flag[1]) != 0) {
+        finalize_poison(g, ustar, f, Fp, nF);
+        return;
+    }
+    __shared__ int tslot[64];                 // G slot of each tile along the row
+    __shared__ uint64_t tmask[64];            // and its row mask
+    const int B = g.box;
+    const int nty = B / TILE, ntx = B / TILE;
+    const int per_box = nty * (B / planes);
+    const int64_t items = (int64_t)g.nbox * per_box;
+    const T tdt = (T)dt;
+    for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
+        const int bid = (int)(it / per_box);
+        const int rem = (int)(it - (int64_t)bid * per_box);
+        const int ty = rem / (B / planes), lz0 = planes * (rem - ty * (B / planes));
+        const int bx0 = g.box_lo[3 * bid], by0 = g.box_lo[3 * bid + 1], bz0 = g.box_lo[3 * bid + 2];
+        const int cz0 = bz0 + lz0, cyt = (by0 >> 3) + ty;
+        for (int k = threadIdx.x; k < ntx; k += blockDim.x) {
+            const int64_t tk = (bx0 >> 3) + k + g.nt[0] * (cyt + g.nt[1] * (cz0 >> 3));
+            tslot[k] = use_g ? slot[tk] : -1;
+            if (MASK)
+                tmask[k] = use_g ? tilemask[tk] : 0ull;
+        }
+        __syncthreads();
+        for (int q = threadIdx.x; q < planes * TILE * B; q += blockDim.x) {
+            const int r = q / B, lx = q - r * B;
+            const int yy = r & (TILE - 1), lz = lz0 + (r >> 3), cz = bz0 + lz;
+            const int ly = ty * TILE + yy;
+            const int s =
+                !MASK || (tmask[lx >> 3] >> (yy + TILE * (cz & 7))) & 1 ? tslot[lx >> 3] : -1;
+            const int64_t off = (int64_t)bid * g.bstride +
+                                ((int64_t)(lz + g.ngrow) * g.ext + (ly + g.ngrow)) * g.ext +
+                                (lx + g.ngrow);
+            const int64_t go =
+                (int64_t)s * 3 * TILE_CELLS + (lx & 7) + TILE * (yy + TILE * (cz & 7));
+            // every load before the first store: the stores may alias u0, so
+            // a load behind one would wait for it
+            T v[3], a[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                v[c] = s >= 0 ? G[go + c * TILE_CELLS] : T(0);
+                if (copy)
+                    a[c] = u0[off + c * g.cstride];
+            }
+            if (ustar && !copy) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c)
+                    a[c] = v[c] != T(0) ? u0[off + c * g.cstride] : T(0);
+            }
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const int64_t o = off + c * g.cstride;
+                if (f && !F_ACC)
+                    put<STREAM, T>(v[c], &f[o]);
+                else if (f && v[c] != T(0))
+                    f[o] += v[c];
+                if (ustar && v[c] != T(0))
+                    put<STREAM, T>(a[c] + tdt * v[c], &ustar[o]);
+                else if (copy)
+                    put<STREAM, T>(a[c], &ustar[o]);
+            }
+        }
+        __syncthreads();
+    }
+}
+
 // The same for an even ghost width, two neighbouring x cells per thread (every
 // pair starts on an even element of the box layout and of the tile slots):
-// one workgroup per (box, row of tiles in y, pair of z planes).
+// one workgroup per (box, row of tiles in y, two or more z planes).
 template <typename T, bool F_ACC, bool MASK, bool STREAM>
 __global__ void __launch_bounds__(256)
 k_finalize_pairs(Grid g, const int32_t* __restrict__ slot, const T* __restrict__ G,
                  const uint64_t* __restrict__ tilemask, const T* u0, T* ustar, T* __restrict__ f,
                  double dt, int use_g, int copy, const int32_t* __restrict__ flag,
-                 T* __restrict__ Fp, int64_t nF)
+                 T* __restrict__ Fp, int64_t nF, int planes)
 {
     using V2 = typename Pair<T>::type;
     if (flag && (flag[0] | flag[1]) != 0) {
@@ -705,13 +706,13 @@ k_finalize_pairs(Grid g, const int32_t* __restrict__ slot, const T* __restrict__
     __shared__ uint64_t tmask[64];            // and its row mask
     const int B = g.box;
     const int nty = B / TILE, ntx = B / TILE, npx = B / 2;
-    const int per_box = nty * (B / 2);
+    const int per_box = nty * (B / planes);
     const int64_t items = (int64_t)g.nbox * per_box;
     const T tdt = (T)dt;
     for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
         const int bid = (int)(it / per_box);
         const int rem = (int)(it - (int64_t)bid * per_box);
-        const int ty = rem / (B / 2), lz0 = 2 * (rem - ty * (B / 2));
+        const int ty = rem / (B / planes), lz0 = planes * (rem - ty * (B / planes));
         const int bx0 = g.box_lo[3 * bid], by0 = g.box_lo[3 * bid + 1], bz0 = g.box_lo[3 * bid + 2];
         const int cz0 = bz0 + lz0, cyt = (by0 >> 3) + ty;
         for (int k = threadIdx.x; k < ntx; k += blockDim.x) {
@@ -721,7 +722,7 @@ k_finalize_pairs(Grid g, const int32_t* __restrict__ slot, const T* __restrict__
                 tmask[k] = use_g ? tilemask[tk] : 0ull;
         }
         __syncthreads();
-        for (int q = threadIdx.x; q < 2 * TILE * npx; q += blockDim.x) {
+        for (int q = threadIdx.x; q < planes * TILE * npx; q += blockDim.x) {
             const int px = q % npx, r = q / npx;
             const int yy = r & (TILE - 1), pz = r >> 3;
             const int lx = 2 * px, ly = ty * TILE + yy, lz = lz0 + pz;
@@ -774,27 +775,38 @@ k_finalize_pairs(Grid g, const int32_t* __restrict__ slot, const T* __restrict__
     }
 }
 
-template <typename T, bool F_ACC, bool MASK>
-static void finalize_kernel(bool pairs, unsigned grid, unsigned gp, hipStream_t st, const Grid& g,
-                            const int32_t* slot, const T* G, const uint64_t* tilemask,
-                            const T* u0, T* ustar, T* f, double dt, int use_g, int copy,
-                            const int32_t* flag, T* Fp, int64_t nF)
+// z planes of one tile that a workgroup of 256 takes: as many as have a thread a
+// cell (or pair of cells), up to the tile's eight, from `least`.  With one plane (two
+// in pairs) whatever the box, half the threads had no cell in boxes of 16: the channel
+// 96 x 160 x 64 with an odd ghost width took 16.5 us, now 12.6 (with plain stores).
+static int finalize_planes(int per_plane, int least)
 {
-    if (pairs && (sizeof(T) == 8 || !copy))
-        k_finalize_pairs<T, F_ACC, MASK, true><<<gp, 256, 0, st>>>(
-            g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF);
-    else if (pairs)
-        k_finalize_pairs<T, F_ACC, MASK, false><<<gp, 256, 0, st>>>(
-            g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF);
+    int n = least;
+    while (n < TILE && 2 * n * per_plane <= 256)
+        n *= 2;
+    return n;
+}
+
+template <typename T, bool F_ACC, bool MASK, bool STREAM>
+static void finalize_kernel(bool pairs, hipStream_t st, const Grid& g, const int32_t* slot,
+                            const T* G, const uint64_t* tilemask, const T* u0, T* ustar, T* f,
+                            double dt, int use_g, int copy, const int32_t* flag, T* Fp, int64_t nF)
+{
+    const int planes = finalize_planes(TILE * g.box / (pairs ? 2 : 1), pairs ? 2 : 1);
+    const int64_t items = (int64_t)g.nbox * (g.box / TILE) * (g.box / planes);
+    const unsigned grid = (unsigned)(items < 65535 ? (items > 0 ? items : 1) : 65535);
+    if (pairs)
+        k_finalize_pairs<T, F_ACC, MASK, STREAM><<<grid, 256, 0, st>>>(
+            g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF, planes);
     else
-        k_finalize<T, F_ACC, MASK><<<grid, 256, 0, st>>>(g, slot, G, tilemask, u0, ustar, f, dt,
-                                                         use_g, copy, flag, Fp, nF);
+        k_finalize<T, F_ACC, MASK, STREAM><<<grid, 256, 0, st>>>(
+            g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF, planes);
 }
 
 // With flag, the kernel also stands in for the flag check of the outputs
 // (ustar, f and Fp[0 .. nF)).
 template <typename T>
-static void launch_finalize(unsigned grid, hipStream_t st, const Grid& g, const int32_t* slot,
+static void launch_finalize(hipStream_t st, const Grid& g, const int32_t* slot,
                             const T* G, const uint64_t* tilemask, const T* u0, T* ustar, T* f,
                             double dt, int use_g, int f_acc, int masks,
                             const int32_t* flag = nullptr, T* Fp = nullptr, int64_t nF = 0)
@@ -805,11 +817,11 @@ static void launch_finalize(unsigned grid, hipStream_t st, const Grid& g, const 
     const uintptr_t am = 2 * sizeof(T) - 1;
     const bool pairs = (g.ngrow & 1) == 0 && !((uintptr_t)u0 & am) &&
                        !((uintptr_t)ustar & am) && !((uintptr_t)f & am);
-    const int64_t items = (int64_t)g.nbox * (g.box / TILE) * (g.box / 2);
-    const unsigned gp = (unsigned)(items < 65535 ? (items > 0 ? items : 1) : 65535);
+    // streamed stores in FP64 and in place; out of place in FP32 plain ones (k_finalize_pairs)
+    const bool stream = sizeof(T) == 8 || !copy;
 #define IBX_FINALIZE(ACC, MASK)                                                                \
-    finalize_kernel<T, ACC, MASK>(pairs, grid, gp, st, g, slot, G, tilemask, u0, ustar, f, dt,  \
-                                  use_g, copy, flag, Fp, nF)
+    (stream ? finalize_kernel<T, ACC, MASK, true> : finalize_kernel<T, ACC, MASK, sizeof(T) == 8>)( \
+        pairs, st, g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF)
     if (f_acc && masks)
         IBX_FINALIZE(true, true);
     else if (f_acc)
@@ -1225,10 +1237,8 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
         return IB_EWORKSPACE;
     BatchedWs<T> w = carve_batched<T>(g, nl, cfg.bw, ws, ws_bytes, &need);
     const unsigned gm = (unsigned)((nl + 255) / 256 > 0 ? (nl + 255) / 256 : 1);
-    const int64_t nfin = (int64_t)g.nbox * (g.box / TILE) * g.box;
-    const unsigned gfin = (unsigned)(nfin < 65535 ? (nfin > 0 ? nfin : 1) : 65535);
     if (nl == 0) {
-        launch_finalize<T>(gfin, st, g, w.slot, w.G, w.tmask, u0, ustar, f, dt, 0, f_acc,
+        launch_finalize<T>(st, g, w.slot, w.G, w.tmask, u0, ustar, f, dt, 0, f_acc,
                           cfg.masks);
         if (resid)
             k_zero<double><<<1, 64, 0, st>>>(ns + 1, resid);
@@ -1246,7 +1256,7 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
     res.add(ns == 0);
     if (ns == 0) {
         // no iteration: ustar = u0, f = 0, F = 0
-        launch_finalize<T>(gfin, st, g, w.slot, w.G, w.tmask, u0, ustar, f, dt, 0, f_acc,
+        launch_finalize<T>(st, g, w.slot, w.G, w.tmask, u0, ustar, f, dt, 0, f_acc,
                           cfg.masks);
         k_zero<T><<<gm, 256, 0, st>>>(3 * nl, F);
         poison_outputs(g, b, ustar, f, F, resid, Fhist, nl, ns, st);
@@ -1273,7 +1283,7 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
     // outputs (F is written before it) and checks the flags itself
     const bool fold = !resid && !Fhist;
     IBX_PROF_BEGIN(PK_FILL);
-    launch_finalize<T>(gfin, st, g, w.slot, w.G, w.tmask, u0, ustar, f, dt, 1, f_acc, cfg.masks,
+    launch_finalize<T>(st, g, w.slot, w.G, w.tmask, u0, ustar, f, dt, 1, f_acc, cfg.masks,
                        fold ? b->flag : nullptr, F, 3 * nl);
     IBX_PROF_END();
     if (resid) {
@@ -1391,8 +1401,6 @@ static void adjoint_step_t(const Grid& g, const BatchedCfg& cfg, const ib_marker
     // the records of Ubar: the loop's U^d and D, 3 nl each, are free here
     static_assert(sizeof(typename Vec4<T>::type) == 4 * sizeof(T), "4 nl values in 6 nl");
     typename Vec4<T>::type* const ub4 = reinterpret_cast<typename Vec4<T>::type*>(w.s.ud);
-    const int64_t nfin = (int64_t)g.nbox * (g.box / TILE) * g.box;
-    const unsigned gfin = (unsigned)(nfin < 65535 ? (nfin > 0 ? nfin : 1) : 65535);
     // Ui = J a_f and the position gradient of S^T with F^m; a_f = dt G after the first step
     if (af)
         launch_interp<T, P, 3>(cfg, st, g, nl, 0.0, w.items, w.nitems, af, nullptr, nullptr,
@@ -1414,7 +1422,7 @@ static void adjoint_step_t(const Grid& g, const BatchedCfg& cfg, const ib_marker
     // G = J^T Ubar = a_u, which the next step takes from the slots
     w.s.f4 = ub4;
     launch_spread<T, P>(cfg, st, g, w, b, 0);
-    launch_finalize<T>(gfin, st, g, w.slot, w.G, w.tmask, gu0, gu0, nullptr, 1.0, 1, 0,
+    launch_finalize<T>(st, g, w.slot, w.G, w.tmask, gu0, gu0, nullptr, 1.0, 1, 0,
                        cfg.masks);
 }
 

@@ -942,3 +942,36 @@ def test_buckets_are_stable_at_every_pass_size(dev, nl):
     assert torch.equal(b.perm.long(), order)
     assert torch.equal(b.tile_offs.long(),
                        torch.searchsorted(tile[order], torch.arange(4097, device=dev)))
+
+
+@pytest.mark.parametrize("dtype,masks", [("f32", False), ("f32", True), ("f64", False)])
+def test_finalize_in_every_box_layout(dev, dtype, masks):
+    """The last pass takes one to eight planes and one or two cells a thread by the
+    box and its ghost width, and streams its stores or not: f and ustar have the
+    same bits in all of them, in place and out of place, and ghosts keep theirs."""
+    import torch
+
+    import paper_2408_14140_amd as ibx
+    announce(f"finalize layouts {dtype} masks={masks}")
+    tdt = torch.float32 if dtype == "f32" else torch.float64
+    u0 = np.random.default_rng(41).normal(size=(3, 48, 48, 48))
+    got = []
+    for box in (8, 16, 24, 48):
+        for ngrow in (1, 2):
+            wl = W.make_workload("fin", 48, box, ngrow, 4, 2, np.array([7.3, 9.1]), seed=3,
+                                 nmodes=1, K=1, cover_all=True, with_field=False)
+            wl.u0 = u0
+            c = Case(wl, dev)
+            for inplace in (False, True):
+                plan = ibx.Plan(4, tdt, 2, row_masks=masks)
+                b = ibx.bucket(c.dl, c.dm, 4)
+                u = c.u0_boxes(tdt)
+                out = u if inplace else torch.full_like(u, np.nan)
+                ustar, f, _ = plan.multidirect_force(c.dl, c.parts, c.dm, b, 2, wl.dt, u, ustar=out,
+                                                     f=torch.full_like(u, np.nan))
+                got.append((c.to_global(ustar), c.to_global(f)))
+                for t in (ustar, f):
+                    assert int(torch.isfinite(t).sum()) == u0.size
+    assert np.abs(got[0][1]).max() > 0
+    for x, y in got[1:]:
+        assert np.array_equal(x, got[0][0]) and np.array_equal(y, got[0][1])
