@@ -22,8 +22,8 @@
 // tiles.h for the two hot ones):
 //   interp   work item = up to bw markers of one tile; tile + halo of u0 or G
 //            staged in LDS, one thread per marker.
-//   spread   work item = one tile with a non-empty source list, one wavefront.
-//            Result to the compact per-tile G slots.
+//   spread   work item = one tile with a non-empty source list, one wavefront
+//            (two or four with few tiles).  Result to the compact per-tile G slots.
 //   finalize f and ustar = u0 + dt G on every valid cell of the covered boxes,
 //            box-wide rows per workgroup.  No float atomics anywhere.
 #include "octants.h"

@@ -10,8 +10,8 @@
 // with few markers spread each marker over 2 or 4 lanes (one z plane of the
 // stencil each), so all waves of the workgroup share the compute phase.
 //
-// Spreading (one work item = one tile with a non-empty source list, one
-// wavefront).  FP64, and FP32 outside the Jacobi loop and the adjoint: a matrix
+// Spreading (one work item = one tile with a non-empty source list; one
+// wavefront, or two or four with few tiles).  FP64, and FP32 outside the Jacobi loop and the adjoint: a matrix
 // product over the tile's sources, octant by octant on the matrix cores
 // (k_spread_mfma).  FP32 loop and adjoint: lane = one (y, z) row of the tile
 // (P = 4) or one 2 x 2 x 2 block (P = 3), accumulated in registers.  Sources are
