@@ -1249,9 +1249,11 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
     Residuals<T> res{w, resid, st};
     IBX_PROF_BEGIN(PK_INTERP_U0);
     // the interpolations write the force history, and the last one F, in marker
-    // order (the last entry of the history is copied with F's order)
+    // order (the last entry of the history is copied with F's order); without a
+    // step there is neither, and the history has no entry to write
+    T* const first = ns == 1 ? F : ns > 1 ? Fhist : nullptr;
     launch_interp<T, P, 0>(cfg, st, g, nl, dt, w.items, w.nitems, u0, w.G, w.rmask, w.nb_u, w.s,
-                           res.row(), w.queue, ns == 1 ? F : Fhist, b->perm);
+                           res.row(), w.queue, first, b->perm);
     IBX_PROF_END();
     res.add(ns == 0);
     if (ns == 0) {

@@ -246,3 +246,26 @@ def test_adjoint_does_not_depend_on_the_ghost_width(dev, delta, dtype, masks):
     for o in out[1:]:
         for x, y in zip(out[0], o):
             assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("path", [1, 2], ids=["plain", "batched"])
+@pytest.mark.parametrize("delta,dtype", [(3, "f32"), (4, "f64")])
+def test_no_step_writes_no_force_history(dev, path, delta, dtype):
+    """With no step the force history has no entry: whatever lies there keeps its
+    value, F and f are zero and ustar is u0."""
+    import torch
+
+    import paper_2408_14140_amd as ibx
+    announce(f"no step path={path} P={delta} {dtype}")
+    wl = W.make_workload("grad_nostep", 32, 16, 2, delta, 1, np.array([6.3, 7.7]), seed=21,
+                         nmodes=4, K=2, cover_all=True)
+    c = Case(wl, dev)
+    tdt = torch.float64 if dtype == "f64" else torch.float32
+    plan = ibx.Plan(delta, tdt, path)
+    b = ibx.bucket(c.dl, c.dm, delta)
+    u0 = torch.as_tensor(W.to_boxes(wl.u0, c.lev, fill=0.0), device=dev).to(tdt)
+    guard = torch.full((3, c.dm.nl, 3), 7.0, dtype=tdt, device=dev)
+    ustar, f, F = plan.multidirect_force(c.dl, c.parts, c.dm, b, 0, wl.dt, u0, Fhist=guard[1:2])
+    assert (guard == 7.0).all()
+    assert (F == 0).all() and (_valid(c.lev, f) == 0).all()
+    assert torch.equal(_valid(c.lev, ustar), _valid(c.lev, u0))
