@@ -37,7 +37,7 @@ HBM_PEAK_GBS = 8000.0
 # Kernel sources whose hash tags the committed HBM counter summary: the traffic
 # figure is reported only while these are unchanged since the counters were taken.
 TRAFFIC_SOURCES = ("paper_2408_14140_amd/csrc/tiles.h", "paper_2408_14140_amd/csrc/octants.h",
-                   "paper_2408_14140_amd/csrc/batched.hip")
+                   "paper_2408_14140_amd/csrc/queues.h", "paper_2408_14140_amd/csrc/batched.hip")
 TRAFFIC_FILE = "profiles/spread_spheres1000_256_hbm_counters.txt"
 TRAFFIC_FILE_CFG4 = "profiles/loop_spheres20000_512_hbm_counters.txt"
 

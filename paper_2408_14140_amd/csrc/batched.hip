@@ -28,6 +28,7 @@
 //            box-wide rows per workgroup.  No float atomics anywhere.
 #include "octants.h"
 #include "paths.h"
+#include "queues.h"
 
 namespace ibx {
 
@@ -528,9 +529,10 @@ k_fill_lists(int64_t T, const int32_t* __restrict__ src_offs,
 
 
 // Persistent grid of a tile kernel: the workgroups that can be resident at
-// once (optionally capped per CU), a multiple of 8 for the XCD split.
+// once (optionally capped per CU), a multiple of 8 for the XCD split and at
+// least `least`.
 template <auto K, int BLOCK>
-int resident_grid(int ncu, int cap)
+int resident_grid(int ncu, int cap, int least)
 {
     static const int fit = [] {
         int n = 0;
@@ -538,9 +540,7 @@ int resident_grid(int ncu, int cap)
             n = 1;
         return n;
     }();
-    const int per_cu = cap > 0 && cap < fit ? cap : fit;
-    const int grid = ncu * per_cu / NXCD * NXCD;
-    return grid > NXCD ? grid : NXCD;
+    return persistent_grid(ncu, cap > 0 && cap < fit ? cap : fit, least);
 }
 
 // ------------------------------------------------------------------ fill
@@ -929,9 +929,9 @@ static void interp_kernel(const BatchedCfg& cfg, hipStream_t st, const Grid& g, 
                               const int64_t* nbase_u)
 {
     constexpr auto K = k_interp_tiles<T, P, MODE, BW, MASK, TXW>;
-    K<<<resident_grid<K, BW>(cfg.ncu, 0), BW, 0, st>>>(g, nl, dt, items, nitems, u0, G, nbase, s,
-                                                       e2, Fout, perm, vin, gX, use_dv, rmask, queue,
-                                                       nbase_u);
+    K<<<resident_grid<K, BW>(cfg.ncu, 0, SLAB_GRID), BW, 0, st>>>(
+        g, nl, dt, items, nitems, u0, G, nbase, s, e2, Fout, perm, vin, gX, use_dv, rmask, queue,
+        nbase_u);
 }
 
 template <typename T, int P, int MODE, bool MASK, int TXW>
@@ -1030,7 +1030,7 @@ template <auto K, int W = 1, typename T>
 static void spread_with(const BatchedCfg& cfg, hipStream_t st, const Grid& g,
                         const BatchedWs<T>& w, const ib_buckets* b, int use_dv)
 {
-    K<<<resident_grid<K, 64 * W>(cfg.ncu, cfg.wgs_s), 64 * W, 0, st>>>(
+    K<<<resident_grid<K, 64 * W>(cfg.ncu, cfg.wgs_s, QUEUE_GRID), 64 * W, 0, st>>>(
         w.sent, w.nactive, b->src_idx, g, w.s, w.G, w.rmask, w.tmask, use_dv, w.queue);
 }
 

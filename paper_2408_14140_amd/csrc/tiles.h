@@ -34,16 +34,6 @@
 // halo cells shared by neighbouring items are fetched into one L2, not eight.
 // The grid is a multiple of 8 workgroups.  Which workgroup computes an item
 // never changes the item's result.
-constexpr int NXCD = 8;
-
-// Spreading queues: the entries of an XCD's slab are dealt to NQ queues, each
-// served by the XCD's workgroups of one residue, with a counter in a cache
-// line of its own.  (A device-scope atomic on a line that many workgroups
-// share takes about 12 ns: with one counter per XCD the spreading of
-// spheres1000_256 went from 80 to 96 us, with one line for all to 443 us.)
-constexpr int NQ = 8;
-constexpr int QSTRIDE = 32;         // ints between two counters
-
 struct Slab {
     int begin, end, stride;
 };
@@ -529,7 +519,8 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
 
 // The spreading entries of one workgroup, (slot, tile, first source, end of
 // sources): every NQ-th entry of its XCD's slab of `sent` (ordered by
-// decreasing cost) is its queue's, which nw workgroups share.  next() gives
+// decreasing cost) is its queue's, which nw workgroups share (queue_share; the
+// grid has QUEUE_GRID workgroups or more).  next() gives
 // entries me, 2 nw - 1 - me and 2 nw + me of the queue, then what its counter
 // hands out, and zeros at the end.  A ticket is drawn one entry before it is
 // used (lane 0 holds it till then), so nothing waits for the atomic.  Dealing
@@ -539,29 +530,22 @@ k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
 struct SpreadQueue {
     const int4* entries;
     int32_t* counter;
-    int me, nw, count, r, tick;
+    QueueShare share;
+    int r, tick;
     __device__ SpreadQueue(const int4* sent, int32_t* queue, int n_act)
     {
-        const int per = (n_act + NXCD - 1) / NXCD;
-        const int x = blockIdx.x % NXCD, nwg = gridDim.x / NXCD, wg = blockIdx.x / NXCD;
-        const int sub = wg % NQ, slab = min(n_act, (x + 1) * per) - x * per;
-        me = wg / NQ;
-        nw = (nwg - sub + NQ - 1) / NQ;
-        count = slab > sub ? (slab - sub + NQ - 1) / NQ : 0;
-        entries = sent + x * per + sub;
-        counter = queue + (x * NQ + sub) * QSTRIDE;
+        share = queue_share(blockIdx.x, gridDim.x, n_act);
+        entries = sent + share.first;
+        counter = queue + share.queue * QSTRIDE;
         r = tick = 0;
     }
     __device__ int4 next()
     {
-        const int q = r == 0   ? me
-                      : r == 1 ? 2 * nw - 1 - me
-                      : r == 2 ? 2 * nw + me
-                               : 3 * nw + __builtin_amdgcn_readfirstlane(tick);
-        if (r >= 2 && 3 * nw < count && threadIdx.x == 0)
+        const int q = queue_entry(share, r, __builtin_amdgcn_readfirstlane(tick));
+        if (r >= 2 && 3 * share.nw < share.count && threadIdx.x == 0)
             tick = atomicAdd(counter, 1);
         ++r;
-        return q < count ? entries[(int64_t)q * NQ] : make_int4(0, 0, 0, 0);
+        return q < share.count ? entries[(int64_t)q * NQ] : make_int4(0, 0, 0, 0);
     }
 };
 

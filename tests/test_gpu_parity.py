@@ -975,3 +975,32 @@ def test_finalize_in_every_box_layout(dev, dtype, masks):
     assert np.abs(got[0][1]).max() > 0
     for x, y in got[1:]:
         assert np.array_equal(x, got[0][0]) and np.array_equal(y, got[0][1])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("delta", [3, 4])
+@pytest.mark.parametrize("k", [12, 232], ids=["few", "many"])
+def test_the_spreading_residency_moves_no_bit(dev, k, delta, dtype):
+    """From one spreading workgroup per compute unit, whose queues are long, to as
+    many as fit: the same bits, with few markers (several wavefronts a tile) and
+    with many (one)."""
+    import torch
+
+    import paper_2408_14140_amd as ibx
+    announce(f"spreading residency k={k} P={delta} {dtype}")
+    n, rng = 128, np.random.default_rng(32)
+    wl = W.make_workload(f"residency{k}", n, 32, 2, delta, 2, np.full(k, 16.0),
+                         centres=rng.uniform(0.1, 0.9, (k, 3)), cover_all=True, with_field=False)
+    wl.u0 = rng.normal(size=(3, n, n, n))
+    c = Case(wl, dev)
+    tdt = torch.float32 if dtype == "f32" else torch.float64
+    b = ibx.bucket(c.dl, c.dm, delta)
+    u = torch.as_tensor(W.to_boxes(wl.u0, c.lev, fill=0.0), device=dev).to(tdt)
+    ref = None
+    for wgs in (0, 1, 2, 5, 32):
+        plan = ibx.Plan(delta, tdt, 2, spread_wgs_per_cu=wgs)
+        got = plan.multidirect_force(c.dl, c.parts, c.dm, b, 2, wl.dt, u)
+        ref = ref or got
+        f, r = c.to_global(got[1]), c.to_global(ref[1])
+        assert np.abs(r).max() > 0 and np.array_equal(f, r)
+        assert torch.equal(got[2], ref[2])
