@@ -63,6 +63,15 @@ struct Mat<double> {
     }
 };
 
+// Memory accesses of the wavefront's lanes before this point stay before those after
+// it (no instruction: one wavefront's LDS accesses are carried out in order).
+__device__ inline void wave_order()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Number of set bits of m below this lane's.
 __device__ inline int bits_below(uint64_t m)
 {
@@ -116,7 +125,9 @@ struct Octants {
         kq = lane >> 4;
     }
 
-    // Before a batch: zero records, and lists of the zero record.
+    // Before a batch: zero records, and lists of the zero record.  The lanes clear
+    // places that other lanes fill next, so the stores must keep their order: the
+    // wavefront's LDS does by itself, the fence makes the compiler do so as well.
     __device__ void clear()
     {
         typedef T Fill __attribute__((ext_vector_type(16 / sizeof(T)), may_alias));
@@ -126,6 +137,7 @@ struct Octants {
             reinterpret_cast<Fill*>(rec)[lane + 64 * q] = Fill(T(0));
         constexpr uint32_t z = 64 * S * sizeof(T);
         reinterpret_cast<Fill4*>(list)[lane] = Fill4(z | z << 16);
+        wave_order();
     }
 
     // Which halves of the tile a lane's source reaches.
