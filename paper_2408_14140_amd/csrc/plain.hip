@@ -178,12 +178,14 @@ k_interp_quads(Grid g, int64_t nl, const double* __restrict__ x, const double* _
     for (int k = 0; k < P; ++k) {
         const int az = quad_int<2>(at[k]);
         const T wz = quad<2>(w[k]);
+        // a component of a large box has more cells than 32 bits count
+        const int64_t plane = (int64_t)(az >> 1) * (g.ext * g.ext);
         if (mine && !out) {
 #pragma unroll
             for (int j = 0; j < P; ++j) {
                 const T* const b = az & 1 ? (ay[j] & 1 ? base[1][1] : base[1][0])
                                           : (ay[j] & 1 ? base[0][1] : base[0][0]);
-                const T* const p = b + ((az >> 1) * g.ext + (ay[j] >> 1)) * g.ext;
+                const T* const p = b + plane + (ay[j] >> 1) * g.ext;
                 const T wt = wy[j] * wz;
                 acc0 += p[0] * wt;
                 acc1 += p[g.cstride] * wt;

@@ -228,3 +228,50 @@ def test_spheres20000_512_full_loop(dev, cfg4):
     rhs = (Fh * mo.dv[mo.pid][:, None]).sum(axis=0)
     scale = (np.abs(Fh) * mo.dv[mo.pid][:, None]).sum(axis=0)
     assert np.all(np.abs(lhs - rhs) <= TOL32 * scale)
+
+
+@pytest.mark.parametrize("delta", [3, 4])
+def test_interp_in_a_box_beyond_32_bits(dev, delta):
+    """One box of 1288^3 cells with two ghosts: a component has 2.16e9 values, so
+    the last planes lie past 2^31.  Markers there and at the low end, whose
+    stencils wrap, against sums over the same few cells in FP64."""
+    import torch
+
+    import paper_2408_14140_amd as ibx
+    announce(f"interp in a 1288^3 box P={delta}")
+    n, g, h = 1288, 2, 1.0
+    e = n + 2 * g
+    assert e ** 3 > 2 ** 31
+    lev = W.Level(n=(n, n, n), h=h, lo=(0.0, 0.0, 0.0), periodic=(1, 1, 1), box=n, ngrow=g,
+                  box_coords=np.zeros((1, 3), np.int32), lut=np.zeros(1, np.int32))
+    rng = np.random.default_rng(3)
+    X = np.concatenate([rng.uniform(n - 4.0, n, (20, 3)), rng.uniform(0.0, 4.0, (20, 3)),
+                        rng.uniform(0.0, n, (20, 3))])
+    # stencil cells and weights of every marker in FP64
+    base = np.floor(X / h - (0.5 if delta == 4 else 0.0)).astype(np.int64) - 1
+    cell = base[:, None, :] + np.arange(delta)[None, :, None]          # [l][P][axis]
+    r = np.abs(X[:, None, :] / h - cell - 0.5)
+    if delta == 3:
+        w = np.where(r <= 0.5, (1 + np.sqrt(np.maximum(1 - 3 * r * r, 0))) / 3,
+                     (5 - 3 * r - np.sqrt(np.maximum(1 - 3 * (1 - r) ** 2, 0))) / 6)
+    else:
+        w = np.where(r <= 1, (3 - 2 * r + np.sqrt(np.maximum(1 + 4 * r - 4 * r * r, 0))) / 8,
+                     (5 - 2 * r - np.sqrt(np.maximum(-7 + 12 * r - 4 * r * r, 0))) / 8)
+    cell %= n
+    ix, iy, iz = (cell[:, :, a] for a in range(3))
+    shape = (len(X), delta, delta, delta)
+    ix, iy, iz = (np.broadcast_to(a, shape) for a in
+                  (ix[:, None, None, :], iy[:, None, :, None], iz[:, :, None, None]))
+    # one value per cell, the same for cells that several markers share
+    val = [np.cos(0.7 * ix + 1.3 * iy + 0.4 * iz + c).astype(np.float32) for c in range(3)]
+    u = torch.full((1, 3, e, e, e), float("nan"), dtype=torch.float32, device=dev)
+    idx = [torch.as_tensor(np.ascontiguousarray(a + g), device=dev) for a in (iz, iy, ix)]
+    for c in range(3):
+        u[0, c].index_put_(tuple(idx), torch.as_tensor(val[c], device=dev))
+    wt = w[:, :, None, None, 2] * w[:, None, :, None, 1] * w[:, None, None, :, 0]
+    ref = np.stack([(v.astype(np.float64) * wt).sum((1, 2, 3)) for v in val], 1)
+    m = ibx.markers_from(X[:, 0], X[:, 1], X[:, 2], np.zeros(len(X), np.int32), np.ones(1),
+                         np.array([0, len(X)]), dev)
+    U = ibx.interp(ibx.device_level(lev, dev), m, delta, u)
+    torch.cuda.synchronize()
+    assert rel(U.cpu().numpy(), ref) <= 1e-5
