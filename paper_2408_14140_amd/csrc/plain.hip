@@ -332,18 +332,26 @@ k_spread_list(Grid g, const double* __restrict__ x, const double* __restrict__ y
             const double X[3] = {x[l], y[l], z[l]};
             const T sc = (T)(dv[pid[l]] * g.inv_h3);
             const T F0 = F[3 * l] * sc, F1 = F[3 * l + 1] * sc, F2 = F[3 * l + 2] * sc;
+            // a coordinate that is not finite, or past the integers, has no stencil:
+            // its distance to the first cell is then outside the kernel's branches
+            bool near = true;
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 const double sa = grid_coord(g, a, X[a]);
                 const int b = stencil_base<P>(sa);
+                const T r = (T)(sa - (double)b - 0.5);
+                near = near && r >= T(P == 4 ? 1.0 : 0.5) && r <= T(P == 4 ? 2.0 : 1.5);
                 T w[P];
-                axis_weights_r<T, P>((T)(sa - (double)b - 0.5), w);
+                axis_weights_r<T, P>(r, w);
                 int q = g.periodic[a] ? wrapi(b, g.n[a]) - lo[a] : b - lo[a];
                 if (g.periodic[a] && q > TILE - 1)
                     q -= g.n[a];
                 oct.put(reach, a, q, w, g.periodic[a] && g.n[a] == TILE);
             }
-            oct.put_force(reach, F0, F1, F2);
+            if (near)
+                oct.put_force(reach, F0, F1, F2);
+            else
+                reach = typename Oct::Reach();
         }
         oct.make_lists(reach);
         __syncthreads();

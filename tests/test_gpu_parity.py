@@ -1004,3 +1004,31 @@ def test_the_spreading_residency_moves_no_bit(dev, k, delta, dtype):
         f, r = c.to_global(got[1]), c.to_global(ref[1])
         assert np.abs(r).max() > 0 and np.array_equal(f, r)
         assert torch.equal(got[2], ref[2])
+
+
+@pytest.mark.parametrize("dtype", ["f32", "f64"])
+@pytest.mark.parametrize("delta", [3, 4])
+def test_markers_without_a_place_spread_nothing(dev, delta, dtype):
+    """On a periodic grid a marker with a coordinate that is not finite, or past the
+    integers, lies in some tile's list without a flag: it adds nothing, and the
+    cells of its tile keep the sum of the others."""
+    import torch
+
+    import oracle as O
+    import paper_2408_14140_amd as ibx
+    announce(f"markers without a place P={delta} {dtype}")
+    wl = small_workload(32, 16, delta, 1, 4)
+    c = Case(wl, dev)
+    tdt = torch.float64 if dtype == "f64" else torch.float32
+    F = np.random.default_rng(8).normal(size=(c.m.nl, 3))
+    pos = [np.array(a) for a in (c.m.x, c.m.y, c.m.z)]
+    bad = np.arange(5, c.m.nl, 7)
+    for k, l in enumerate(bad):
+        pos[k % 3][l] = (np.nan, np.inf, 1e300)[(k // 3) % 3]
+    m = ibx.markers_from(*pos, c.m.pid, c.m.dv, c.m.offs, dev)
+    b = ibx.bucket(c.dl, m, delta)
+    assert int(b.flag.abs().max()) == 0
+    f = ibx.spread(c.dl, m, b, delta, torch.as_tensor(F, device=dev).to(tdt))
+    torch.cuda.synchronize()
+    F[bad] = 0.0
+    assert c.field_rel(f, O.spread(c.g, delta, c.m, F)) <= (TOL64 if dtype == "f64" else TOL32)
