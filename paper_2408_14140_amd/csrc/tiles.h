@@ -84,6 +84,21 @@ __device__ inline void item_base(const Grid& g, int t, int k, const int32_t* __r
     }
 }
 
+// Waves per SIMD that the registers of the interpolation have to allow (1: the
+// compiler's own choice), for 256-marker items of one tile.  FP32: five with the
+// field of the first step, seven with row masks (what the unmasked kernel has).
+// FP64 with the 3-point kernel: five, as many as the LDS lets run; by itself the
+// compiler takes 100 registers, four waves (142 us a launch on 1000 spheres in
+// 256^3, 134 with five).
+constexpr int interp_waves(int bytes, int P, int mode, int bw, bool mask, int txw)
+{
+    if (bw != 256 || txw != TILE || mode >= 3)
+        return 1;
+    if (bytes == 8)
+        return P == 3 && mode == 1 && !mask ? 5 : 1;
+    return mask ? 7 : mode == 0 ? 5 : 1;
+}
+
 // mode 0: field = u0 (box layout): D = (U^d - J u0)/dt, F = D.
 // mode 1: field = G (slots): F += D - J G.
 // mode 2: field = G (slots): residual only.
@@ -95,12 +110,9 @@ __device__ inline void item_base(const Grid& g, int t, int k, const int32_t* __r
 //         fields of spheres64_128 they took 13 us each, four a call of three steps.
 // e2 (nullable) receives the sum of dV |U^d - J u^(m)|^2 over the markers of each
 // item, by a fixed tree.
-// (FP32 with the row masks, 256-marker items of one tile: registers capped at
-// the unmasked kernel's seven waves per SIMD.)
 template <typename T, int P, int MODE, int BW, bool MASK = false, int TXW = TILE>
 __global__ void __launch_bounds__(BW)
-__attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && BW == 256 && TXW == TILE
-                                        ? (MODE >= 3 ? 1 : MASK ? 7 : MODE == 0 ? 5 : 1) : 1, 8)))
+__attribute__((amdgpu_waves_per_eu(interp_waves(sizeof(T), P, MODE, BW, MASK, TXW), 8)))
 k_interp_tiles(Grid g, int64_t nl, double dt, const Item* __restrict__ items,
                const int32_t* __restrict__ nitems, const T* __restrict__ u0,
                const T* __restrict__ G, const int64_t* __restrict__ nbase, MarkerData<T> s,
