@@ -26,6 +26,8 @@
 //            (two or four with few tiles).  Result to the compact per-tile G slots.
 //   finalize f and ustar = u0 + dt G on every valid cell of the covered boxes,
 //            box-wide rows per workgroup.  No float atomics anywhere.
+#include <type_traits>
+
 #include "octants.h"
 #include "paths.h"
 #include "queues.h"
@@ -583,15 +585,9 @@ struct Pair<double> {
     typedef double type __attribute__((ext_vector_type(2)));
 };
 
-// Store of the finalize, streamed (nothing here is read again by this kernel)
-// or plain.  In place, streaming leaves more of the next loop's inputs in the
-// caches (interp_u0 of spheres1000_256: 137 us after streamed stores, 155 after
-// plain ones).  Out of place in FP32, box rows end inside a 32-byte sector, and
-// streamed pieces of a sector reach memory apart where the L2 joins plain ones
-// (finalize of spheres1000_256: 262 us plain, 301 streamed).  FP64 rows are
-// whole sectors: streamed (spheres8_256: 447 us, plain 455).
-// (A template parameter: the compiler merges the two stores of a branch at run
-// time into one plain store.)
+// Store of the finalize, streamed (nothing here is read again by this kernel) or
+// plain (finalize_form).  A template parameter: the compiler merges the two stores
+// of a branch at run time into one plain store.
 template <bool STREAM, typename V>
 __device__ inline void put(V v, V* p)
 {
@@ -601,12 +597,17 @@ __device__ inline void put(V v, V* p)
         *p = v;
 }
 
+// Order of a cell's accesses in k_finalize: the loads of all components first, or
+// component by component, the force before u*; APART_DENSE (out of place) has one
+// store of u* for the cells with force and without.
+enum FinalizeOrder { LOADS_FIRST = 0, APART = 1, APART_DENSE = 2 };
+
 // Last step of Algorithm 1 on every valid cell of the covered boxes:
 // f = G^ns and ustar = u0 + dt G^ns, with G = 0 on tiles no marker reaches
 // (and everywhere when use_g is 0) and on the slot rows whose bit in the
 // tile's row mask (tilemask, indexed by tile) is clear.  One workgroup per
 // (box, row of tiles in y, z plane): box-wide x rows, so the box layout is
-// written in long runs.  (As many z planes as give each thread a cell.)
+// written in long runs.  (As many z planes as finalize_planes gives.)
 // In place (ustar == u0) only the cells whose force is not exactly zero are
 // read and rewritten (u0 + dt 0 = u0): inside the tiles that have a force
 // slot, most cells lie outside every stencil.  With f_acc, f += G^ns instead,
@@ -614,7 +615,7 @@ __device__ inline void put(V v, V* p)
 // on the cells without force (copy).  With flag (nullable) raised (a flagged
 // bucket set), f and ustar are NaN on every such cell instead, and so is
 // Fp[0 .. nF) (the marker forces, written before this kernel).
-template <typename T, bool F_ACC, bool MASK, bool STREAM>
+template <typename T, bool F_ACC, bool MASK, bool STREAM, int ORDER>
 __global__ void __launch_bounds__(256)
 k_finalize(Grid g, const int32_t* __restrict__ slot, const T* __restrict__ G,
            const uint64_t* __restrict__ tilemask, const T* u0, T* ustar, T* __restrict__ f,
@@ -656,6 +657,26 @@ k_finalize(Grid g, const int32_t* __restrict__ slot, const T* __restrict__ G,
                                 (lx + g.ngrow);
             const int64_t go =
                 (int64_t)s * 3 * TILE_CELLS + (lx & 7) + TILE * (yy + TILE * (cz & 7));
+            if constexpr (ORDER != LOADS_FIRST) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    const int64_t o = off + c * g.cstride;
+                    const T v = s >= 0 ? G[go + c * TILE_CELLS] : T(0);
+                    if (f && !F_ACC)
+                        put<STREAM, T>(v, &f[o]);
+                    else if (f && v != T(0))
+                        f[o] += v;
+                    if (!ustar)
+                        continue;
+                    if (ORDER == APART_DENSE)
+                        put<STREAM, T>(v != T(0) ? u0[o] + tdt * v : u0[o], &ustar[o]);
+                    else if (v != T(0))
+                        put<STREAM, T>(u0[o] + tdt * v, &ustar[o]);
+                    else if (copy)
+                        put<STREAM, T>(u0[o], &ustar[o]);
+                }
+                continue;
+            }
             // every load before the first store: the stores may alias u0, so
             // a load behind one would wait for it
             T v[3], a[3];
@@ -775,62 +796,137 @@ k_finalize_pairs(Grid g, const int32_t* __restrict__ slot, const T* __restrict__
     }
 }
 
+// How the last pass stores, and in which order.
+struct FinalizeForm {
+    bool pairs, stream;
+    int order, planes;
+};
+
 // z planes of one tile that a workgroup of 256 takes: as many as have a thread a
-// cell (or pair of cells), up to the tile's eight, from `least`.  With one plane (two
-// in pairs) whatever the box, half the threads had no cell in boxes of 16: the channel
-// 96 x 160 x 64 with an odd ghost width took 16.5 us, now 12.6 (with plain stores).
-static int finalize_planes(int per_plane, int least)
+// cell (or pair of cells), up to the tile's eight.  With one plane (two in pairs)
+// whatever the box, half the threads had no cell in boxes of 16: the channel 96 x 160
+// x 64 with an odd ghost width took 16.5 us, now 12.6 (with plain stores).  FP64 with
+// ghosts stays at the least from boxes of 16 on: the loop of four spheres in 256^3,
+// one ghost, boxes of 16, takes 591 us, 677 with two planes.
+static int finalize_planes(bool pairs, int bytes, const Grid& g)
 {
-    int n = least;
+    const int per_plane = TILE * g.box / (pairs ? 2 : 1);
+    int n = pairs ? 2 : 1;
+    if (bytes == 8 && g.ngrow > 0 && g.box >= 16)
+        return n;
     while (n < TILE && 2 * n * per_plane <= 256)
         n *= 2;
     return n;
 }
 
-template <typename T, bool F_ACC, bool MASK, bool STREAM>
-static void finalize_kernel(bool pairs, hipStream_t st, const Grid& g, const int32_t* slot,
-                            const T* G, const uint64_t* tilemask, const T* u0, T* ustar, T* f,
-                            double dt, int use_g, int copy, const int32_t* flag, T* Fp, int64_t nF)
-{
-    const int planes = finalize_planes(TILE * g.box / (pairs ? 2 : 1), pairs ? 2 : 1);
-    const int64_t items = (int64_t)g.nbox * (g.box / TILE) * (g.box / planes);
-    const unsigned grid = (unsigned)(items < 65535 ? (items > 0 ? items : 1) : 65535);
-    if (pairs)
-        k_finalize_pairs<T, F_ACC, MASK, STREAM><<<grid, 256, 0, st>>>(
-            g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF, planes);
-    else
-        k_finalize<T, F_ACC, MASK, STREAM><<<grid, 256, 0, st>>>(
-            g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF, planes);
-}
-
-// With flag, the kernel also stands in for the flag check of the outputs
-// (ustar, f and Fp[0 .. nF)).
+// The rule, from loops of two steps on 128^3 to 256^3 with boxes of 8 to 64, ghost
+// widths of 0 to 4 and 4 to 1000 spheres (dense: 64 cells a marker or fewer, where
+// most cells have force):
+// * Plain stores in FP32, out of place, where rows are not whole 32-byte sectors, so
+//   that the L2 joins what rows share, and
+//   - the fields, with the loop's data of about 512 bytes a marker, take up to 1.6
+//     times the 256 MiB of the memory-side cache, where the next pass finds the lines:
+//     four spheres on 192^3, two ghosts (363 MB), 100 us plain, 148 streamed; 150
+//     spheres on 256^3 in boxes of 64 (724 MB), 305 and 281; with whole sectors (no
+//     ghosts), 150 spheres on 256^3, 209 and 163; or
+//   - a dense loop in pairs has rows of one line of 128 bytes to one and a quarter whose
+//     ghosts leave less than a sector between them: 1000 spheres, two ghosts, boxes of
+//     32 645 us plain, 662 streamed, of 40 577 and 581; of 24 606 and 592, of 48 562
+//     and 551; four ghosts, boxes of 32, 683 and 679; or
+//   - it is a level of the particle order, whose fields the next level reads: 1000
+//     spheres 3332 us, 3383 streamed.
+// * Pairs, and in place in FP32: all loads first (1000 spheres on 256^3 in place 514
+//   us, 529 component by component).
+// * Cell by cell out of place: component by component, the streamed pieces of a row
+//   closer together.  FP64, four spheres on 256^3, one ghost: 403 us, 495 with the
+//   loads first.  Dense, with one store for the cells with force and without (1000
+//   spheres in FP32 590 us, 678 with two), else with two (four spheres 254, 292 with
+//   one).
+// * In place in FP64 cell by cell: dense, loads first (300 spheres 409 us, 457 apart),
+//   else apart (60 spheres 163, 191 with the loads first).
+// * Cell by cell, fields of up to 64 MiB out of place or 256 MiB in place: loads first
+//   (FP64, four spheres, one ghost: 64^3 52 us, 54 apart; 128^3 in place 61 and 63).
 template <typename T>
-static void launch_finalize(hipStream_t st, const Grid& g, const int32_t* slot,
-                            const T* G, const uint64_t* tilemask, const T* u0, T* ustar, T* f,
-                            double dt, int use_g, int f_acc, int masks,
-                            const int32_t* flag = nullptr, T* Fp = nullptr, int64_t nF = 0)
+static FinalizeForm finalize_form(const Grid& g, int64_t nl, bool level, const T* u0,
+                                  const T* ustar, const T* f)
 {
-    const int copy = ustar && ustar != u0;
+    const bool copy = ustar && ustar != u0;
     // pairs of cells: rows start on even elements when ngrow is even, and the
     // pair loads and stores need the fields aligned to two elements
     const uintptr_t am = 2 * sizeof(T) - 1;
     const bool pairs = (g.ngrow & 1) == 0 && !((uintptr_t)u0 & am) &&
                        !((uintptr_t)ustar & am) && !((uintptr_t)f & am);
-    // streamed stores in FP64 and in place; out of place in FP32 plain ones (k_finalize_pairs)
-    const bool stream = sizeof(T) == 8 || !copy;
-#define IBX_FINALIZE(ACC, MASK)                                                                \
-    (stream ? finalize_kernel<T, ACC, MASK, true> : finalize_kernel<T, ACC, MASK, sizeof(T) == 8>)( \
-        pairs, st, g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, Fp, nF)
-    if (f_acc && masks)
-        IBX_FINALIZE(true, true);
-    else if (f_acc)
-        IBX_FINALIZE(true, false);
-    else if (masks)
-        IBX_FINALIZE(false, true);
+    const int planes = finalize_planes(pairs, sizeof(T), g);
+    const bool dense = (int64_t)g.nbox * g.box * g.box * g.box <= 64 * nl;
+    const int row = g.box * (int)sizeof(T), gap = 2 * g.ngrow * (int)sizeof(T);
+    const int64_t fields = (f ? 3 : 2) * (int64_t)sizeof(T) * g.nbox * g.bstride;
+    const bool cached = fields + 512 * nl <= (int64_t)(1.6 * (1 << 28));
+    const bool joined = pairs && dense && gap < 32 && row >= 128 && row <= 160;
+    if (sizeof(T) == 4 && copy && gap % 64 != 0 && (cached || joined || level))
+        return {pairs, false, LOADS_FIRST, planes};
+    const bool small = fields <= (int64_t(1) << (copy ? 26 : 28));
+    if (pairs || small || (!copy && (sizeof(T) == 4 || dense)))
+        return {pairs, true, LOADS_FIRST, planes};
+    return {pairs, true, copy && dense ? APART_DENSE : APART, planes};
+}
+
+// With flag, the kernel also stands in for the flag check of the outputs
+// (ustar, f and Fp[0 .. nF)).
+template <typename T, bool F_ACC, bool MASK>
+static void finalize_kernel(const FinalizeForm& form, hipStream_t st, const Grid& g,
+                            const int32_t* slot, const T* G, const uint64_t* tilemask,
+                            const T* u0, T* ustar, T* f, double dt, int use_g,
+                            const int32_t* flag, T* Fp, int64_t nF)
+{
+    const int copy = ustar && ustar != u0;
+    const int planes = form.planes;
+    const int64_t items = (int64_t)g.nbox * (g.box / TILE) * (g.box / planes);
+    const unsigned grid = (unsigned)(items < 65535 ? (items > 0 ? items : 1) : 65535);
+#define IBX_FINALIZE(...)                                                                      \
+    __VA_ARGS__<<<grid, 256, 0, st>>>(g, slot, G, tilemask, u0, ustar, f, dt, use_g, copy, flag, \
+                                      Fp, nF, planes)
+    if constexpr (sizeof(T) == 4) {
+        if (!form.stream) {
+            if (form.pairs)
+                IBX_FINALIZE(k_finalize_pairs<T, F_ACC, MASK, false>);
+            else
+                IBX_FINALIZE(k_finalize<T, F_ACC, MASK, false, LOADS_FIRST>);
+            return;
+        }
+    }
+    if (form.pairs)
+        IBX_FINALIZE(k_finalize_pairs<T, F_ACC, MASK, true>);
+    else if (form.order == LOADS_FIRST)
+        IBX_FINALIZE(k_finalize<T, F_ACC, MASK, true, LOADS_FIRST>);
+    else if (form.order == APART)
+        IBX_FINALIZE(k_finalize<T, F_ACC, MASK, true, APART>);
     else
-        IBX_FINALIZE(false, false);
+        IBX_FINALIZE(k_finalize<T, F_ACC, MASK, true, APART_DENSE>);
 #undef IBX_FINALIZE
+}
+
+template <typename T>
+static void launch_finalize(const BatchedCfg& cfg, hipStream_t st, const Grid& g, int64_t nl,
+                            const int32_t* slot, const T* G, const uint64_t* tilemask,
+                            const T* u0, T* ustar, T* f, double dt, int use_g, int f_acc,
+                            const int32_t* flag = nullptr, T* Fp = nullptr, int64_t nF = 0)
+{
+    const FinalizeForm form = finalize_form(g, nl, cfg.products != 0, u0, ustar, f);
+    const int masks = cfg.masks;
+    auto run = [&](auto acc, auto mask) {
+        finalize_kernel<T, acc.value, mask.value>(form, st, g, slot, G, tilemask, u0, ustar, f,
+                                                  dt, use_g, flag, Fp, nF);
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    if (f_acc && masks)
+        run(yes, yes);
+    else if (f_acc)
+        run(yes, no);
+    else if (masks)
+        run(no, yes);
+    else
+        run(no, no);
 }
 
 template <typename T>
@@ -1238,8 +1334,7 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
     BatchedWs<T> w = carve_batched<T>(g, nl, cfg.bw, ws, ws_bytes, &need);
     const unsigned gm = (unsigned)((nl + 255) / 256 > 0 ? (nl + 255) / 256 : 1);
     if (nl == 0) {
-        launch_finalize<T>(st, g, w.slot, w.G, w.tmask, u0, ustar, f, dt, 0, f_acc,
-                          cfg.masks);
+        launch_finalize<T>(cfg, st, g, nl, w.slot, w.G, w.tmask, u0, ustar, f, dt, 0, f_acc);
         if (resid)
             k_zero<double><<<1, 64, 0, st>>>(ns + 1, resid);
         poison_outputs(g, b, ustar, f, F, resid, Fhist, nl, ns, st);
@@ -1258,8 +1353,7 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
     res.add(ns == 0);
     if (ns == 0) {
         // no iteration: ustar = u0, f = 0, F = 0
-        launch_finalize<T>(st, g, w.slot, w.G, w.tmask, u0, ustar, f, dt, 0, f_acc,
-                          cfg.masks);
+        launch_finalize<T>(cfg, st, g, nl, w.slot, w.G, w.tmask, u0, ustar, f, dt, 0, f_acc);
         k_zero<T><<<gm, 256, 0, st>>>(3 * nl, F);
         poison_outputs(g, b, ustar, f, F, resid, Fhist, nl, ns, st);
         return launch_status();
@@ -1285,7 +1379,7 @@ static int run_batched(const Grid& g, const BatchedCfg& cfg, const ib_particles*
     // outputs (F is written before it) and checks the flags itself
     const bool fold = !resid && !Fhist;
     IBX_PROF_BEGIN(PK_FILL);
-    launch_finalize<T>(st, g, w.slot, w.G, w.tmask, u0, ustar, f, dt, 1, f_acc, cfg.masks,
+    launch_finalize<T>(cfg, st, g, nl, w.slot, w.G, w.tmask, u0, ustar, f, dt, 1, f_acc,
                        fold ? b->flag : nullptr, F, 3 * nl);
     IBX_PROF_END();
     if (resid) {
@@ -1424,8 +1518,7 @@ static void adjoint_step_t(const Grid& g, const BatchedCfg& cfg, const ib_marker
     // G = J^T Ubar = a_u, which the next step takes from the slots
     w.s.f4 = ub4;
     launch_spread<T, P>(cfg, st, g, w, b, 0);
-    launch_finalize<T>(st, g, w.slot, w.G, w.tmask, gu0, gu0, nullptr, 1.0, 1, 0,
-                       cfg.masks);
+    launch_finalize<T>(cfg, st, g, nl, w.slot, w.G, w.tmask, gu0, gu0, nullptr, 1.0, 1, 0);
 }
 
 int tile_adjoint_step(const Grid& g, int P, ib_prec prec, const BatchedCfg& cfg,

@@ -1032,3 +1032,41 @@ def test_markers_without_a_place_spread_nothing(dev, delta, dtype):
     torch.cuda.synchronize()
     F[bad] = 0.0
     assert c.field_rel(f, O.spread(c.g, delta, c.m, F)) <= (TOL64 if dtype == "f64" else TOL32)
+
+
+@pytest.mark.parametrize("dtype,masks", [("f32", False), ("f64", False), ("f64", True)])
+@pytest.mark.parametrize("k", [4, 180], ids=["sparse", "dense"])
+def test_finalize_of_large_fields_in_every_order(dev, k, dtype, masks):
+    """With fields beyond the caches the last pass streams its stores, and with an odd
+    ghost width goes component by component, by the number of markers and in place or
+    not: f and ustar have the same bits with every ghost width, and ghosts keep
+    theirs."""
+    import torch
+
+    import paper_2408_14140_amd as ibx
+    announce(f"finalize of large fields k={k} {dtype} masks={masks}")
+    tdt = torch.float32 if dtype == "f32" else torch.float64
+    n, rng = 208, np.random.default_rng(43)
+    xc = rng.uniform(0.1, 0.9, (k, 3))
+    gen = torch.Generator(device=dev).manual_seed(44)
+    u0 = torch.randn((3, n, n, n), dtype=tdt, device=dev, generator=gen)
+    ref = None
+    for ngrow in (0, 1, 2, 3):
+        wl = W.make_workload(f"finlarge{k}", n, 16, ngrow, 4, 1, np.full(k, 16.0), seed=3,
+                             centres=xc, cover_all=True, with_field=False)
+        c = Case(wl, dev)
+        assert (c.dm.nl * 64 >= n ** 3) == (k == 180)
+        plan = ibx.Plan(4, tdt, 2, row_masks=masks)
+        b = ibx.bucket(c.dl, c.dm, 4)
+        u = torch.full(c.dl.field_shape(), float("nan"), dtype=tdt, device=dev)
+        ibx.field_to_boxes(c.dl, u0, u)
+        for out in (torch.full_like(u, float("nan")), u):
+            ustar, f, _ = plan.multidirect_force(c.dl, c.parts, c.dm, b, 1, wl.dt, u, ustar=out,
+                                                 f=torch.full_like(u, float("nan")))
+            got = [ibx.field_from_boxes(c.dl, t, torch.zeros_like(u0)) for t in (ustar, f)]
+            for t in (ustar, f):
+                assert int(torch.isfinite(t).sum()) == u0.numel()
+            if ref is None:
+                ref = got
+                assert float(got[1].abs().max()) > 0
+            assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
