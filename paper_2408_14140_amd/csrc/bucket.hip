@@ -212,10 +212,14 @@ void scan_exclusive2(const int32_t* in0, int32_t* out0, const int32_t* in1, int3
 
 constexpr int RS_THREADS = 256;
 // Elements of a workgroup and thread: fewer for fewer elements, so that a pass fills
-// the chip (124 K elements in tiles of 2048: 61 workgroups).
+// the chip (124 K elements in tiles of 2048: 61 workgroups).  Bucketing in 256^3 with
+// the smaller and the larger number, in us: 393 K markers 115 (2), 113 (4), 118 (8);
+// 524 K 126 (2), 120 (4), 124 (8); 655 K 129 (4), 130 (8); 786 K 137 (4), 135 (8);
+// 1.5 M 196 (4), 184 (8).
+constexpr int64_t RS_LIMIT[3] = {1 << 17, 3 << 17, 5 << 17};    // of 1, 2 and 4 a thread
 __host__ __device__ inline int rs_rounds(int64_t n_max)
 {
-    return n_max <= (1 << 17) ? 1 : n_max <= (1 << 19) ? 2 : n_max <= (1 << 21) ? 4 : 8;
+    return n_max <= RS_LIMIT[0] ? 1 : n_max <= RS_LIMIT[1] ? 2 : n_max <= RS_LIMIT[2] ? 4 : 8;
 }
 constexpr int RS_WAVES = RS_THREADS / 64;
 
@@ -454,8 +458,9 @@ static int64_t rs_blocks(int64_t n_max)
 size_t radix_workspace(int64_t n_max)
 {
     int64_t nb = rs_blocks(n_max > 0 ? n_max : 1);
-    for (int64_t n = 1 << 17; n < n_max && n <= 1 << 21; n <<= 2)
-        nb = nb > rs_blocks(n) ? nb : rs_blocks(n);
+    for (int64_t n : RS_LIMIT)
+        if (n < n_max && rs_blocks(n) > nb)
+            nb = rs_blocks(n);
     return align_up(sizeof(int32_t) * 256 * nb) + align_up(sizeof(int32_t) * 256);
 }
 

@@ -1070,3 +1070,10 @@ def test_finalize_of_large_fields_in_every_order(dev, k, dtype, masks):
                 ref = got
                 assert float(got[1].abs().max()) > 0
             assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+
+
+@pytest.mark.parametrize("nl", [393216, 393217, 655360, 655361])
+def test_buckets_are_stable_where_the_pass_size_changes(dev, nl):
+    """The stable order by tile on both sides of each change of the elements a thread
+    (beyond 131072 markers)."""
+    test_buckets_are_stable_at_every_pass_size(dev, nl)
