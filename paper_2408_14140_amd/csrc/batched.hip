@@ -1102,22 +1102,34 @@ static void launch_interp(const BatchedCfg& cfg, hipStream_t st, const Grid& g, 
 }
 
 // Wavefronts that share a tile in the spreading.  One, unless the call's tiles
-// leave the chip idle: with W of them a workgroup takes W times the staging memory,
-// so that 3 (W = 4) or 7 (W = 2) tiles fit on a CU at once.  How many tiles have
-// markers is known on the device only; the host has their number on the grid, and
-// that of the markers, 27 a tile or more.  Loops of five steps on 256^3 (256 CUs),
-// spheres of 16 cells, W = 1, 2, 4 in us: 24 spheres, 19 K markers, 185, 158, 144;
-// 96, 77 K, 410, 379, 428; 160, 129 K, 495, 499, 587; 320, 621, 671, 841 (4-point
-// kernel; the 3-point one 151, 131, 120; 357, 336, 369; 445, 438, 497; 532, 559,
-// 690).  Small spheres cross at the same marker counts, clumps of overlapping
-// spheres, with fewer tiles, later.  The matrix products, whose wavefronts do more
-// at a time, cross two against one earlier: FP64, 4-point, 24 spheres 265, 247,
-// 235; 48, 39 K markers, 442, 414, 417; 96, 588, 596, 630.
-static int spread_waves(const BatchedCfg& cfg, const Grid& g, int64_t nl, bool products)
+// leave the chip idle: with W of them a workgroup takes W times the staging memory.
+// Of the FP32 row and block kernels 3 (W = 4) or 7 (W = 2) tiles then fit on a CU at
+// once, of the matrix products 2 or 5 (FP64; 10 with one wavefront), 4 or 9 (FP32).
+// How many tiles have markers is known on the device only; the host has their number
+// on the grid, and that of the markers, 27 a tile or more.  Loops of five steps on
+// 256^3 (256 CUs), spheres of 16 cells, W = 1, 2, 4 in us: 24 spheres, 19 K markers,
+// 185, 158, 144; 96, 77 K, 410, 379, 428; 160, 129 K, 495, 499, 587; 320, 621, 671, 841
+// (4-point kernel; the 3-point one 151, 131, 120; 357, 336, 369; 445, 438, 497; 532,
+// 559, 690).  Small spheres cross at the same marker counts, clumps of overlapping
+// spheres, with fewer tiles, later.
+// The matrix products, whose wavefronts do more at a time, cross two against one
+// earlier: FP64, 4-point, 24 spheres 265, 247, 235; 48, 39 K markers, 442, 414, 417;
+// 96, 588, 596, 630.  In FP64 two are ahead once more where the tiles are several
+// rounds of what is resident, and one again where the tiles are many: W = 1 and 2,
+// 160 spheres, 129 K markers, 3-point 728 and 739, 4-point 831 and 844; 240, 193 K, 852
+// and 838, 994 and 989; 320, 257 K, 961 and 942, 1158 and 1136; 640, 515 K, 1343 and
+// 1337, 1732 and 1697; 700 of 8 to 32 cells, 648 K, 1324 and 1308, 1757 and 1742, but
+// 700 in clumps, 599 K, 1019 and 1010, 1373 and 1420; 850, 796 K, 1565 and 1548, 2031
+// and 2032; 1200, 1.13 M, 1996 and 2011, 2605 and 2653.  (With one, 300 spheres took
+// 747 us in FP64, 3-point, where the block kernel in place of the products took 732.)
+static int spread_waves(const BatchedCfg& cfg, const Grid& g, int64_t nl, bool products, int P,
+                        bool f64)
 {
     const int64_t cu = cfg.ncu;
     if (nl <= 128 * cu || g.ntiles <= 3 * cu)
         return 4;
+    if (products && f64 && nl > 640 * cu && nl <= (P == 3 ? 3584 : 2048) * cu)
+        return 2;
     return nl <= (products ? 256 : 512) * cu || g.ntiles <= 7 * cu ? 2 : 1;
 }
 
@@ -1136,7 +1148,7 @@ static void spread_kernel(const BatchedCfg& cfg, hipStream_t st, const Grid& g,
 {
     if constexpr (sizeof(T) == 4) {
         if (!cfg.products) {
-            const int waves = spread_waves(cfg, g, w.nl, false);
+            const int waves = spread_waves(cfg, g, w.nl, false, P, false);
             if (waves == 4)
                 return spread_with<k_spread_waves<T, P, MASK, 4>, 4>(cfg, st, g, w, b, use_dv);
             if (waves == 2)
@@ -1152,7 +1164,7 @@ static void spread_kernel(const BatchedCfg& cfg, hipStream_t st, const Grid& g,
             return;
         }
     }
-    const int waves = spread_waves(cfg, g, w.nl, true);
+    const int waves = spread_waves(cfg, g, w.nl, true, P, sizeof(T) == 8);
     if (waves == 4)
         return spread_with<k_spread_mfma_waves<T, P, MASK, 4>, 4>(cfg, st, g, w, b, use_dv);
     if (waves == 2)

@@ -1077,3 +1077,43 @@ def test_buckets_are_stable_where_the_pass_size_changes(dev, nl):
     """The stable order by tile on both sides of each change of the elements a thread
     (beyond 131072 markers)."""
     test_buckets_are_stable_at_every_pass_size(dev, nl)
+
+
+@pytest.mark.parametrize("masks", [False, True], ids=["", "masks"])
+@pytest.mark.parametrize("delta", [3, 4])
+def test_every_share_of_a_tile_spreads_the_same_bits_in_fp64(dev, delta, masks):
+    """The matrix products of FP64 plans take four, two, one and two wavefronts a tile
+    as the markers grow: the first spheres give the same bits on their cells whatever is
+    placed far from them."""
+    import oracle as O
+    import torch
+
+    import paper_2408_14140_amd as ibx
+    announce(f"FP64 spread by marker count P={delta} masks={masks}")
+    cu = torch.cuda.get_device_properties(dev).multi_processor_count
+    n, per = 128, 804                       # markers of a sphere of 16 cells
+    counts = [c * cu // per for c in (100, 200, 400, 1000)]
+    rng = np.random.default_rng(35)
+    near = 0.25 + np.clip(rng.normal(0.0, 0.05, (12, 3)), -0.1, 0.1)
+    far = np.concatenate([rng.uniform(0.1, 0.9, (counts[-1], 2)),
+                          rng.uniform(0.62, 0.9, (counts[-1], 1))], 1)
+    up, om = (rng.normal(0.0, s, (12 + counts[-1], 3)) for s in (0.1, 1.0))
+    u0 = rng.normal(size=(3, n, n, n))
+    ref = None
+    for k in counts:
+        xc = np.concatenate([near, far[:k]])
+        d = np.full(len(xc), 16.0 / n)
+        lev = W.make_workload("bits", n, 32, 2, delta, 2, d * n, centres=xc, cover_all=True,
+                              with_field=False).level
+        m = O.build_markers(xc, d, lev.h)
+        dl = ibx.device_level(lev, dev)
+        dm = ibx.markers_from(m.x, m.y, m.z, m.pid, m.dv, m.offs, dev)
+        plan = ibx.Plan(delta, torch.float64, 2, row_masks=masks)
+        b = ibx.bucket(dl, dm, delta)
+        u = torch.as_tensor(W.to_boxes(u0, lev, fill=0.0), device=dev)
+        parts = ibx.particles(xc, d, up[:len(xc)], om[:len(xc)], dev)
+        _, f, F = plan.multidirect_force(dl, parts, dm, b, 2, 0.5 / n, u)
+        got = W.from_boxes(f.cpu().numpy(), lev)[:, :60], F[:int(m.offs[12])].cpu().numpy()
+        ref = ref or got
+        assert np.abs(ref[0]).max() > 0
+        assert np.array_equal(got[0], ref[0]) and np.array_equal(got[1], ref[1])
