@@ -214,3 +214,68 @@ def test_whole_time_step(dev, dtype):
     # here the projection's input carries the loop's own error (up to tol),
     # which the solve amplifies like any error of D V
     assert rel(p1.cpu().numpy(), ref_p) <= tol * _kappa(n)
+
+
+def _plane_wave(n, kk, dev):
+    """Phase of the wave (kk[0] x + kk[1] y + kk[2] z) on the nodes of one z plane, as a
+    function of the plane, and half a cell's advance along each axis."""
+    import torch
+    th = 2.0 * np.pi / n * torch.arange(n, dtype=torch.float64, device=dev)
+    half = [np.pi * k / n for k in kk]
+    return (lambda k: (kk[0] * th)[None, :] + (kk[1] * th)[:, None] + kk[2] * th[k]), half
+
+
+def _grad_wave(half, h):
+    """G cos = amp sin at the cell centre, per axis."""
+    return [-2.0 * np.sin(half[d]) / h * np.prod([np.cos(half[e]) for e in range(3) if e != d])
+            for d in range(3)]
+
+
+@pytest.mark.parametrize("n,dtype", [(256, "f64"), (512, "f32"), (512, "f64"), (1024, "f32"),
+                                     (1024, "f64")])
+def test_long_lines_predict_a_plane_wave(dev, n, dtype):
+    """u = a cos, p = cos of one mode, a chosen so that the convective term of the wave
+    vanishes on the grid: every term of Eq. (31) is then known, and the solve divides
+    by one known factor (the three-field passes of grids beyond what the oracle
+    solves in a test)."""
+    import torch
+
+    import paper_2408_14140_amd as ibx
+    announce(f"prediction of a plane wave n={n} {dtype}")
+    tdt = torch.float64 if dtype == "f64" else torch.float32
+    h, rho, mu, dt, grav = 1.0 / n, 1.3, 0.02, 0.5 / n, (0.3, -9.81, 0.5)
+    kk = (3, 2, 1)
+    phase, half = _plane_wave(n, kk, dev)
+    # the flux differences of a plane wave: sum over d of a_d cos^2 sin(2 x half_d) = 0
+    q = np.array([np.cos(x) ** 2 * np.sin(2 * x) for x in half])
+    a = np.cross(q, [0.2, 1.0, -0.4])
+    a /= np.linalg.norm(a)
+    gp = _grad_wave(half, h)
+    lam = sum((2.0 * np.cos(2 * x) - 2.0) / h ** 2 for x in half)
+    visc = 0.5 * mu / rho * dt
+    u = torch.empty((3, n, n, n), dtype=tdt, device=dev)
+    p = torch.empty((n, n, n), dtype=tdt, device=dev)
+    for k in range(n):
+        p[k] = torch.cos(phase(k)).to(tdt)
+        c = torch.cos(phase(k) + sum(half))
+        for d in range(3):
+            u[d, k] = (a[d] * c).to(tdt)
+    fl = ibx.Fluid(n, h, tdt, dev)
+    fl.predict(u, p, rho, mu, dt, grav, out=u)
+    torch.cuda.synchronize()
+    # rounding: u of size 1, and dt times differences of values of size 1 over h (u u, p)
+    # and over h^2 with visc (visc / h^2 is below 4 here)
+    tol = TOL64 if dtype == "f64" else TOL32
+    err = 0.0
+    for k in range(n):
+        c, s = torch.cos(phase(k) + sum(half)), torch.sin(phase(k) + sum(half))
+        for d in range(3):
+            want = (a[d] * c * (1.0 + visc * lam) - dt / rho * gp[d] * s) / (1.0 - visc * lam)
+            err = max(err, float((u[d, k].double() - (want + dt * grav[d])).abs().max()))
+    assert err <= tol
+
+
+@pytest.mark.parametrize("n", [256, 1024])
+def test_long_lines_recover_a_known_pressure_in_fp64(dev, n):
+    """The FP64 projection at the sizes that the test above leaves out."""
+    test_long_lines_recover_a_known_pressure(dev, n, "f64")
