@@ -829,10 +829,12 @@ static int finalize_planes(bool pairs, int bytes, const Grid& g)
 //     four spheres on 192^3, two ghosts (363 MB), 100 us plain, 148 streamed; 150
 //     spheres on 256^3 in boxes of 64 (724 MB), 305 and 281; with whole sectors (no
 //     ghosts), 150 spheres on 256^3, 209 and 163; or
-//   - a dense loop in pairs has rows of one line of 128 bytes to one and a quarter whose
-//     ghosts leave less than a sector between them: 1000 spheres, two ghosts, boxes of
-//     32 645 us plain, 662 streamed, of 40 577 and 581; of 24 606 and 592, of 48 562
-//     and 551; four ghosts, boxes of 32, 683 and 679; or
+//   - a loop in pairs, of 108 cells a marker or fewer, has rows of one line of 128 bytes
+//     to one and a quarter whose ghosts leave less than a sector between them: 1000
+//     spheres, two ghosts, boxes of 32 645 us plain, 662 streamed, of 40 577 and 581;
+//     of 24 606 and 592, of 48 562 and 551; four ghosts, boxes of 32, 683 and 679; five
+//     steps, boxes of 32, 200 spheres (104 cells a marker) 470 and 480, 150 (110) 442
+//     and 439; or
 //   - it is a level of the particle order, whose fields the next level reads: 1000
 //     spheres 3332 us, 3383 streamed.
 // * Pairs, and in place in FP32: all loads first (1000 spheres on 256^3 in place 514
@@ -857,11 +859,12 @@ static FinalizeForm finalize_form(const Grid& g, int64_t nl, bool level, const T
     const bool pairs = (g.ngrow & 1) == 0 && !((uintptr_t)u0 & am) &&
                        !((uintptr_t)ustar & am) && !((uintptr_t)f & am);
     const int planes = finalize_planes(pairs, sizeof(T), g);
-    const bool dense = (int64_t)g.nbox * g.box * g.box * g.box <= 64 * nl;
+    const int64_t cells = (int64_t)g.nbox * g.box * g.box * g.box;
+    const bool dense = cells <= 64 * nl;
     const int row = g.box * (int)sizeof(T), gap = 2 * g.ngrow * (int)sizeof(T);
     const int64_t fields = (f ? 3 : 2) * (int64_t)sizeof(T) * g.nbox * g.bstride;
     const bool cached = fields + 512 * nl <= (int64_t)(1.6 * (1 << 28));
-    const bool joined = pairs && dense && gap < 32 && row >= 128 && row <= 160;
+    const bool joined = pairs && cells <= 108 * nl && gap < 32 && row >= 128 && row <= 160;
     if (sizeof(T) == 4 && copy && gap % 64 != 0 && (cached || joined || level))
         return {pairs, false, LOADS_FIRST, planes};
     const bool small = fields <= (int64_t(1) << (copy ? 26 : 28));
