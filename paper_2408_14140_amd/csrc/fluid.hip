@@ -444,8 +444,11 @@ k_fft_x_inv(const Cx<T>* __restrict__ spec, T* __restrict__ out)
     }
 }
 
-// y and z passes: C neighbouring columns per workgroup, so that an access
-// moves C consecutive values (128 bytes where the LDS allows it).
+// y and z passes: C neighbouring columns per workgroup, so that an access moves C
+// consecutive values: 128 bytes, or what the LDS allows on lines above 256 (64 bytes
+// at 512 and 32 at 1024 in FP32).  Grids up to 64 take 8 columns, which is 64 bytes in
+// FP32: 16 would make 192 workgroups of a field's 33 columns on 64^3, fewer than
+// compute units.
 template <typename T, int LOGN>
 struct Cols {
     static constexpr int C = (LOGN <= 6 ? 8 : LOGN <= 8 ? 16 : LOGN == 9 ? 8 : 4) /

@@ -636,7 +636,7 @@ __device__ inline uint64_t drop_low_bits(uint64_t m, int s)
 // visits exactly those sources in list order.  Each lane holds one (y, z) row
 // of the tile and stores it straight to the slot (rows are contiguous there).
 // LDS stays near 5.9 KB so that 24 or more workgroups fit on a CU.
-// EU: waves per SIMD that the registers allow.  6 cost four spilled registers,
+// EU: waves per SIMD that the registers allow.  6 cost two spilled registers,
 // which pays only where more than five run (a plan that allows more than 20
 // workgroups per CU; loop of spheres1000_256 1.090 ms against 1.098): with the
 // default 16, 5 waves take 103 us a launch there and 6 take 110.
@@ -861,7 +861,8 @@ k_spread_tiles(const int4* __restrict__ sent, const int32_t* __restrict__ nactiv
 // whose stencil covers less of an 8-cell row; the rows are faster for the
 // 4-point kernel.  A block cell just outside the stencil reads a zero pad.
 // LDS stays near 6.5 KB so that 24 workgroups fit on a CU.
-// (6 waves per SIMD: the residency that the latency-bound visit chain wants.)
+// (6 waves per SIMD, at nine spilled registers, twelve with row masks: the residency
+// that the latency-bound visit chain wants.)
 template <typename T, int P, bool MASK>
 __global__ void __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(6, 8)))
 k_spread_blocks(const int4* __restrict__ sent, const int32_t* __restrict__ nactive,
